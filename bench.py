@@ -35,31 +35,6 @@ PROBE_WAVES = (1, 2, 3, 4, 6, 7)                         # waves per SIMD swept 
 PROBE_ITERS = 20000                                      # 256 instructions per iteration
 
 
-# HBM bytes per launch of the 16x16 miter's specialized kernel, from rocprofv3 FETCH_SIZE and
-# WRITE_SIZE (each scaled by what the counter reads for a device copy of known size; summary
-# and commands in profiles/es_specialized_mult16_counters.md).  Valid only for the kernel whose
-# generated source has this SHA-256; any other kernel reports null.
-PROFILED_TRAFFIC = {"source_sha256": "ccfed8e35eb6ab3f4566538fd3ce89de8cf2566bf0f9ba1c2d1a3c6eb9a9df06",
-                    "bytes_per_launch": 1372081}
-
-
-def profiled_traffic(es, c):
-    import hashlib
-    src = es.fastlec_es_specialized_source(c, 3)
-    if PROFILED_TRAFFIC["source_sha256"] == hashlib.sha256(src.encode()).hexdigest():
-        return PROFILED_TRAFFIC["bytes_per_launch"]
-    return None
-
-
-def body_counts(es, c):
-    """(VALU, SALU) instructions of the specialized kernel's per-pass body (2,048 patterns per
-    wave pass), from its generated source; None when the kernel is not one asm block."""
-    import re
-    src = es.fastlec_es_specialized_source(c, 3)
-    m = re.search(r"one asm block: (\d+) VGPRs, (\d+) SGPRs, (\d+) VALU and (\d+) SALU", src)
-    return (int(m.group(3)), int(m.group(4))) if m else None
-
-
 PROBE_VARIANTS = {0: "v_bitop3_b32, three VGPR sources in three banks", 1: "v_bitop3_b32, two VGPRs and an SGPR",
                   2: "v_xor_b32, two VGPRs"}
 
@@ -416,23 +391,23 @@ def main():
     k_mean_s = sum(kernel_ms) / len(kernel_ms) / 1e3
     achieved_np = node_patterns / k_mean_s
     # Roofline of the specialized kernel: executed wave64 VALU instructions per second (the
-    # generated body's count per 2,048-pattern pass times the passes of the space) against the
-    # issue peak, the larger of the published figure and the probe's measurement.
+    # generated pass's count per call times the calls that cover the space; a call evaluates 2^inner
+    # times 2,048 patterns) against the issue peak, the larger of the published figure and the
+    # probe's measurement.
     probe = valu_peak(es, waves=(3, 7), variants=(1, 2))
     peak = max(PEAK_WAVE_INSTR, probe["best_instr_per_s"])
-    counts = body_counts(es, c) if a.kernel == "specialized" else None
-    passes = 1 << max(0, n - 11)
+    counts = es.fastlec_es_native_info(c) if a.kernel == "specialized" else None
     if counts:
-        valu, salu = counts
+        valu, passes = counts["valu"], 1 << max(0, n - 11 - counts["inner"])
         roofline = {"bound": "alu", "achieved": valu * passes / k_mean_s, "peak": peak, "unit": "wave64 VALU instr/s",
                     "frac": valu * passes / k_mean_s / peak,
-                    "traffic": profiled_traffic(es, c),
+                    "traffic": None,
                     "kernel_ms_mean": k_mean_s * 1e3, "kernel_ms_median": k_ms,
-                    "valu_per_pass": valu, "salu_per_pass": salu, "passes": passes,
+                    "valu_per_call": valu, "inner_inputs": counts["inner"], "calls": passes,
+                    "waves_per_simd": counts["waves_per_simd"],
                     "peak_spec": PEAK_WAVE_INSTR, "peak_probe": probe["best_instr_per_s"],
-                    "note": "achieved = VALU instructions of the generated per-pass body x 2^(n-11) passes / mean "
-                            "kernel time (HIP events); the loop adds about 6 VALU per pass (SQ_INSTS_VALU, profiles/); "
-                            "peak = max(256 CU x 2 wave64 instr/clk x 2.4 GHz, v_bitop3 probe)"}
+                    "note": "achieved = VALU instructions of the generated pass x its 2^(n-11-inner) calls / mean "
+                            "kernel time (HIP events); peak = max(256 CU x 2 wave64 instr/clk x 2.4 GHz, v_bitop3 probe)"}
     else:
         roofline = {"bound": "alu", "achieved": achieved_np, "peak": PEAK_NODE_PATTERNS, "unit": "node*patterns/s",
                     "frac": achieved_np / PEAK_NODE_PATTERNS, "traffic": None, "kernel_ms_mean": k_mean_s * 1e3,
@@ -456,9 +431,10 @@ def main():
         "roofline": roofline,
         "roofline_algorithmic": {"achieved": achieved_np, "one_op_per_and_peak": PEAK_NODE_PATTERNS,
                                  "unit": "node*patterns/s", "ratio": achieved_np / PEAK_NODE_PATTERNS,
-                                 "and_gates_per_valu_instr": N / counts[0] if counts else None,
+                                 "and_gates_per_valu_instr": N * (1 << counts["inner"]) / counts["valu"] if counts else None,
                                  "note": "N*2^n per launch over a peak of one int32 lane-op per AND gate per 32 "
-                                         "patterns; above 1 because one LUT instruction evaluates several AND gates"},
+                                         "patterns; above 1 because one LUT instruction evaluates several AND gates "
+                                         "and one call shares what its 2^inner input assignments have in common"},
         "load_ms": load_ms,
         "compile_ms": compile_ms,
         "all_steps_equivalent": bool(for_each_ok),

@@ -54,7 +54,8 @@ enum { FASTLEC_EQUIVALENT = 0, FASTLEC_NONEQUIVALENT = 1 };
 enum {
     FASTLEC_KERNEL_AUTO = 0,        /* specialized for large spaces, interpreter otherwise */
     FASTLEC_KERNEL_INTERP = 1,      /* generic interpreter, node values in LDS */
-    FASTLEC_KERNEL_SPECIALIZED = 2, /* straight-line kernel compiled for this circuit, values in VGPRs */
+    FASTLEC_KERNEL_SPECIALIZED = 2, /* straight-line machine code of this circuit, values in VGPRs (a native
+                                       kernel; compiled by hipRTC where that does not fit) */
     FASTLEC_KERNEL_INTERP_HBM = 3   /* generic interpreter, node values in device memory */
 };
 
@@ -105,7 +106,8 @@ typedef struct {
                                     EQUIVALENT (2^n for a full check), range start .. cex when not */
     uint64_t next_word;          /* resume point: first word not known to be clean */
     double plan_ms;              /* host planning time (at load) */
-    double compile_ms;           /* specialized-kernel compile time paid by this call (0 if cached) */
+    double compile_ms;           /* hipRTC compile time paid by this call (0 if cached, and for native
+                                    kernels: those are encoded by the library, not compiled) */
     double kernel_ms;            /* device time of the simulation kernel(s) */
     double queued_ms;            /* server: admission - submission (host steady clock); 0 otherwise */
     double latency_ms;           /* server: completion - submission (host steady clock); 0 otherwise */
@@ -351,8 +353,15 @@ int fastlec_es_valu_probe(int device, uint32_t variant, uint32_t waves_per_simd,
 
 /* ---- diagnostics (no GPU needed) ------------------------------------------ */
 
+/* The native kernel that a check of the whole space of c runs on (built if needed; see
+ * FASTLEC_KERNEL_SPECIALIZED).  *inner = inner inputs (one call of its pass evaluates 2^inner times
+ * 2,048 patterns), *valu = VALU instructions of a call, *waves = waves per SIMD it is launched with.
+ * Outputs may be NULL.  FASTLEC_ERR_UNSUPPORTED when the circuit has none. */
+int fastlec_es_native_info(const fastlec_es_circuit *c, uint32_t *inner, uint32_t *valu, uint32_t *waves);
+
 /* Compile the specialized kernel of c for gfx950 with hipRTC (cached per circuit and by
- * source hash) without running it.  waves_per_eu: occupancy target 1..8.  Outputs may be
+ * source hash) without running it, and build its native kernel; nothing is compiled for a circuit
+ * that already has one.  waves_per_eu: occupancy target 1..8.  Outputs may be
  * NULL: *compile_ms = compile time paid by this call (0 when cached), *code_bytes = size of
  * the code object. */
 int fastlec_es_compile_specialized(const fastlec_es_circuit *c, int waves_per_eu, double *compile_ms,

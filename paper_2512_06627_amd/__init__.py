@@ -104,6 +104,8 @@ SIGNATURES = [
                                                       ctypes.POINTER(ctypes.c_size_t)]),
     ("fastlec_es_compile_specialized_many", ctypes.c_int, [ctypes.POINTER(_P), ctypes.c_size_t, ctypes.c_int,
                                                            ctypes.POINTER(ctypes.c_double)]),
+    ("fastlec_es_native_info", ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(ctypes.c_uint32),
+                                              ctypes.POINTER(ctypes.c_uint32)]),
     ("fastlec_es_specialized_source", ctypes.c_size_t, [_P, ctypes.c_int, ctypes.c_char_p, ctypes.c_size_t]),
     ("fastlec_es_host_replay", ctypes.c_int, [_P, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64,
                                               ctypes.POINTER(ctypes.c_uint32)]),
@@ -281,6 +283,15 @@ def fastlec_es_compile_specialized_many(circuits, waves_per_eu: int = 3) -> floa
     if rc:
         _raise(rc)
     return ms.value
+
+
+def fastlec_es_native_info(circuit: Circuit) -> dict:
+    """Inner inputs, VALU instructions per call of the pass and waves per SIMD of the native kernel."""
+    i, v, w = ctypes.c_uint32(), ctypes.c_uint32(), ctypes.c_uint32()
+    rc = lib().fastlec_es_native_info(circuit.handle, ctypes.byref(i), ctypes.byref(v), ctypes.byref(w))
+    if rc:
+        _raise(rc)
+    return {"inner": i.value, "valu": v.value, "waves_per_simd": w.value}
 
 
 def fastlec_es_specialized_source(circuit: Circuit, waves_per_eu: int = 2) -> str:

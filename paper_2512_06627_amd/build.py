@@ -37,12 +37,35 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _native_template(verbose: bool) -> str:
+    """Object file that embeds the code object of native/es_native.hip, the host kernel of the
+    passes that the library encodes at run time."""
+    code = os.path.join(BUILD, "es_native.co")
+    cmd = [HIPCC, "-x", "hip"] + DEVICE + COMMON + ["--cuda-device-only", "--no-gpu-bundle-output", "-fuse-cuid=none",
+           "-c", os.path.join(HERE, "native", "es_native.hip"), "-o", code]
+    src = os.path.join(BUILD, "es_native_template.S")
+    obj = src + ".o"
+    with open(src, "w") as f:
+        f.write('.section .rodata\n.globl fes_native_template\n.hidden fes_native_template\n'
+                '.globl fes_native_template_end\n.hidden fes_native_template_end\n.balign 64\n'
+                f'fes_native_template:\n.incbin "{code}"\nfes_native_template_end:\n.byte 0\n'
+                '.section .note.GNU-stack,"",@progbits\n')
+    for c in (cmd, ["gcc", "-c", src, "-o", obj]):
+        if verbose:
+            print(" ".join(c), flush=True)
+        r = subprocess.run(c, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"native template failed\n{r.stdout}\n{r.stderr}")
+    return obj
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     os.makedirs(OUT_DIR, exist_ok=True)
     srcs = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".cpp", ".hip")))
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), srcs))
+        template = ex.submit(_native_template, verbose)
+        objs = list(ex.map(lambda s: _compile(s, verbose), srcs)) + [template.result()]
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs + [
         "-L/opt/rocm/lib", "-lhiprtc", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"]

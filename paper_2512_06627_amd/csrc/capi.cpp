@@ -102,6 +102,31 @@ bool use_specialized(Circuit& c, const fastlec_es_options& o, const HwRange& r) 
     return model_specialized_ms(luts, patterns) + kCompileMargin * model_compile_ms(luts) < t_interp;
 }
 
+// The specialized kernel of a check is the native one unless a switch that only hipRTC kernels
+// have asks for those.
+bool native_allowed() {
+    if (!native_tier()) return false;
+    for (const char* v : {"FASTLEC_ES_JIT_EMIT", "FASTLEC_ES_JIT_SCALAR", "FASTLEC_ES_JIT_DIST", "FASTLEC_ES_JIT_BANKS",
+                          "FASTLEC_ES_JIT_VGPR_CAP", "FASTLEC_ES_JIT_WAVES", "FASTLEC_ES_JIT_BLOCK"})
+        if (std::getenv(v)) return false;
+    return true;
+}
+
+// The native kernel that a check of `span` half-words at a time (out of `patterns` patterns) runs
+// on, or null.  SPECIALIZED always takes it.  AUTO takes one that is built when it is expected to
+// be faster than the interpreter, and builds one when that pays (native_pays); a caller that
+// fixes the interpreter's schedule keeps the interpreter until a kernel is built.
+std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o, uint64_t span, double patterns) {
+    if (o.kernel != FASTLEC_KERNEL_SPECIALIZED && o.kernel != FASTLEC_KERNEL_AUTO) return nullptr;
+    if (!native_allowed()) return nullptr;
+    const NativeTier* t = native_tier();
+    if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) return t->get(c, span, 0.0);
+    if (o.words_per_thread || o.wg_size) return nullptr;
+    const double interp = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
+    if (auto k = t->ready(c, span)) return t->run_ms(*k, patterns) < interp ? k : nullptr;
+    return native_pays(c, interp, patterns, 1.0) ? t->get(c, span, 0.5) : nullptr;
+}
+
 void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) {
     if (o.kernel < FASTLEC_KERNEL_AUTO || o.kernel > FASTLEC_KERNEL_INTERP_HBM)
         throw Error{kErrInvalid, "unknown kernel"};
@@ -109,22 +134,24 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
     hipStream_t stream = o.hip_stream ? (hipStream_t)o.hip_stream : dev.stream;
     HwRange full = range_of(c.plan1.num_inputs, o.begin_word, o.end_word);
     std::memset(out, 0, sizeof(*out));
-    const bool spec = use_specialized(c, o, full);
-    std::shared_ptr<JitKernel> jk;
+    // Without a deadline or cancel flag the whole range is one launch.  With one, the range
+    // runs as ascending chunks with the host checking between chunks.
+    const bool chunked = o.deadline_s > 0 || o.cancel_flag;
+    uint64_t chunk = full.end - full.begin;
+    if (chunked) chunk = std::max<uint64_t>(4096, (full.end - full.begin) / 256);
+    const double t_start = now_ms();
+    const double patterns = 32.0 * (double)(full.end - full.begin);
     double compile_ms = 0;
-    if (spec) jk = jit_kernel(c, specialized_waves_per_eu(), &compile_ms);
+    std::shared_ptr<JitKernel> jk = native_kernel(c, o, std::min(chunk, full.end - full.begin), patterns);
+    const bool native = jk != nullptr;
+    const bool spec = native || use_specialized(c, o, full);
+    if (spec && !native) jk = jit_kernel(c, specialized_waves_per_eu(), &compile_ms);
     Schedule sch;
     if (!spec) {
         std::vector<Circuit*> one{&c};
         sch = default_schedule(dev, one, &o, full.end - full.begin);
         if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
     }
-    // Without a deadline or cancel flag the whole range is one launch.  With one, the range
-    // runs as ascending chunks with the host checking between chunks.
-    const bool chunked = o.deadline_s > 0 || o.cancel_flag;
-    const double t_start = now_ms();
-    uint64_t chunk = full.end - full.begin;
-    if (chunked) chunk = std::max<uint64_t>(4096, (full.end - full.begin) / 256);
     double kernel_ms = 0;
     uint64_t best = ~0ull;
     uint64_t done_to = full.begin;
@@ -161,9 +188,9 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
     fill_result(c, full, best, out);
     out->kernel_ms = kernel_ms;
     out->compile_ms = compile_ms;
-    const double patterns = 32.0 * (double)(full.end - full.begin);
-    out->predicted_ms = spec ? model_specialized_ms(c.lut_program().lut_steps, patterns)
-                             : model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
+    out->predicted_ms = native ? native_tier()->run_ms(*jk, patterns)
+                        : spec ? model_specialized_ms(c.lut_program().lut_steps, patterns)
+                               : model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
 }
 
 }  // namespace
@@ -271,7 +298,44 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             v.push_back(const_cast<Circuit*>(&cs[i]->c));
             rs.push_back(range_of(v.back()->plan1.num_inputs, 0, 0));
         }
-        // Cones the runtime model gives to the specialized kernel (AUTO only) run as their own
+        // Native kernels first: every cone with kernel SPECIALIZED, and under AUTO those that have one
+        // or for which one pays.  They are built on host threads in parallel and run as one launch
+        // per register tier.
+        std::vector<size_t> nat;
+        std::vector<std::shared_ptr<JitKernel>> nk;
+        std::vector<uint8_t> is_nat(k, 0);
+        if (native_allowed() && (o.kernel == FASTLEC_KERNEL_SPECIALIZED ||
+                                 (o.kernel == FASTLEC_KERNEL_AUTO && !o.words_per_thread && !o.wg_size &&
+                                  batch_jit_mode() == 1))) {
+            const NativeTier* t = native_tier();
+            std::vector<size_t> want;
+            for (size_t i = 0; i < k; ++i) {
+                Circuit& c = *v[i];
+                const uint64_t span = rs[i].end - rs[i].begin;
+                const double patterns = 32.0 * (double)span;
+                if (o.kernel == FASTLEC_KERNEL_AUTO) {
+                    // A grouped launch's share of a cone, without the launch itself.
+                    const double interp = model_interp_share_ms(c.interp_gates(), c.interp_rows(), patterns);
+                    const std::shared_ptr<JitKernel> have = t->ready(c, span);
+                    if (have ? t->share_ms(*have, patterns) >= interp
+                             : !native_pays(c, interp, patterns, 1.0 / 8)) continue;
+                }
+                want.push_back(i);
+            }
+            std::vector<std::shared_ptr<JitKernel>> got(want.size());
+            parallel_for(want.size(), [&](size_t j) {
+                const uint64_t span = rs[want[j]].end - rs[want[j]].begin;
+                if (o.kernel == FASTLEC_KERNEL_AUTO) got[j] = t->ready(*v[want[j]], span);
+                if (!got[j]) got[j] = t->get(*v[want[j]], span, o.kernel == FASTLEC_KERNEL_AUTO ? 0.2 : 0.0);
+            });
+            for (size_t j = 0; j < want.size(); ++j) {
+                if (!got[j]) continue;  // its values fit neither registers nor LDS
+                is_nat[want[j]] = 1;
+                nat.push_back(want[j]);
+                nk.push_back(got[j]);
+            }
+        }
+        // Of the others, cones the runtime model gives to the specialized kernel (AUTO only) run as their own
         // launches; the rest share interpreter launches.  Their kernels compile together as
         // hipRTC programs side by side in helper processes, so a cone is a candidate when its
         // predicted saving beats its own part of the group's compile (kCompileMargin on its
@@ -281,6 +345,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
         std::vector<uint8_t> is_spec(k, 0);
         if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) {
             for (size_t i = 0; i < k; ++i) {
+                if (is_nat[i]) continue;
                 is_spec[i] = 1;
                 spec.push_back(i);
             }
@@ -302,6 +367,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             const int helpers = compile_helpers();
             const double fixed_ms = model_group_compile_fixed_ms(helpers);
             for (size_t i = 0; i < k; ++i) {
+                if (is_nat[i]) continue;
                 Circuit& c = *v[i];
                 const double patterns = 32.0 * (double)(rs[i].end - rs[i].begin);
                 const double ti = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
@@ -397,7 +463,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
         std::vector<uint8_t> is_alone(k, 0);
         if (!o.words_per_thread && !o.wg_size)
             for (size_t i = 0; i < k; ++i) {
-                if (is_spec[i]) continue;
+                if (is_spec[i] || is_nat[i]) continue;
                 Circuit& c = *v[i];
                 const double patterns = 32.0 * (double)(rs[i].end - rs[i].begin);
                 if (model_interp_ms(c.interp_gates(), c.interp_rows(), patterns) >= 1.0) {
@@ -413,7 +479,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
         // rows: the waves per SIMD a launch gets), the others by powers of two of their rows.
         std::map<uint32_t, std::vector<size_t>> groups;
         for (size_t i = 0; i < k; ++i) {
-            if (is_spec[i] || is_alone[i]) continue;
+            if (is_spec[i] || is_nat[i] || is_alone[i]) continue;
             const int t = regs_tier_enabled() ? model_interp_tier(v[i]->interp_rows()) : 3;
             if (t < 3) {
                 groups[(uint32_t)t].push_back(i);
@@ -452,7 +518,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             }
         }
         for (size_t i = 0; i < k; ++i)
-            if (!is_spec[i] && !is_alone[i]) out[i].kernel_ms = total_ms;
+            if (!is_spec[i] && !is_nat[i] && !is_alone[i]) out[i].kernel_ms = total_ms;
         auto run_alone = [&](size_t i) {
             std::vector<Circuit*> one{v[i]};
             std::vector<HwRange> r1{rs[i]};
@@ -468,6 +534,20 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                                                   32.0 * (double)(rs[i].end - rs[i].begin));
         };
         for (size_t i : alone) run_alone(i);
+        if (!nat.empty()) {
+            std::vector<HwRange> nr;
+            for (size_t i : nat) nr.push_back(rs[i]);
+            std::vector<uint64_t> best;
+            double ms = 0;
+            native_tier()->run_many(dev, nk, nr, stream, best, &ms);
+            for (size_t j = 0; j < nat.size(); ++j) {
+                const size_t i = nat[j];
+                std::memset(&out[i], 0, sizeof(out[i]));
+                fill_result(*v[i], rs[i], best[j], &out[i]);
+                out[i].kernel_ms = ms;
+                out[i].predicted_ms = native_tier()->run_ms(*nk[j], 32.0 * (double)(rs[i].end - rs[i].begin));
+            }
+        }
         if (compile_job.t.joinable()) compile_job.t.join();
         if (compile_error) std::rethrow_exception(compile_error);
         if (!spec.empty()) {
@@ -525,9 +605,31 @@ int fastlec_es_compile_specialized(const fastlec_es_circuit* c, int waves_per_eu
         if (!c) throw Error{kErrInvalid, "null circuit"};
         if (waves_per_eu < 1 || waves_per_eu > 8) throw Error{kErrInvalid, "waves_per_eu must be 1..8"};
         double ms = 0;
-        auto k = jit_kernel(const_cast<Circuit&>(c->c), waves_per_eu, &ms);
+        // A circuit with a native kernel for its whole space runs on that one: nothing to compile.
+        // One without gets it beside its hipRTC kernel (milliseconds against 0.1 s), so its first
+        // check builds nothing.
+        Circuit& cc = const_cast<Circuit&>(c->c);
+        const uint64_t whole = range_of(cc.plan1.num_inputs, 0, 0).end;
+        std::shared_ptr<JitKernel> k;
+        if (native_allowed()) {
+            k = native_tier()->ready(cc, whole);
+            if (!k) native_tier()->get(cc, whole, 0.0);
+        }
+        if (!k) k = jit_kernel(cc, waves_per_eu, &ms);
         if (compile_ms) *compile_ms = ms;
         if (code_bytes) *code_bytes = k->code->bytes->size();
+        return FASTLEC_OK;
+    });
+}
+
+int fastlec_es_native_info(const fastlec_es_circuit* c, uint32_t* inner, uint32_t* valu, uint32_t* waves) {
+    return guarded([&] {
+        if (!c) throw Error{kErrInvalid, "null circuit"};
+        Circuit& cc = const_cast<Circuit&>(c->c);
+        std::shared_ptr<JitKernel> k;
+        if (const NativeTier* t = native_tier()) k = t->get(cc, range_of(cc.plan1.num_inputs, 0, 0).end, 0.0);
+        if (!k) throw Error{kErrUnsupported, "no native kernel for this circuit"};
+        native_tier()->counts(*k, inner, valu, waves);
         return FASTLEC_OK;
     });
 }

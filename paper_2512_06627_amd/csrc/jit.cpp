@@ -34,6 +34,7 @@
 #include <sstream>
 #include <thread>
 
+#include "native.hpp"
 #include "rtc_options.hpp"
 #include "runtime.hpp"
 
@@ -703,6 +704,7 @@ CodeObject::~CodeObject() {
 }
 
 JitLaunchPlan jit_prepare(Device& dev, JitKernel& k, const HwRange& r, uint64_t tile_hw) {
+    if (k.native) return native_prepare(dev, k, r, tile_hw);
     JitLaunchPlan lp;
     int blocks_per_cu;
     {
@@ -752,6 +754,7 @@ JitLaunchPlan jit_prepare(Device& dev, JitKernel& k, const HwRange& r, uint64_t 
 }
 
 void jit_enqueue(const JitLaunchPlan& lp, uint64_t* next_item, uint64_t* best, const int* cancel, hipStream_t stream) {
+    if (lp.native) return native_enqueue(lp, next_item, best, stream);
     uint64_t hw_begin = lp.hw_begin, hw_end = lp.hw_end, hw_first = lp.hw_first, tile = lp.tile,
              total_items = lp.total_items;
     void* args[] = {&hw_begin, &hw_end, &hw_first, &tile, &total_items, &next_item, &best, &cancel};

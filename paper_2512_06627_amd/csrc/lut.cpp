@@ -12,37 +12,31 @@ namespace {
 
 constexpr uint32_t kInputWord[5] = {0xAAAAAAAAu, 0xCCCCCCCCu, 0xF0F0F0F0u, 0xFF00FF00u, 0xFFFF0000u};
 
+// Truth tables of 1- and 2-leaf functions with their leaves moved to other positions (position j
+// is bit 2-j of a table's index): 0: leaf 0 at position 1; 1: leaf 0 at position 2; 2: leaves 0, 1
+// at positions 0, 2; 3: leaves 0, 1 at positions 1, 2.
+struct Moves {
+    uint8_t to[4][256];
+    Moves() {
+        constexpr uint32_t pos[4][2] = {{1, 0}, {2, 0}, {0, 2}, {1, 2}};
+        for (uint32_t m = 0; m < 4; ++m)
+            for (uint32_t t = 0; t < 256; ++t) {
+                uint32_t out = 0;
+                for (uint32_t idx = 0; idx < 8; ++idx) {
+                    uint32_t from = ((idx >> (2 - pos[m][0])) & 1u) << 2;
+                    if (m >= 2) from |= ((idx >> (2 - pos[m][1])) & 1u) << 1;
+                    out |= ((t >> from) & 1u) << idx;
+                }
+                to[m][t] = (uint8_t)out;
+            }
+    }
+};
+const Moves kMoves;
+
 struct Val {  // value of an AIG variable: ref, complemented when neg
     LutRef ref;
     bool neg;
 };
-
-bool same(const LutRef& a, const LutRef& b) { return a.kind == b.kind && a.index == b.index; }
-
-struct Cover {  // a LUT in construction: function `tt` of `leaves` (bit idx = sum leaf_j << (2 - j))
-    std::vector<LutRef> leaves;
-    uint8_t tt = 0;
-    uint32_t gates = 0;
-};
-
-// Truth table (over the first k positions, position j = bit 2-j of the index) of leaf j.
-uint8_t proj(uint32_t j) { return j == 0 ? 0xF0 : j == 1 ? 0xCC : 0xAA; }
-
-// Re-express `sub` (over its own leaves) over the leaf list `L`.
-uint8_t remap(const Cover& sub, const std::vector<LutRef>& L) {
-    uint8_t out = 0;
-    for (uint32_t idx = 0; idx < 8; ++idx) {
-        uint32_t local = 0;
-        for (uint32_t j = 0; j < sub.leaves.size(); ++j) {
-            uint32_t pos = 0;
-            while (!same(L[pos], sub.leaves[j])) ++pos;
-            const uint32_t bit = (idx >> (2 - pos)) & 1u;
-            local |= bit << (2 - j);
-        }
-        if ((sub.tt >> local) & 1u) out |= (uint8_t)(1u << idx);
-    }
-    return out;
-}
 
 }  // namespace
 
@@ -145,14 +139,17 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
         return l;
     };
     // ---- 2. three-input cuts of varying gates, chosen by area flow --------------------
-    // A cut leaf is a varying gate or a fixed ref (input, word or uniform value); key
-    // encodes both so leaf sets can be compared.
-    auto key_node = [](uint32_t var) { return (uint64_t)var; };
-    auto key_ref = [](const LutRef& r) { return (1ull << 40) | ((uint64_t)r.kind << 32) | r.index; };
+    // A cut leaf is a varying gate or a fixed ref (input, word or uniform value); a key
+    // encodes either, so leaf sets can be compared.  Cuts are plain arrays in one flat table
+    // (kMaxCuts entries per gate): the merges of a gate touch no allocator and no map.
+    constexpr uint64_t kRefBit = 1ull << 40;
+    auto key_ref = [](const LutRef& r) { return kRefBit | ((uint64_t)r.kind << 32) | r.index; };
+    auto ref_of = [](uint64_t key) { return LutRef{(LutRef::Kind)((key >> 32) & 0xFF), (uint32_t)key}; };
     struct Cut {
-        std::vector<uint64_t> keys;  // sorted leaf keys
-        uint8_t tt;                  // over keys in order (position j = bit 2-j)
+        uint64_t keys[3];  // ascending; entries past n are unused
         double af;
+        uint8_t n;
+        uint8_t tt;        // over keys in order (position j = bit 2-j)
     };
     std::vector<uint32_t> fanout(V + 1, 0);
     for (uint32_t k : plan.order) {
@@ -160,75 +157,98 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
         ++fanout[g.and_r1[k] >> 1];
     }
     for (uint32_t o : g.outputs) ++fanout[o >> 1];
-    std::vector<std::vector<Cut>> cuts(V + 1);
-    std::vector<double> best_af(V + 1, 0.0);
-    auto tt_remap = [](const Cut& c, const std::vector<uint64_t>& L) {
-        uint8_t out = 0;
-        for (uint32_t idx = 0; idx < 8; ++idx) {
-            uint32_t local = 0;
-            for (uint32_t j = 0; j < c.keys.size(); ++j) {
-                const uint32_t pos = (uint32_t)(std::find(L.begin(), L.end(), c.keys[j]) - L.begin());
-                local |= ((idx >> (2 - pos)) & 1u) << (2 - j);
-            }
-            if ((c.tt >> local) & 1u) out |= (uint8_t)(1u << idx);
-        }
-        return out;
-    };
-    auto trivial = [&](uint64_t key) { return Cut{{key}, 0xF0, 0.0}; };
-    std::map<uint64_t, LutRef> ref_of_key;
-    auto cuts_of = [&](const Leaf& l) -> std::vector<Cut> {
-        if (l.node) {
-            std::vector<Cut> cs = cuts[l.var];
-            Cut t = trivial(key_node(l.var));
-            t.af = best_af[l.var] / std::max<uint32_t>(1, fanout[l.var]);
-            cs.push_back(t);
-            return cs;
-        }
-        ref_of_key[key_ref(l.ref)] = l.ref;
-        Cut t = trivial(key_ref(l.ref));
-        t.af = is_scalar_ref(l.ref) ? 0.25 : 0.0;  // a second scalar leaf costs a copy
-        return {t};
-    };
     constexpr size_t kMaxCuts = 10;
+    std::vector<uint32_t> cut_at(V + 1, 0);  // first entry of a gate's cuts
+    std::vector<uint8_t> cut_n(V + 1, 0);
+    std::vector<Cut> table;
+    table.reserve(plan.order.size() * kMaxCuts + 1);
+    std::vector<double> best_af(V + 1, 0.0);
+    // Truth table of c over the sorted leaf list L, which holds c's own sorted leaves.  Entries of
+    // leaves a cut does not have repeat, so only leaves that move to a later position change the
+    // table, and each of the four possible moves is a table of its own.
+    auto tt_remap = [](const Cut& c, const uint64_t* L, uint32_t n) {
+        if (c.n == n) return c.tt;
+        if (c.n == 1) return L[0] == c.keys[0] ? c.tt : L[1] == c.keys[0] ? kMoves.to[0][c.tt] : kMoves.to[1][c.tt];
+        if (L[0] != c.keys[0]) return kMoves.to[3][c.tt];
+        return L[1] == c.keys[1] ? c.tt : kMoves.to[2][c.tt];
+    };
+    Cut side[2][kMaxCuts + 1];
+    uint32_t nside[2];
+    auto cuts_of = [&](const Leaf& l, int s) {
+        uint32_t m = 0;
+        Cut t{};
+        t.n = 1;
+        t.tt = 0xF0;
+        if (l.node) {
+            for (; m < cut_n[l.var]; ++m) side[s][m] = table[cut_at[l.var] + m];
+            t.keys[0] = l.var;
+            t.af = best_af[l.var] / std::max<uint32_t>(1, fanout[l.var]);
+        } else {
+            t.keys[0] = key_ref(l.ref);
+            t.af = is_scalar_ref(l.ref) ? 0.25 : 0.0;  // a second scalar leaf costs a copy
+        }
+        side[s][m++] = t;
+        nside[s] = m;
+    };
+    std::vector<Cut> out;
     for (uint32_t k : plan.order) {
         const uint32_t v = n + 1 + k;
         if (varying[v] != 1) continue;
         const Leaf A = leaf_of(g.and_r0[k]), B = leaf_of(g.and_r1[k]);
-        const std::vector<Cut> ca = cuts_of(A), cb = cuts_of(B);
-        std::vector<Cut> out;
-        for (const Cut& x : ca)
-            for (const Cut& y : cb) {
-                std::vector<uint64_t> L = x.keys;
-                for (uint64_t q : y.keys)
-                    if (std::find(L.begin(), L.end(), q) == L.end()) L.push_back(q);
-                if (L.size() > 3) continue;
-                std::sort(L.begin(), L.end());
+        cuts_of(A, 0);
+        cuts_of(B, 1);
+        out.clear();
+        for (uint32_t xi = 0; xi < nside[0]; ++xi)
+            for (uint32_t yi = 0; yi < nside[1]; ++yi) {
+                const Cut &x = side[0][xi], &y = side[1][yi];
                 Cut c;
-                c.keys = L;
-                const uint8_t tx = (uint8_t)(tt_remap(x, L) ^ (A.neg ? 0xFF : 0x00));
-                const uint8_t ty = (uint8_t)(tt_remap(y, L) ^ (B.neg ? 0xFF : 0x00));
-                c.tt = (uint8_t)(tx & ty);
+                c.n = 0;  // sorted union of the two leaf lists
+                uint32_t i = 0, j = 0;
+                bool fits = true;
+                while (i < x.n || j < y.n) {
+                    if (c.n == 3) {
+                        fits = false;
+                        break;
+                    }
+                    if (j >= y.n || (i < x.n && x.keys[i] < y.keys[j])) c.keys[c.n++] = x.keys[i++];
+                    else if (i >= x.n || y.keys[j] < x.keys[i]) c.keys[c.n++] = y.keys[j++];
+                    else {
+                        c.keys[c.n++] = x.keys[i++];
+                        ++j;
+                    }
+                }
+                if (!fits) continue;
                 // area flow: this LUT plus the shared cost of its gate leaves
                 c.af = 1.0;
                 int scalars = 0;
-                for (uint64_t q : L) {
-                    if (q < (1ull << 40)) c.af += best_af[(uint32_t)q] / std::max<uint32_t>(1, fanout[(uint32_t)q]);
-                    else if (is_scalar_ref(ref_of_key[q])) ++scalars;
+                for (uint32_t q = 0; q < c.n; ++q) {
+                    if (c.keys[q] < kRefBit) c.af += best_af[(uint32_t)c.keys[q]] / std::max<uint32_t>(1, fanout[(uint32_t)c.keys[q]]);
+                    else if (is_scalar_ref(ref_of(c.keys[q]))) ++scalars;
                 }
                 if (scalars > 1) c.af += 0.25 * (scalars - 1);
                 bool dup = false;
+                Cut* same_leaves = nullptr;
                 for (Cut& e : out)
-                    if (e.keys == c.keys) {
+                    if (e.n == c.n && e.keys[0] == c.keys[0] && (c.n < 2 || e.keys[1] == c.keys[1]) &&
+                        (c.n < 3 || e.keys[2] == c.keys[2])) {
                         dup = true;
-                        if (c.af < e.af) e = c;
+                        same_leaves = &e;
+                        break;
                     }
-                if (!dup) out.push_back(c);
+                if (dup && !(c.af < same_leaves->af)) continue;
+                const uint8_t tx = (uint8_t)(tt_remap(x, c.keys, c.n) ^ (A.neg ? 0xFF : 0x00));
+                const uint8_t ty = (uint8_t)(tt_remap(y, c.keys, c.n) ^ (B.neg ? 0xFF : 0x00));
+                c.tt = (uint8_t)(tx & ty);
+                if (dup) *same_leaves = c;
+                else out.push_back(c);
             }
         std::sort(out.begin(), out.end(), [](const Cut& a, const Cut& b) {
-            return a.af != b.af ? a.af < b.af : a.keys.size() < b.keys.size();
+            return a.af != b.af ? a.af < b.af : a.n < b.n;
         });
         if (out.size() > kMaxCuts) out.resize(kMaxCuts);
-        cuts[v] = out;
+        cut_at[v] = (uint32_t)table.size();
+        cut_n[v] = (uint8_t)out.size();
+        table.insert(table.end(), out.begin(), out.end());
         best_af[v] = out.empty() ? 1.0 : out[0].af;
     }
     // ---- 3. cover: gates needed by the outputs through their chosen cuts --------------
@@ -236,39 +256,54 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
     // in topological order and keeps the cut that adds the fewest LUTs given the rest of
     // the cover (reference counts over the chosen cuts), two rounds.
     std::vector<uint32_t> sel(V + 1, 0), ref(V + 1, 0);
-    std::function<uint32_t(uint32_t, const Cut&)> ref_cut, deref_cut;
-    ref_cut = [&](uint32_t, const Cut& c) {
-        uint32_t a = 1;
-        for (uint64_t q : c.keys)
-            if (q < (1ull << 40) && ref[(uint32_t)q]++ == 0) a += ref_cut((uint32_t)q, cuts[(uint32_t)q][sel[(uint32_t)q]]);
-        return a;
+    auto cut = [&](uint32_t v, uint32_t i) -> const Cut& { return table[cut_at[v] + i]; };
+    std::vector<uint32_t> work;  // gates whose chosen cut joins (leaves) the cover
+    auto ref_cut = [&](const Cut& first) {
+        uint32_t a = 0;
+        const Cut* c = &first;
+        work.clear();
+        for (;;) {
+            ++a;
+            for (uint32_t j = 0; j < c->n; ++j)
+                if (c->keys[j] < kRefBit && ref[(uint32_t)c->keys[j]]++ == 0) work.push_back((uint32_t)c->keys[j]);
+            if (work.empty()) return a;
+            const uint32_t v = work.back();
+            work.pop_back();
+            c = &cut(v, sel[v]);
+        }
     };
-    deref_cut = [&](uint32_t, const Cut& c) {
-        uint32_t a = 1;
-        for (uint64_t q : c.keys)
-            if (q < (1ull << 40) && --ref[(uint32_t)q] == 0) a += deref_cut((uint32_t)q, cuts[(uint32_t)q][sel[(uint32_t)q]]);
-        return a;
+    auto deref_cut = [&](const Cut& first) {
+        const Cut* c = &first;
+        work.clear();
+        for (;;) {
+            for (uint32_t j = 0; j < c->n; ++j)
+                if (c->keys[j] < kRefBit && --ref[(uint32_t)c->keys[j]] == 0) work.push_back((uint32_t)c->keys[j]);
+            if (work.empty()) return;
+            const uint32_t v = work.back();
+            work.pop_back();
+            c = &cut(v, sel[v]);
+        }
     };
     for (uint32_t o : g.outputs) {
         const uint32_t v = o >> 1;
-        if (varying[v] == 1 && ref[v]++ == 0) ref_cut(v, cuts[v][sel[v]]);
+        if (varying[v] == 1 && ref[v]++ == 0) ref_cut(cut(v, sel[v]));
     }
     for (int round = 0; round < 2; ++round) {
         for (uint32_t k : plan.order) {
             const uint32_t v = n + 1 + k;
             if (varying[v] != 1 || ref[v] == 0) continue;
-            deref_cut(v, cuts[v][sel[v]]);
+            deref_cut(cut(v, sel[v]));
             uint32_t best = sel[v], best_area = UINT32_MAX;
-            for (uint32_t i = 0; i < cuts[v].size(); ++i) {
-                const uint32_t a = ref_cut(v, cuts[v][i]);
-                deref_cut(v, cuts[v][i]);
+            for (uint32_t i = 0; i < cut_n[v]; ++i) {
+                const uint32_t a = ref_cut(cut(v, i));
+                deref_cut(cut(v, i));
                 if (a < best_area) {
                     best_area = a;
                     best = i;
                 }
             }
             sel[v] = best;
-            ref_cut(v, cuts[v][best]);
+            ref_cut(cut(v, best));
         }
     }
     std::vector<uint8_t> required(V + 1, 0);
@@ -288,9 +323,11 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
         }
     };
     for (uint32_t v = 0; v <= V; ++v)
-        if (required[v])
-            for (uint64_t q : cuts[v][sel[v]].keys)
-                if (q >= (1ull << 40)) need_ref(ref_of_key[q]);
+        if (required[v]) {
+            const Cut& c = cut(v, sel[v]);
+            for (uint32_t j = 0; j < c.n; ++j)
+                if (c.keys[j] >= kRefBit) need_ref(ref_of(c.keys[j]));
+        }
     for (uint32_t o : g.outputs)
         if (varying[o >> 1] != 1) need_ref(val[o >> 1].ref);
     while (!stack.empty()) {
@@ -319,13 +356,13 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
         const uint32_t v = n + 1 + k;
         if (varying[v] == 1) ++total_varying;
         if (varying[v] != 1 || !required[v]) continue;
-        const Cut& c = cuts[v][sel[v]];
+        const Cut& c = cut(v, sel[v]);
         LutStep st{};
         st.op = LutStep::Lut;
-        st.nleaves = (uint8_t)c.keys.size();
+        st.nleaves = c.n;
         for (uint32_t j = 0; j < 3; ++j) {
-            const uint64_t q = c.keys[std::min<size_t>(j, c.keys.size() - 1)];
-            st.leaf[j] = q < (1ull << 40) ? LutRef{LutRef::Varying, value_of_var[(uint32_t)q]} : ref_of_key[q];
+            const uint64_t q = c.keys[std::min<uint32_t>(j, c.n - 1u)];
+            st.leaf[j] = q < kRefBit ? LutRef{LutRef::Varying, value_of_var[(uint32_t)q]} : ref_of(q);
         }
         for (uint32_t j = 0; j < st.nleaves; ++j) ensure(st.leaf[j]);
         st.table = c.tt;

@@ -14,8 +14,8 @@ constexpr double kInterpT0Ms = 0.0116;
 constexpr uint32_t kTierRows[3] = {104, 144, 232};  // register tier files; LDS or device memory above
 constexpr double kInterpRate[4] = {1.958e14, 2.126e14, 1.940e14, 4.04e13};  // gate instructions*patterns/s
 constexpr double kInterpMsPerGateFloor = 2.24e-5; // one wave pass per gate: spaces below a chip's waves
-constexpr double kSpecT0Ms = 0.0135;
-constexpr double kSpecLutPassesPerS = 6.08e11;
+constexpr double kSpecT0Ms = 0.0062;
+constexpr double kSpecLutPassesPerS = 7.5e11;
 constexpr double kCompileC0Ms = 101.7;
 constexpr double kCompileMsPerLut = 0.00664;
 // Multi-kernel programs (GPU machine host, comgr's cache off): 16 kernels of about 500 LUT steps
@@ -37,6 +37,10 @@ int model_interp_tier(uint32_t rows) {
 double model_interp_ms(uint32_t gates, uint32_t rows, double patterns) {
     const double rate = model::kInterpRate[model_interp_tier(rows)];
     return model::kInterpT0Ms + (double)gates * std::max(patterns / rate * 1e3, model::kInterpMsPerGateFloor);
+}
+
+double model_interp_share_ms(uint32_t gates, uint32_t rows, double patterns) {
+    return (double)gates * std::max(2048.0, patterns) / model::kInterpRate[model_interp_tier(rows)] * 1e3;
 }
 
 double model_specialized_ms(uint32_t lut_steps, double patterns) {

@@ -18,6 +18,9 @@ namespace fes {
 //  specialized:  t = t0 + LUT steps * passes / R, passes = patterns / 2048 (at least 1)
 //  compile:      t = c0 + c1 * LUT steps
 double model_interp_ms(uint32_t gates, uint32_t rows, double patterns);
+// A cone's share of a launch that many cones fill: no launch cost, and a space below one pass per
+// wave costs its own passes only.
+double model_interp_share_ms(uint32_t gates, uint32_t rows, double patterns);
 // Tier of a value file of `rows` rows: 0..2 register tier (104, 144, 232 rows), 3 LDS or device memory.
 int model_interp_tier(uint32_t rows);
 double model_specialized_ms(uint32_t lut_steps, double patterns);

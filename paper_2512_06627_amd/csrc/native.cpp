@@ -1,0 +1,287 @@
+// Native tier on the device: kernels per circuit, modules and launches.
+#include <algorithm>
+#include <cmath>
+#include <cstdlib>
+#include <cstring>
+#include <numeric>
+
+#include "native.hpp"
+#include "runtime.hpp"
+
+namespace fes {
+namespace {
+
+// Test hook: FASTLEC_ES_NATIVE_INNER fixes the number of inner inputs (where the circuit has them).
+int forced_inner() {
+    const char* v = std::getenv("FASTLEC_ES_NATIVE_INNER");
+    return v && *v ? std::atoi(v) : -1;
+}
+
+// Inner inputs of checks that cover `span` half-words at a time: any input for the whole space,
+// else inputs whose block of patterns is at most a sixteenth of the span (a range is covered in
+// whole blocks, so its ragged ends cost at most an eighth more).  Steps of three inputs keep the
+// number of kernels per circuit small.
+uint32_t inner_limit(const Circuit& c, uint64_t span) {
+    const uint32_t n = c.plan1.num_inputs;
+    if (n <= 11 || span >= 1ull << (n - 5)) return std::max<uint32_t>(n, 11);
+    uint32_t q = 0;
+    while (q < 58 && (span >> (q + 1))) ++q;
+    const int top = (int)q + 5 - 4;
+    return top <= 11 ? 11 : 11 + (uint32_t)(top - 11) / 3 * 3;
+}
+
+double passes_of(double patterns) { return std::max(1.0, patterns / 2048.0); }
+
+std::shared_ptr<JitKernel> find(Circuit& c, uint64_t span, bool exact) {
+    const uint32_t limit = inner_limit(c, span);
+    std::lock_guard<std::mutex> g(c.mu);
+    auto it = c.native.upper_bound(limit);
+    if (it == c.native.begin()) return nullptr;
+    --it;
+    return exact && it->first != limit ? nullptr : it->second;
+}
+
+std::shared_ptr<JitKernel> ready(Circuit& c, uint64_t span) { return find(c, span, false); }
+
+std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight) {
+    if (auto k = find(c, span, true)) return k;
+    std::lock_guard<std::mutex> build(c.native_mu);
+    if (auto k = find(c, span, true)) return k;
+    const uint32_t limit = inner_limit(c, span);
+    const double patterns = 32.0 * (double)span;
+    std::shared_ptr<NativeKernel> n;
+    const int inner = forced_inner();
+    if (inner >= 0) n = build_native(c.aig, c.plan1.order, limit, passes_of(patterns), 0, inner);
+    if (!n) n = build_native(c.aig, c.plan1.order, limit, passes_of(patterns), weight);
+    if (!n) return nullptr;
+    auto k = std::make_shared<JitKernel>();
+    k->native = n;
+    k->name = n->waves == 3 ? "fes_native_168" : "fes_native_256";
+    k->waves_per_eu = k->waves_used = n->waves;
+    k->block = 64;
+    std::vector<uint64_t> at;
+    k->code = std::make_shared<CodeObject>();
+    k->code->bytes = std::make_shared<const std::vector<char>>(native_code_object({&n->code}, &at));
+    trace("native: %zu inner inputs, %u VALU and %u LDS instructions, %d waves per SIMD, built in %.2f ms",
+          n->bits.size(), n->code.valu, n->code.lds, n->waves, n->build_ms);
+    std::lock_guard<std::mutex> g(c.mu);
+    c.native[limit] = k;
+    return k;
+}
+
+double run_ms(const JitKernel& k, double patterns) {
+    const NativeKernel& n = *k.native;
+    return 0.012 + native_run_ms(n.code.valu + n.code.lds, (uint32_t)n.bits.size(), passes_of(patterns));
+}
+
+double share_ms(const JitKernel& k, double patterns) {
+    const NativeKernel& n = *k.native;
+    return std::ceil(passes_of(patterns) / (double)(1u << n.bits.size())) * (n.code.valu + n.code.lds + 200) * 1.0e-9;
+}
+
+double guess_run_ms(const Circuit& c, double patterns) {
+    return 0.012 + native_run_ms(0.26 * c.plan1.num_ands_tfi + 10, 0, passes_of(patterns));
+}
+
+// Building and loading: a module load takes 0.6 to 1.3 ms.
+double guess_build_ms(const Circuit& c) { return 1.0 + native_build_ms(c.plan1.num_ands_tfi); }
+
+void counts(const JitKernel& k, uint32_t* inner, uint32_t* valu, uint32_t* waves) {
+    if (inner) *inner = (uint32_t)k.native->bits.size();
+    if (valu) *valu = k.native->code.valu;
+    if (waves) *waves = (uint32_t)k.native->waves;
+}
+
+// Descriptor of kernel k over range r, its work items numbered from item_begin; returns the next
+// free item number.
+uint64_t fill(const NativeKernel& k, uint64_t code_offset, const HwRange& r, uint64_t tile_hw, uint64_t waves,
+              uint64_t item_begin, uint32_t best_index, NativeDesc& d) {
+    d = NativeDesc{};
+    d.code_offset = code_offset;
+    d.hw_begin = r.begin;
+    d.hw_end = r.end;
+    d.inner = (uint32_t)k.bits.size();
+    for (uint32_t j = 0; j < d.inner; ++j) d.inner_bit[j] = k.bits[j];
+    if (d.inner == 0) {
+        d.u_first = r.begin / 64 * 64;
+        d.u_end = r.end;
+    } else {  // whole blocks of patterns up to the highest inner input
+        const uint32_t block = k.bits.back() + 1, packed = block - d.inner;
+        d.u_first = (r.begin >> block) << packed;
+        d.u_end = ((r.end + ((1ull << block) - 1)) >> block) << packed;
+    }
+    const uint64_t span = d.u_end - d.u_first;
+    // About 16 work items per wave, of one to 64 passes.
+    uint64_t tile = tile_hw >> d.inner;
+    if (!tile_hw) {
+        const uint64_t target = span / std::max<uint64_t>(1, waves * 16);
+        tile = 64;
+        while (tile < target && tile < 64ull * 64) tile *= 2;
+    }
+    d.tile_hw = std::max<uint64_t>(64, (tile + 63) / 64 * 64);
+    d.item_begin = item_begin;
+    d.best_index = best_index;
+    return item_begin + (span + d.tile_hw - 1) / d.tile_hw;
+}
+
+hipFunction_t function_of(Device& dev, JitKernel& k) {
+    std::lock_guard<std::mutex> g(k.mu);
+    auto it = k.per_device.find(dev.ordinal);
+    if (it != k.per_device.end()) return it->second;
+    hipFunction_t fn;
+    FES_HIP(hipModuleGetFunction(&fn, k.code->module(dev.ordinal), k.name.c_str()));
+    k.per_device[dev.ordinal] = fn;
+    return fn;
+}
+
+uint64_t resident_waves(const Device& dev, int waves_per_simd) {
+    return (uint64_t)dev.prop.multiProcessorCount * 4 * waves_per_simd;
+}
+
+void launch(hipFunction_t fn, const NativeLaunch& L, uint64_t grid, uint32_t lds, hipStream_t stream) {
+    void* args[] = {const_cast<NativeLaunch*>(&L)};
+    trace("native launch: %u cones, %llu items, grid=%llu", L.num_cones, (unsigned long long)L.total_items,
+          (unsigned long long)grid);
+    FES_HIP(hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, 64, 1, 1, lds, stream, args, nullptr));
+}
+
+// Kernels of a batch as one code object.  Sets are kept (least recently used dropped) so that a
+// batch of the same kernels loads nothing again.
+struct KernelSet {
+    std::vector<std::shared_ptr<JitKernel>> ks;
+    std::shared_ptr<CodeObject> code;
+    std::vector<uint64_t> at;
+    uint64_t last_use = 0;
+};
+constexpr size_t kMaxSets = 8;
+std::mutex g_sets_mu;
+std::vector<std::shared_ptr<KernelSet>>& sets() {
+    static std::vector<std::shared_ptr<KernelSet>> v;
+    return v;
+}
+uint64_t g_set_clock = 0;
+
+std::shared_ptr<KernelSet> set_of(const std::vector<std::shared_ptr<JitKernel>>& ks) {
+    std::lock_guard<std::mutex> g(g_sets_mu);
+    for (auto& s : sets())
+        if (s->ks == ks) {
+            s->last_use = ++g_set_clock;
+            return s;
+        }
+    auto s = std::make_shared<KernelSet>();
+    s->ks = ks;
+    std::vector<const NativeCode*> codes;
+    for (auto& k : ks) codes.push_back(&k->native->code);
+    s->code = std::make_shared<CodeObject>();
+    s->code->bytes = std::make_shared<const std::vector<char>>(native_code_object(codes, &s->at));
+    s->last_use = ++g_set_clock;
+    auto& v = sets();
+    if (v.size() >= kMaxSets)
+        v.erase(std::min_element(v.begin(), v.end(),
+                                 [](const auto& a, const auto& b) { return a->last_use < b->last_use; }));
+    v.push_back(s);
+    return s;
+}
+
+void run_many(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks, const std::vector<HwRange>& ranges,
+              hipStream_t stream, std::vector<uint64_t>& best, double* ms) {
+    const size_t n = ks.size();
+    best.assign(n, ~0ull);
+    if (ms) *ms = 0;
+    if (!n) return;
+    const std::shared_ptr<KernelSet> set = set_of(ks);
+    // Longest first within a register tier, so that the short ones fill the end of the launch.
+    std::vector<size_t> order(n);
+    std::iota(order.begin(), order.end(), 0);
+    std::vector<double> cost(n);
+    for (size_t i = 0; i < n; ++i) cost[i] = run_ms(*ks[i], 32.0 * (double)(ranges[i].end - ranges[i].begin));
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+    const size_t best_off = 2 * kClaimBytes, desc_off = (best_off + 8 * n + 63) & ~size_t(63);
+    const size_t total = desc_off + sizeof(NativeDesc) * n;
+    Buffer buf = dev.acquire(total);
+    struct Releaser {
+        Device& d;
+        Buffer b;
+        ~Releaser() { d.release(b); }
+    } rel{dev, buf};
+    uint8_t *host = (uint8_t*)buf.host, *devp = (uint8_t*)buf.dev;
+    std::memset(host, 0, best_off);
+    std::memset(host + best_off, 0xFF, 8 * n);
+    struct Group {
+        NativeLaunch L{};
+        uint64_t grid = 0;
+        uint32_t lds = 0;
+        const char* name = nullptr;
+    } groups[2];
+    size_t at = 0;
+    for (int t = 0; t < 2; ++t) {
+        Group& g = groups[t];
+        const int waves = t == 0 ? 3 : 2;
+        const uint64_t resident = resident_waves(dev, waves);
+        const size_t from = at;
+        uint64_t items = 0;
+        for (size_t i : order) {
+            const NativeKernel& k = *ks[i]->native;
+            if (k.waves != waves) continue;
+            items = fill(k, set->at[i], ranges[i], 0, resident, items, (uint32_t)i,
+                         ((NativeDesc*)(host + desc_off))[at++]);
+            g.lds = std::max(g.lds, k.code.lds_slots * 256);
+            g.name = ks[i]->name.c_str();
+        }
+        g.L.cones = (const NativeDesc*)(devp + desc_off) + from;
+        g.L.num_cones = (uint32_t)(at - from);
+        g.L.total_items = items;
+        g.L.counters = (unsigned long long*)(devp + t * kClaimBytes);
+        g.L.best = (unsigned long long*)(devp + best_off);
+        g.grid = std::min(items, resident);
+    }
+    ScopedEvent e0, e1;
+    FES_HIP(hipMemcpyAsync(devp, host, total, hipMemcpyHostToDevice, stream));
+    FES_HIP(hipEventRecord(e0.e, stream));
+    for (Group& g : groups) {
+        if (!g.L.num_cones) continue;
+        hipFunction_t fn;
+        FES_HIP(hipModuleGetFunction(&fn, set->code->module(dev.ordinal), g.name));
+        launch(fn, g.L, g.grid, g.lds, stream);
+    }
+    FES_HIP(hipEventRecord(e1.e, stream));
+    FES_HIP(hipMemcpyAsync(host + best_off, devp + best_off, 8 * n, hipMemcpyDeviceToHost, stream));
+    FES_HIP(hipStreamSynchronize(stream));
+    float t = 0;
+    FES_HIP(hipEventElapsedTime(&t, e0.e, e1.e));
+    if (ms) *ms = t;
+    std::memcpy(best.data(), host + best_off, 8 * n);
+}
+
+const NativeTier kTier = {ready, get, run_ms, share_ms, guess_run_ms, guess_build_ms, counts, run_many};
+const bool g_registered = (register_native_tier(&kTier), true);
+
+}  // namespace
+
+JitLaunchPlan native_prepare(Device& dev, JitKernel& k, const HwRange& r, uint64_t tile_hw) {
+    const NativeKernel& n = *k.native;
+    JitLaunchPlan lp;
+    lp.native = true;
+    lp.fn = function_of(dev, k);
+    const uint64_t resident = resident_waves(dev, n.waves);
+    lp.total_items = fill(n, 0, r, tile_hw, resident, 0, 0, lp.one);
+    lp.grid = (int)std::min(lp.total_items, resident);
+    lp.block = 64;
+    lp.lds_bytes = n.code.lds_slots * 256;
+    lp.hw_begin = r.begin;
+    lp.hw_end = r.end;
+    return lp;
+}
+
+void native_enqueue(const JitLaunchPlan& lp, uint64_t* next_item, uint64_t* best, hipStream_t stream) {
+    NativeLaunch L{};
+    L.cones = nullptr;
+    L.num_cones = 1;
+    L.total_items = lp.total_items;
+    L.counters = (unsigned long long*)next_item;
+    L.best = (unsigned long long*)best;
+    L.one = lp.one;
+    launch(lp.fn, L, (uint64_t)lp.grid, lp.lds_bytes, stream);
+}
+
+}  // namespace fes

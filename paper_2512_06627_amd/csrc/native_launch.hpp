@@ -1,0 +1,43 @@
+// Data layouts shared by the native tier's host code and its kernel (native/es_native.hip).
+#pragma once
+#include <cstdint>
+
+namespace fes {
+
+// Work claims are spread over C = min(kClaimCounters, waves in the grid) counters, each on
+// its own 128-byte line: the wave with global index w claims from counter s = w % C and gets
+// the items s, s + C, s + 2C, ... in that order.  One shared counter
+// serialises every claim of the launch at the atomic unit (about 30 ns each), which bounds
+// launches of many short work items; spread over separate lines the claims proceed in
+// parallel, and the items still start in roughly ascending order.
+constexpr uint32_t kClaimCounters = 16;
+constexpr uint32_t kClaimStride = 16;  // 64-bit words from one counter to the next (128 bytes)
+
+constexpr uint32_t kMaxInner = 5;  // inner inputs of a native pass: up to 2^5 assignments
+
+// One circuit of a native launch.  Half-word h holds patterns 32h .. 32h+31.
+struct NativeDesc {
+    uint64_t code_offset;  // of its pass in the generated section
+    uint64_t hw_begin;     // checked range, real half-words
+    uint64_t hw_end;
+    uint64_t u_first;      // packed half-words covered (inner positions removed)
+    uint64_t u_end;
+    uint64_t tile_hw;      // packed half-words per work item (multiple of 64)
+    uint64_t item_begin;   // first work item of this cone in the launch
+    uint32_t best_index;
+    uint32_t inner;                 // inner inputs
+    uint32_t inner_bit[kMaxInner];  // their bits of the real half-word index, ascending
+    uint32_t pad;
+};
+static_assert(sizeof(NativeDesc) == 88, "descriptor layout");
+
+struct NativeLaunch {
+    const NativeDesc* cones;  // device array, or null for a launch of the single cone `one`
+    uint32_t num_cones;
+    uint64_t total_items;
+    unsigned long long* counters;  // claim counters, zero before the launch
+    unsigned long long* best;      // per cone: lowest failing pattern, ~0 = none yet
+    NativeDesc one;
+};
+
+}  // namespace fes

@@ -41,6 +41,34 @@ double now_ms() {
     return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
 
+// ---- native tier ---------------------------------------------------------------
+
+namespace {
+const NativeTier* g_native_tier = nullptr;
+}
+
+void register_native_tier(const NativeTier* t) { g_native_tier = t; }
+
+const NativeTier* native_tier() {
+    static const bool on = [] {
+        const char* v = std::getenv("FASTLEC_ES_NATIVE");
+        return !(v && *v && std::atoi(v) == 0);
+    }();
+    return on ? g_native_tier : nullptr;
+}
+
+bool native_pays(Circuit& c, double interp_ms, double patterns, double build_share) {
+    const NativeTier* t = native_tier();
+    if (!t) return false;
+    // Margin on the building: its estimate is good to about a factor of 1.5.
+    const double cost = t->guess_run_ms(c, patterns) + 1.5 * build_share * t->guess_build_ms(c);
+    double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
+    if (interp_ms + spent > cost) return true;
+    while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + interp_ms, std::memory_order_relaxed)) {
+    }
+    return false;
+}
+
 // ---- circuits --------------------------------------------------------------
 
 Circuit::~Circuit() {

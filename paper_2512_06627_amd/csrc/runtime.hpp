@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <array>
+#include <atomic>
 #include <functional>
 #include <map>
 #include <memory>
@@ -14,6 +15,7 @@
 #include "aig.hpp"
 #include "kernels.hpp"
 #include "model.hpp"
+#include "native_launch.hpp"
 #include "plan.hpp"
 
 namespace fes {
@@ -54,7 +56,10 @@ struct CodeObject {
     ~CodeObject();
 };
 
+struct NativeKernel;  // native.hpp
+
 struct JitKernel {
+    std::shared_ptr<const NativeKernel> native;  // machine code of the native tier, else null
     std::string source;                // the kernel's own source (entry point fes_es_kernel)
     std::string name = "fes_es_kernel";  // entry point in the code object
     std::shared_ptr<CodeObject> code;  // set once compiled
@@ -84,6 +89,9 @@ struct Circuit {
     std::map<uint32_t, std::unique_ptr<Plan>> bundled;                  // bundle size -> plan
     std::map<std::pair<int, uint32_t>, Instr*> dev_prog;                  // (device, bundle) -> stream
     std::map<int, std::shared_ptr<JitKernel>> jit;                       // waves_per_eu -> kernel
+    std::map<uint32_t, std::shared_ptr<JitKernel>> native;               // inner-input limit -> native kernel
+    std::mutex native_mu;                                                 // one native build at a time
+    std::atomic<double> interp_ms_spent{0};                               // see native_pays
     std::unique_ptr<LutProgram> lut;                                      // specialized-kernel program
     std::map<uint32_t, std::unique_ptr<Plan>> sim;                        // bundle -> simulation plan
     std::map<std::pair<int, uint32_t>, Instr*> dev_sim_prog;              // (device, bundle) -> stream
@@ -281,10 +289,45 @@ struct JitLaunchPlan {
     hipFunction_t fn = nullptr;
     int grid = 0, block = 0;
     uint64_t hw_begin = 0, hw_end = 0, hw_first = 0, tile = 0, total_items = 0;
+    bool native = false;  // a native kernel over the cone `one`
+    uint32_t lds_bytes = 0;
+    NativeDesc one{};
 };
 JitLaunchPlan jit_prepare(Device& dev, JitKernel& k, const HwRange& r, uint64_t tile_hw);
 void jit_enqueue(const JitLaunchPlan& lp, uint64_t* next_item, uint64_t* best, const int* cancel, hipStream_t stream);
 std::string jit_source(const LutProgram& lp, int waves_per_eu, int block, int* waves_used = nullptr);
+
+// ---- native tier -------------------------------------------------------------------------------
+//
+// jit_prepare and jit_enqueue of a native kernel.
+JitLaunchPlan native_prepare(Device& dev, JitKernel& k, const HwRange& r, uint64_t tile_hw);
+void native_enqueue(const JitLaunchPlan& lp, uint64_t* next_item, uint64_t* best, hipStream_t stream);
+// Machine code that the library encodes itself (native.hpp): a circuit's kernel costs milliseconds
+// of planning and a module load, not a compile.  The library links the tier; host-only builds of
+// its sources do without it (native_tier() is then null) and use the interpreter and hipRTC kernels.
+struct NativeTier {
+    // The circuit's kernel for checks that cover `span` half-words at a time of its space, if one is
+    // built (get: build it if not; null when the circuit's values fit neither registers nor LDS).
+    // `weight`: what a millisecond of building costs against one of kernel time.
+    std::shared_ptr<JitKernel> (*ready)(Circuit& c, uint64_t span);
+    std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight);
+    // Expected kernel time over `patterns` patterns, and of get() for a circuit without one.
+    double (*run_ms)(const JitKernel& k, double patterns);
+    double (*share_ms)(const JitKernel& k, double patterns);  // of a launch that many cones fill
+    double (*guess_run_ms)(const Circuit& c, double patterns);
+    double (*guess_build_ms)(const Circuit& c);
+    void (*counts)(const JitKernel& k, uint32_t* inner, uint32_t* valu, uint32_t* waves);
+    // One launch per register tier over several kernels' ranges.
+    void (*run_many)(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks,
+                     const std::vector<HwRange>& ranges, hipStream_t stream, std::vector<uint64_t>& best, double* ms);
+};
+const NativeTier* native_tier();  // null: not linked, or off (FASTLEC_ES_NATIVE=0)
+void register_native_tier(const NativeTier* t);
+// Whether a native kernel pays for a circuit that has none: the interpreter's time for this check
+// plus what the interpreter has already taken for this circuit exceeds the native kernel's time
+// and its building.  A circuit checked again and again thus spends at most about twice the better
+// of the two; one checked once is built only when that check alone pays.
+bool native_pays(Circuit& c, double interp_ms, double patterns, double build_share);
 
 // The per-pass body as one asm statement with planner-assigned registers (v0.., s<sgpr_base>..).
 // Returns false, with the register counts in stats, when it needs more than the limits.

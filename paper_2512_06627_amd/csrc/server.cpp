@@ -60,6 +60,16 @@ uint64_t env_u64(const char* name, uint64_t dflt) {
     return std::strtoull(v, nullptr, 0);
 }
 
+// Half-words of a job that one native slice covers: its whole space, or a sixteenth of it (a slice
+// is about a step of work, so large jobs run as many slices and their kernel's inner inputs must
+// fit in one).
+uint64_t slice_span(const Circuit& c) {
+    const uint32_t n = c.plan1.num_inputs;
+    const uint64_t whole = n >= 5 ? 1ull << (n - 5) : 1ull;
+    return n <= 26 ? whole : whole / 16;
+}
+constexpr double kServerBuildWeight = 0.2;  // building runs beside the launches
+
 // Interpreter configuration of the server's launches: half-words per lane (1), gates per bundle
 // (16), and the LDS group's workgroup chosen for the most waves per CU (else shrunk only until
 // it fits).  Measured on the serving mix at 0.7 load against 2 half-words, 8-gate bundles and
@@ -165,8 +175,22 @@ void fastlec_es_server::compile_loop() {
         for (Job* j : group) cs.push_back(j->c);
         std::vector<std::shared_ptr<JitKernel>> ks;
         try {
-            ks = jit_kernels(cs, specialized_waves_per_eu(), nullptr,
-                             helpers ? CompileSplit::kEach : CompileSplit::kGroup);
+            if (const NativeTier* t = native_tier())
+                for (Circuit* c : cs) ks.push_back(t->get(*c, slice_span(*c), kServerBuildWeight));
+            else ks.assign(cs.size(), nullptr);
+            // what has no native kernel is compiled
+            std::vector<Circuit*> rest;
+            std::vector<size_t> at;
+            for (size_t t = 0; t < cs.size(); ++t)
+                if (!ks[t]) {
+                    rest.push_back(cs[t]);
+                    at.push_back(t);
+                }
+            if (!rest.empty()) {
+                const auto compiled = jit_kernels(rest, specialized_waves_per_eu(), nullptr,
+                                                  helpers ? CompileSplit::kEach : CompileSplit::kGroup);
+                for (size_t r = 0; r < rest.size(); ++r) ks[at[r]] = compiled[r];
+            }
         } catch (...) {
             // one kernel that does not compile must not keep the others on the interpreter
             ks.assign(group.size(), nullptr);
@@ -197,8 +221,26 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
     for (Job* j : act) sharing += j->jit ? 0 : 1;
     for (Job* j : act) {
         if (j->jit || j->compile_queued) continue;
+        const double left = 32.0 * (double)(j->range.end - j->cursor);
+        const NativeTier* nt = native_tier();
+        if (nt)
+            if (auto k = nt->ready(*j->c, slice_span(*j->c))) {
+                j->jit = k;
+                continue;
+            }
         if (auto k = jit_ready(*j->c, specialized_waves_per_eu())) {
             j->jit = k;
+            continue;
+        }
+        // A native kernel takes milliseconds to build, on a compile thread, while the job keeps
+        // running on the interpreter.
+        if (nt && jit_mode == 1) {
+            const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows(), left);
+            if (native_pays(*j->c, share * (double)std::max<size_t>(1, sharing), left, 1.0)) {
+                j->compile_queued = true;
+                compile_queue.push_back(j);
+                cv_compile.notify_one();
+            }
             continue;
         }
         // The runtime model's rule: remaining interpreter time at this job's share against the
