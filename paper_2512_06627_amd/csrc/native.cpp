@@ -56,7 +56,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight) {
     if (!n) return nullptr;
     auto k = std::make_shared<JitKernel>();
     k->native = n;
-    k->name = n->waves == 3 ? "fes_native_168" : "fes_native_256";
+    k->name = n->waves == 4 ? "fes_native_128" : n->waves == 3 ? "fes_native_168" : "fes_native_256";
     k->waves_per_eu = k->waves_used = n->waves;
     k->block = 64;
     std::vector<uint64_t> at;
@@ -196,7 +196,7 @@ void run_many(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks, co
     std::vector<double> cost(n);
     for (size_t i = 0; i < n; ++i) cost[i] = run_ms(*ks[i], 32.0 * (double)(ranges[i].end - ranges[i].begin));
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
-    const size_t best_off = 2 * kClaimBytes, desc_off = (best_off + 8 * n + 63) & ~size_t(63);
+    const size_t best_off = 3 * kClaimBytes, desc_off = (best_off + 8 * n + 63) & ~size_t(63);
     const size_t total = desc_off + sizeof(NativeDesc) * n;
     Buffer buf = dev.acquire(total);
     struct Releaser {
@@ -212,11 +212,11 @@ void run_many(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks, co
         uint64_t grid = 0;
         uint32_t lds = 0;
         const char* name = nullptr;
-    } groups[2];
+    } groups[3];
     size_t at = 0;
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < 3; ++t) {
         Group& g = groups[t];
-        const int waves = t == 0 ? 3 : 2;
+        const int waves = 4 - t;
         const uint64_t resident = resident_waves(dev, waves);
         const size_t from = at;
         uint64_t items = 0;

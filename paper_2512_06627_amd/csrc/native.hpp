@@ -37,6 +37,10 @@ struct InnerChoice {
 std::vector<InnerChoice> plan_inner(const Aig& g, const std::vector<uint32_t>& cone, uint32_t limit);
 SharedCone share_cofactors(const Aig& g, const std::vector<uint32_t>& cone, const std::vector<uint32_t>& inner);
 
+// The program's LUT steps in an order that keeps few values alive (outputs stay last): list
+// scheduling by how many operands a step is the last to read.
+void order_for_registers(LutProgram& lp);
+
 // Machine code of one pass.
 struct NativeCode {
     std::vector<uint32_t> words;
@@ -52,7 +56,7 @@ bool emit_native(const LutProgram& lp, const std::vector<uint64_t>& offset, int 
 struct NativeKernel {
     NativeCode code;
     std::vector<uint32_t> bits;  // inner inputs' bits of the half-word index, ascending
-    int waves = 3;               // per SIMD: 3 (152 registers) or 2 (240)
+    int waves = 3;               // per SIMD: 4, 3 or 2 (112, 152 or 240 registers)
     uint32_t limit = 0;          // inner inputs are below this input
     double build_ms = 0;
 };

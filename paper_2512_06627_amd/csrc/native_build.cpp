@@ -21,17 +21,34 @@ double clock_ms() {
     return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
 
-// Milliseconds of a wave64 VALU instruction over the whole chip (1.0e12 a second, what the passes
-// reach) and in one wave alone (about five clocks); of building, per gate of the shared graph.
+// Milliseconds of a wave64 VALU instruction over the whole chip (1.0e12 a second) and in one wave
+// alone (about five clocks); of building, per gate of the shared graph.
 constexpr double kMsPerWaveInstr = 1.0e-9, kMsPerLoneInstr = 2.1e-6, kBuildMsPerGate = 0.8e-3;
 constexpr double kLutsPerSharedGate = 0.26;
 constexpr double kChipWaves = 256 * 4 * 2;
-// Instructions of a pass that shares work: beyond about 56 KB it no longer stays in the 64 KB
-// instruction cache of two CUs.
-constexpr double kMaxSharedValu = 7000;
-// Registers of the mapped program against values alive at once in the graph (0.65 to 0.75 measured
-// on multipliers, up to 1.0 on layered cones).
-constexpr double kVgprsPerLive = 0.72;
+// A pass that shares work is not made longer than this: the 16x16 miter's 8,519 instructions with
+// five inner inputs still beat four (0.72 against 0.77 ms), though beyond 64 KB they stream through
+// the instruction cache.
+constexpr double kMaxSharedValu = 9000;
+// Registers of the mapped and reordered program against values alive at once in the graph (0.5 to
+// 0.75 on multipliers, up to 0.97 on layered cones).
+constexpr double kVgprsPerLive = 0.58;
+
+// Registers from v16 up and LDS spill slots by waves per SIMD (512 registers per SIMD lane, 160 KB
+// of LDS per CU).
+struct Tier {
+    int waves, vgprs, slots;
+};
+constexpr Tier kTiers[] = {{4, 112, 0}, {3, 152, 0}, {3, 152, 53}, {2, 240, 0}, {2, 240, 80}};
+
+// Time of an instruction against one at full rate, by the registers a pass is expected to take and
+// its length.  16x16 and MAC8 miters: four waves per SIMD 1.04 to 1.10e12 instructions a second,
+// three 1.00 to 1.07e12, two 0.88 to 0.94e12 (a wave issues at most every fifth clock); passes of
+// 40 KB and more 0.78 to 0.86e12 against 12 KB, through the instruction cache.
+double slowdown(double vgprs, double valu) {
+    const double waves = vgprs <= 112 ? 1.0 : vgprs <= 152 ? 1.03 : vgprs <= 205 ? 1.1 : vgprs <= 240 ? 1.2 : vgprs / 200;
+    return waves * (1.0 + 0.25 * std::min(1.0, std::max(0.0, (8 * valu - 12e3) / 28e3)));
+}
 
 }  // namespace
 
@@ -64,31 +81,34 @@ std::shared_ptr<NativeKernel> build_native(const Aig& g, const std::vector<uint3
     std::stable_sort(options.begin(), options.end(), by_time);
     // The shared graph of the best ones tells their true size and how many values they keep alive.
     std::vector<Option> tried;
-    const size_t most = weight > 0 ? 3 : 7;
+    const size_t most = weight > 0 ? 2 : 6;
     for (Option& o : options) {
         const uint32_t j = (uint32_t)o.c.inputs.size();
         if (tried.size() >= most && j) continue;
         o.s = share_cofactors(g, cone, o.c.inputs);
         const double vgprs = kVgprsPerLive * o.s.peak_live;
-        if (inner < 0 && j && (vgprs > 300 || kLutsPerSharedGate * (double)o.s.order.size() > kMaxSharedValu)) continue;
-        o.ms = estimate((double)o.s.order.size(), j) * (vgprs > 152 ? 1.04 : 1.0) * (vgprs > 240 ? vgprs / 240 : 1.0);
+        const double luts = kLutsPerSharedGate * (double)o.s.order.size();
+        if (inner < 0 && j && (vgprs > 320 || luts > kMaxSharedValu)) continue;
+        o.ms = estimate((double)o.s.order.size(), j) * slowdown(vgprs, luts);
         tried.push_back(std::move(o));
     }
     std::stable_sort(tried.begin(), tried.end(), by_time);
     for (Option& o : tried) {
         Plan p;
         p.order = std::move(o.s.order);
-        const LutProgram lp = make_lut_program(o.s.aig, p, 2);
+        LutProgram lp = make_lut_program(o.s.aig, p, 2);
+        order_for_registers(lp);
         auto k = std::make_shared<NativeKernel>();
         k->bits = o.s.bits;
         k->limit = limit;
-        k->waves = 3;
-        bool ok = emit_native(lp, o.s.offset, 152, 0, k->code);
-        if (!ok) {
-            k->waves = 2;
-            ok = emit_native(lp, o.s.offset, 240, 80, k->code);
-            // Shared work that has to go through LDS is no longer cheap.
-            if (ok && inner < 0 && !o.c.inputs.empty() && k->code.lds > k->code.valu / 8) ok = false;
+        bool ok = false;
+        for (const Tier& t : kTiers) {
+            k->waves = t.waves;
+            ok = emit_native(lp, o.s.offset, t.vgprs, t.slots, k->code);
+            // The third wave pays for a few LDS operations (one in twenty instructions), shared work
+            // for one in eight; beyond that the wave, or the sharing, costs more than it saves.
+            if (ok && k->code.lds > k->code.valu / (t.waves == 3 ? 20 : inner < 0 && !o.c.inputs.empty() ? 8 : 1)) ok = false;
+            if (ok) break;
         }
         if (!ok) continue;
         k->build_ms = clock_ms() - t0;

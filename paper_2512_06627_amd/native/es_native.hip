@@ -17,8 +17,11 @@
 // lowest failure found so far cannot lower it and is dropped.  A launch may hold many cones (each
 // with its own code address).
 //
-// The pass is bound by VALU issue (one v_bitop3_b32 per three-input LUT); one wave per workgroup
-// and three waves per SIMD (two for passes with many live values) keep the issue slots full.
+// The pass is bound by VALU issue (one v_bitop3_b32 per three-input LUT; a wave issues at most one
+// every five clocks, a SIMD one every two): one wave per workgroup, and as many of two to four waves
+// per SIMD as the pass's registers allow.  16x16 miter without inner inputs, 2^32 patterns: 2.96 ms
+// at four waves (1.10e12 instructions a second), 3.05 at three, 3.48 at two; with five inner inputs
+// 0.72 ms at two.
 //
 // Contract with the generated code.  Inputs: v2..v7 lane words of inputs 5..10, v8 byte address
 // of the lane's first LDS spill slot, s[38:39] packed half-word index, s[48:49] fes_native_report,
@@ -77,6 +80,9 @@ __device__ __forceinline__ uint64_t report_address() {
 #define S10(d) "s" #d "0", "s" #d "1", "s" #d "2", "s" #d "3", "s" #d "4", "s" #d "5", "s" #d "6", "s" #d "7", \
                "s" #d "8", "s" #d "9"
 #define SCLOB "s36", "s37", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", S10(6), S10(7), S10(8), S10(9)
+#define VCLOB_128                                                                                            \
+    "v15", "v16", "v17", "v18", "v19", V10(2), V10(3), V10(4), V10(5), V10(6), V10(7), V10(8), V10(9), V10(10), \
+        V10(11), "v120", "v121", "v122", "v123", "v124", "v125", "v126", "v127"
 #define VCLOB_168                                                                                            \
     "v15", "v16", "v17", "v18", "v19", V10(2), V10(3), V10(4), V10(5), V10(6), V10(7), V10(8), V10(9), V10(10), \
         V10(11), V10(12), V10(13), V10(14), V10(15), "v160", "v161", "v162", "v163", "v164", "v165", "v166", "v167"
@@ -140,7 +146,10 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
             }
             if (32u * real >= limit) break;  // nothing at or above here can lower best
             uint64_t found = ~0ull;
-            if constexpr (R == 168)
+            if constexpr (R == 128)
+                asm volatile("s_swappc_b64 s[36:37], s[50:51]" PASS_OPERANDS
+                             : SCLOB, "vcc", "scc", "memory", VCLOB_128);
+            else if constexpr (R == 168)
                 asm volatile("s_swappc_b64 s[36:37], s[50:51]" PASS_OPERANDS
                              : SCLOB, "vcc", "scc", "memory", VCLOB_168);
             else
@@ -158,7 +167,11 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
 
 }  // namespace
 
-// 168 registers per lane: three waves per SIMD; 256: two.  Passes of 152 and 240 registers.
+// 128 registers per lane: four waves per SIMD; 168: three; 256: two.  The pass has those from v16 up.
+extern "C" __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+fes_native_128(NativeLaunch L) {
+    native_body<128>(L);
+}
 extern "C" __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3)))
 fes_native_168(NativeLaunch L) {
     native_body<168>(L);

@@ -87,6 +87,14 @@ Text step(const std::vector<uint32_t>& w, size_t pc, Machine& m, bool run) {
             for (int l = 0; l < 64; ++l) m.v[d][l] = src_value(m, c, y, l) ^ (inv ? ~0u : 0u);
         return {b, c == 255 ? 2 : 1};
     }
+    if ((x & 0xFFFFFF00u) == 0xD1410000u) {
+        const uint32_t d = x & 255, c = y & 511;
+        std::snprintf(b, sizeof b, "v_mov_b32_e64 v%u, %s", d, src_text(c, 0).c_str());
+        if (run)
+            for (int l = 0; l < 64; ++l) m.v[d][l] = src_value(m, c, 0, l);
+        return {b, 2};
+    }
+    if (x == 0xBF800000u) return {"s_nop 0", 1};
     if ((x >> 23) == 0x126) {  // s_bfe_i32
         const uint32_t d = (x >> 16) & 127, c = x & 255;
         if (((x >> 8) & 255) != 255) std::exit(4);
