@@ -1,5 +1,6 @@
 // C ABI of the exact-simulation library.  No exception crosses this boundary:
 // every entry point catches, stores a thread-local message and returns a status.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -78,6 +79,8 @@ void fill_result(const Circuit& c, const HwRange& r, uint64_t best, fastlec_es_r
 // compile model's largest error here is 4%.  The LUT program (needed for the specialized
 // prediction) is only built when the interpreter's time could pay for a compile.
 constexpr double kCompileMargin = 1.2;
+// Planning a cone's interpreter stream, per AND gate, and loading a module of native kernels.
+constexpr double kPlanMsPerGate = 0.5e-3, kLoadMs = 1.2;
 
 // Specialized kernels in batches under AUTO (FASTLEC_ES_BATCH_JIT): 0 never, 1 by the runtime
 // model (default), 2 every cone whose kernel already exists (a test hook).
@@ -122,9 +125,9 @@ std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o
     const NativeTier* t = native_tier();
     if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) return t->get(c, span, 0.0);
     if (o.words_per_thread || o.wg_size) return nullptr;
-    const double interp = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
+    const double interp = model_interp_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
     if (auto k = t->ready(c, span)) return t->run_ms(*k, patterns) < interp ? k : nullptr;
-    return native_pays(c, interp, patterns, 1.0) ? t->get(c, span, 0.5) : nullptr;
+    return native_pays(c, interp, patterns) ? t->get(c, span, 0.5) : nullptr;
 }
 
 void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) {
@@ -309,24 +312,57 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                                   batch_jit_mode() == 1))) {
             const NativeTier* t = native_tier();
             std::vector<size_t> want;
-            for (size_t i = 0; i < k; ++i) {
-                Circuit& c = *v[i];
-                const uint64_t span = rs[i].end - rs[i].begin;
-                const double patterns = 32.0 * (double)span;
-                if (o.kernel == FASTLEC_KERNEL_AUTO) {
-                    // A grouped launch's share of a cone, without the launch itself.
-                    const double interp = model_interp_share_ms(c.interp_gates(), c.interp_rows(), patterns);
-                    const std::shared_ptr<JitKernel> have = t->ready(c, span);
-                    if (have ? t->share_ms(*have, patterns) >= interp
-                             : !native_pays(c, interp, patterns, 1.0 / 8)) continue;
+            if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) {
+                for (size_t i = 0; i < k; ++i) want.push_back(i);
+            } else {
+                // A cone's gain is its share of a grouped interpreter launch against its share of a
+                // native one; where the interpreter's stream is not planned yet, that planning
+                // (about as long as building a kernel) is saved too.  Building and planning run on
+                // all host threads.  A module load on top has to be paid by all new kernels together.
+                const double threads = (double)std::min<size_t>({k, 16, std::max(1u, std::thread::hardware_concurrency())});
+                double gain = 0;
+                std::vector<size_t> fresh;
+                std::vector<double> fresh_ms;
+                for (size_t i = 0; i < k; ++i) {
+                    Circuit& c = *v[i];
+                    const uint64_t span = rs[i].end - rs[i].begin;
+                    const double patterns = 32.0 * (double)span;
+                    const double interp = model_interp_share_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
+                    if (const std::shared_ptr<JitKernel> have = t->ready(c, span)) {
+                        if (t->share_ms(*have, patterns) < interp) want.push_back(i);
+                        continue;
+                    }
+                    const double plan = c.planned(4) ? 0.0 : kPlanMsPerGate * c.plan1.num_ands_tfi;
+                    const double net = interp + c.interp_ms_spent.load(std::memory_order_relaxed) +
+                                       (plan - 1.5 * t->guess_build_ms(c)) / threads;
+                    fresh.push_back(i);
+                    fresh_ms.push_back(interp);
+                    if (net > 0) gain += net;
+                    else fresh_ms.back() = -interp;  // not this one
                 }
-                want.push_back(i);
+                for (size_t j = 0; j < fresh.size(); ++j) {
+                    Circuit& c = *v[fresh[j]];
+                    if (gain > kLoadMs && fresh_ms[j] > 0) {
+                        want.push_back(fresh[j]);
+                        continue;
+                    }
+                    double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
+                    while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + std::abs(fresh_ms[j]),
+                                                                    std::memory_order_relaxed)) {
+                    }
+                }
+                std::sort(want.begin(), want.end());
             }
+            const bool forced = o.kernel == FASTLEC_KERNEL_SPECIALIZED;
             std::vector<std::shared_ptr<JitKernel>> got(want.size());
-            parallel_for(want.size(), [&](size_t j) {
-                const uint64_t span = rs[want[j]].end - rs[want[j]].begin;
-                if (o.kernel == FASTLEC_KERNEL_AUTO) got[j] = t->ready(*v[want[j]], span);
-                if (!got[j]) got[j] = t->get(*v[want[j]], span, o.kernel == FASTLEC_KERNEL_AUTO ? 0.2 : 0.0);
+            std::vector<size_t> build;
+            for (size_t j = 0; j < want.size(); ++j) {
+                got[j] = t->ready(*v[want[j]], rs[want[j]].end - rs[want[j]].begin);
+                if (!got[j]) build.push_back(j);
+            }
+            parallel_for(build.size(), [&](size_t b) {
+                const size_t j = build[b];
+                got[j] = t->get(*v[want[j]], rs[want[j]].end - rs[want[j]].begin, forced ? 0.0 : 0.2);
             });
             for (size_t j = 0; j < want.size(); ++j) {
                 if (!got[j]) continue;  // its values fit neither registers nor LDS
@@ -335,6 +371,11 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                 nk.push_back(got[j]);
             }
         }
+        // The interpreter's streams of the others, planned on host threads.
+        std::vector<Circuit*> plan;
+        for (size_t i = 0; i < k; ++i)
+            if (!is_nat[i] && !v[i]->planned(4)) plan.push_back(v[i]);
+        parallel_for(plan.size(), [&](size_t j) { (void)plan[j]->plan_for(4); });
         // Of the others, cones the runtime model gives to the specialized kernel (AUTO only) run as their own
         // launches; the rest share interpreter launches.  Their kernels compile together as
         // hipRTC programs side by side in helper processes, so a cone is a candidate when its
@@ -492,33 +533,52 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             }
             groups[3 + b].push_back(i);
         }
-        double total_ms = 0;
+        std::vector<BatchPart> parts;
         for (auto& gi : groups) {
-            std::vector<Circuit*> gv;
-            std::vector<HwRange> gr;
+            BatchPart p;
+            p.entries = gi.second;
             for (size_t i : gi.second) {
-                gv.push_back(v[i]);
-                gr.push_back(rs[i]);
+                p.cs.push_back(v[i]);
+                p.ranges.push_back(rs[i]);
             }
             // Schedule: the caller's fields when given, otherwise the autotuner's choice.
-            Schedule sch;
-            if (o.words_per_thread || o.wg_size) sch = default_schedule(dev, gv, &o);
-            else sch = autotune(dev, gv, gr, stream, o.kernel == FASTLEC_KERNEL_INTERP_HBM);
-            if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
-            std::vector<uint64_t> best;
-            double ms = 0;
-            run_batch_graph(dev, gv, gr, sch, stream, best, &ms);
-            total_ms += ms;
-            for (size_t t = 0; t < gi.second.size(); ++t) {
-                const size_t i = gi.second[t];
-                std::memset(&out[i], 0, sizeof(out[i]));
-                fill_result(*v[i], rs[i], best[t], &out[i]);
-                out[i].predicted_ms = model_interp_ms(v[i]->interp_gates(), v[i]->interp_rows(),
-                                                      32.0 * (double)(rs[i].end - rs[i].begin));
+            if (o.words_per_thread || o.wg_size) p.sch = default_schedule(dev, p.cs, &o);
+            else p.sch = autotune(dev, p.cs, p.ranges, stream, o.kernel == FASTLEC_KERNEL_INTERP_HBM);
+            if (o.tile_words) p.sch.tile_hw = 2ull * o.tile_words;
+            parts.push_back(std::move(p));
+        }
+        if (!nat.empty()) {
+            BatchPart p;
+            p.entries = nat;
+            p.native = nk;
+            for (size_t i : nat) p.ranges.push_back(rs[i]);
+            parts.push_back(std::move(p));
+        }
+        // All of it as launches on one stream with one wait.
+        double total_ms = 0;
+        std::vector<uint64_t> found(k, ~0ull);
+        if (const BatchRunner run = batch_runner()) {
+            if (!parts.empty()) run(dev, parts, k, stream, found, &total_ms);
+        } else {
+            for (const BatchPart& p : parts) {  // host-only builds have no native kernels
+                std::vector<uint64_t> best;
+                double ms = 0;
+                run_batch_graph(dev, p.cs, p.ranges, p.sch, stream, best, &ms);
+                total_ms += ms;
+                for (size_t t = 0; t < p.entries.size(); ++t) found[p.entries[t]] = best[t];
             }
         }
-        for (size_t i = 0; i < k; ++i)
-            if (!is_spec[i] && !is_nat[i] && !is_alone[i]) out[i].kernel_ms = total_ms;
+        for (const BatchPart& p : parts)
+            for (size_t t = 0; t < p.entries.size(); ++t) {
+                const size_t i = p.entries[t];
+                const double patterns = 32.0 * (double)(rs[i].end - rs[i].begin);
+                std::memset(&out[i], 0, sizeof(out[i]));
+                fill_result(*v[i], rs[i], found[i], &out[i]);
+                out[i].kernel_ms = total_ms;
+                out[i].predicted_ms = p.native.empty()
+                                          ? model_interp_ms(v[i]->interp_gates(), v[i]->interp_rows(), patterns)
+                                          : native_tier()->run_ms(*p.native[t], patterns);
+            }
         auto run_alone = [&](size_t i) {
             std::vector<Circuit*> one{v[i]};
             std::vector<HwRange> r1{rs[i]};
@@ -534,20 +594,6 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                                                   32.0 * (double)(rs[i].end - rs[i].begin));
         };
         for (size_t i : alone) run_alone(i);
-        if (!nat.empty()) {
-            std::vector<HwRange> nr;
-            for (size_t i : nat) nr.push_back(rs[i]);
-            std::vector<uint64_t> best;
-            double ms = 0;
-            native_tier()->run_many(dev, nk, nr, stream, best, &ms);
-            for (size_t j = 0; j < nat.size(); ++j) {
-                const size_t i = nat[j];
-                std::memset(&out[i], 0, sizeof(out[i]));
-                fill_result(*v[i], rs[i], best[j], &out[i]);
-                out[i].kernel_ms = ms;
-                out[i].predicted_ms = native_tier()->run_ms(*nk[j], 32.0 * (double)(rs[i].end - rs[i].begin));
-            }
-        }
         if (compile_job.t.joinable()) compile_job.t.join();
         if (compile_error) std::rethrow_exception(compile_error);
         if (!spec.empty()) {

@@ -52,6 +52,20 @@ __device__ __forceinline__ const FES_CONST T* as_const(const T* p) {
     return (const FES_CONST T*)(p);
 }
 
+// Next item number of a claim counter.  Each of the wave's 64 lanes adds 1, which the compiler turns
+// into one atomic of 64; an operand that differs by lane (1 from lane 0 only) becomes a scalar loop
+// over the 64 lanes, as long as a pass over a hundred gates.  A launch with a wave for every item
+// claims nothing (wave w takes item w).
+__device__ __forceinline__ uint64_t next_claim(unsigned long long* counter) {
+    return uniform64(atomicAdd(counter, 1ull)) >> 6;
+}
+
+// The launch's descriptors: its device array, or the one that comes with the kernel's arguments.
+__device__ __forceinline__ const FES_CONST ConeDesc* cones_of(const InterpLaunch& L) {
+    if (L.cones) return as_const(L.cones);
+    return &((const FES_CONST InterpLaunch*)__builtin_amdgcn_kernarg_segment_ptr())->one;
+}
+
 template <int K>
 struct alignas(4 * K) Words {
     uint32_t w[K];
@@ -86,9 +100,9 @@ __global__ void __launch_bounds__(1024) es_interp_kernel(InterpLaunch L) {
     uint32_t* col = file + lane * K;  // row r of this lane: col + r * kRowWords
     using V = Words<K>;
 
-    // Control flow stays wave-uniform: every lane takes part in the claim (lane 0 adds 1,
-    // the others 0) and in the atomicMin (all lanes hold the same value), so no branch
-    // depends on the lane and every loop exit is a scalar branch.
+    // Control flow stays wave-uniform: every lane takes part in the claim and in the
+    // atomicMin (all lanes hold the same value), so no branch depends on the lane and every
+    // loop exit is a scalar branch.
     const uint32_t wave_gid = blockIdx.x * (blockDim.x >> 6) + wave;
     // A grid with fewer waves than counters uses one counter per wave, so every counter in
     // use has a wave and every item is claimed.
@@ -96,15 +110,16 @@ __global__ void __launch_bounds__(1024) es_interp_kernel(InterpLaunch L) {
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
     const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);  // wave-uniform
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
-    for (;;) {
-        const uint64_t k = uniform64(atomicAdd(counter, lane == 0 ? 1ull : 0ull));
-        const uint64_t item = claim + k * nclaim;
+    const bool one_each = L.total_items <= waves;
+    for (bool more = true; more;) {
+        const uint64_t item = one_each ? wave_gid : claim + next_claim(counter) * nclaim;
+        more = !one_each;
         if (item >= L.total_items) break;
         if (L.cancel && __builtin_amdgcn_readfirstlane(
                             __hip_atomic_load(L.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)))
             break;
 
-        const FES_CONST ConeDesc* cones = as_const(L.cones);
+        const FES_CONST ConeDesc* cones = cones_of(L);
         uint32_t lo = 0, hi = L.num_cones - 1;  // cone holding this item (uniform search)
         while (lo < hi) {
             uint32_t mid = (lo + hi + 1) >> 1;
@@ -487,14 +502,15 @@ es_interp_regs_kernel(InterpLaunch L) {
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
     const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
-    for (;;) {
-        const uint64_t k = uniform64(atomicAdd(counter, lane == 0 ? 1ull : 0ull));
-        const uint64_t item = claim + k * nclaim;
+    const bool one_each = L.total_items <= waves;
+    for (bool more = true; more;) {
+        const uint64_t item = one_each ? wave_gid : claim + next_claim(counter) * nclaim;
+        more = !one_each;
         if (item >= L.total_items) break;
         if (L.cancel && __builtin_amdgcn_readfirstlane(
                             __hip_atomic_load(L.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)))
             break;
-        const FES_CONST ConeDesc* cones = as_const(L.cones);
+        const FES_CONST ConeDesc* cones = cones_of(L);
         uint32_t lo = 0, hi = L.num_cones - 1;
         while (lo < hi) {
             uint32_t mid = (lo + hi + 1) >> 1;
@@ -676,16 +692,17 @@ es_sim_regs_kernel(InterpLaunch L) {
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
     const uint32_t claim = __builtin_amdgcn_readfirstlane(blockIdx.x % nclaim);
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
-    const FES_CONST ConeDesc* c = as_const(L.cones);
+    const FES_CONST ConeDesc* c = cones_of(L);
     const uint32_t n = __builtin_amdgcn_readfirstlane(c->n_inputs);
     const uint32_t nb = __builtin_amdgcn_readfirstlane(c->n_instr / 4u);
     const uint32_t* prog = (const uint32_t*)c->prog;
     const uint64_t W = L.sim_words, tile = c->tile_hw;
     const uint64_t wb = W * 4u;
     const uint64_t sig = (uint64_t)L.sim_sig;
-    for (;;) {
-        const uint64_t k = uniform64(atomicAdd(counter, lane == 0 ? 1ull : 0ull));
-        const uint64_t item = claim + k * nclaim;
+    const bool one_each = L.total_items <= waves;
+    for (bool more = true; more;) {
+        const uint64_t item = one_each ? blockIdx.x : claim + next_claim(counter) * nclaim;
+        more = !one_each;
         if (item >= L.total_items) break;
         const uint64_t hw0 = item * tile, hw_stop = min(hw0 + tile, W);
         for (uint64_t base = hw0; base < hw_stop; base += 64u) {
@@ -703,7 +720,29 @@ hipError_t launch_sim_regs_t(const InterpLaunch& L, int grid, hipStream_t stream
     return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(256) finish_kernel(unsigned long long* __restrict__ claims, uint32_t words,
+                                                     unsigned long long* __restrict__ best, uint32_t n,
+                                                     unsigned long long* __restrict__ host_best) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < n) {
+        host_best[i] = best[i];
+        best[i] = ~0ull;
+    }
+    if (i < words) claims[i] = 0ull;
+}
+
+// Registers launch_finish with the host runtime.
+const bool g_finish_registered = (register_finish(&launch_finish), true);
+
 }  // namespace
+
+hipError_t launch_finish(unsigned long long* claims, uint32_t words, unsigned long long* best, uint32_t n,
+                         unsigned long long* host_best, hipStream_t stream) {
+    const uint32_t threads = words > n ? words : n;
+    hipLaunchKernelGGL(finish_kernel, dim3((threads + 255) / 256), dim3(256), 0, stream, claims, words, best, n,
+                       host_best);
+    return hipGetLastError();
+}
 
 int interp_regs_rows(uint32_t rows, int* waves_per_simd) {
     int w = 0, r = 0;

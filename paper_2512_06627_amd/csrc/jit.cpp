@@ -767,8 +767,14 @@ void run_jit(Device& dev, Circuit& c, JitKernel& k, const HwRange& r, uint64_t t
              const int* cancel, uint64_t* best_out, double* kernel_ms, DevMem mem) {
     (void)c;
     const JitLaunchPlan lp = jit_prepare(dev, k, r, tile_hw);
-    if (mem.ptr) check_dev_mem(mem, kClaimBytes + 8);
-    Buffer buf = dev.acquire(mem.ptr ? 0 : 4096, 4096);
+    if (!mem.ptr) {
+        *best_out = run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& s) {
+            jit_enqueue(lp, (uint64_t*)s.claims(), (uint64_t*)s.best(), cancel, stream);
+        });
+        return;
+    }
+    check_dev_mem(mem, kClaimBytes + 8);
+    Buffer buf = dev.acquire(0, 4096);
     struct Releaser {
         Device& d;
         Buffer b;
@@ -779,7 +785,7 @@ void run_jit(Device& dev, Circuit& c, JitKernel& k, const HwRange& r, uint64_t t
     std::memset(host, 0, kClaimBytes);
     uint64_t* hbest = host + kClaimBytes / 8;
     *hbest = ~0ull;  // the claim counters at 0, best right after them
-    uint8_t* devp = (uint8_t*)(mem.ptr ? mem.ptr : buf.dev);
+    uint8_t* devp = (uint8_t*)mem.ptr;
     uint64_t* next_item = (uint64_t*)devp;
     uint64_t* best = (uint64_t*)(devp + kClaimBytes);
     hipEvent_t e0, e1;

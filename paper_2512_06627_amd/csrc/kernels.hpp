@@ -36,7 +36,7 @@ struct alignas(128) LaunchCtl {
 static_assert(sizeof(LaunchCtl) == kClaimBytes, "control block layout");
 
 struct InterpLaunch {
-    const ConeDesc* cones;
+    const ConeDesc* cones;    // device array, or null for a launch of the single cone `one`
     uint32_t num_cones;
     uint32_t rows_max;        // value-file rows per wave
     uint64_t total_items;
@@ -49,6 +49,7 @@ struct InterpLaunch {
     const uint32_t* sim_pi = nullptr;  // n rows of sim_words 32-bit words (row i = input i)
     uint32_t* sim_sig = nullptr;       // rows 0..max_var of sim_words words (row v = variable v)
     uint64_t sim_words = 0;
+    ConeDesc one{};                    // comes with the kernel's arguments: nothing to upload
 };
 
 // Launch the interpreter.  K = half-words per lane per row (1, 2, 4); B = bundle size
@@ -94,6 +95,18 @@ hipError_t launch_sim_regs(const InterpLaunch& L, int regs, int grid, hipStream_
 // does, with the waves per SIMD it allows.  launch_interp_regs: `regs` is that file size.
 int interp_regs_rows(uint32_t rows, int* waves_per_simd);
 hipError_t launch_interp_regs(const InterpLaunch& L, int regs, int grid, hipStream_t stream);
+
+// After the kernels of a call: best[0..n) goes to pinned host memory, and best[] and the `words`
+// claim words return to their state before a launch (all ones and zero), so that the next call
+// on this control block uploads nothing.
+hipError_t launch_finish(unsigned long long* claims, uint32_t words, unsigned long long* best, uint32_t n,
+                         unsigned long long* host_best, hipStream_t stream);
+
+using FinishLaunch = decltype(&launch_finish);
+// The library's launch_finish; null in host-only builds of the runtime, which then upload and read
+// back the control block around every call.
+void register_finish(FinishLaunch f);
+FinishLaunch finish_launch();
 
 // Largest per-workgroup dynamic LDS the interpreter may request.
 size_t interp_lds_bytes(uint32_t rows, int K, int waves_per_block);

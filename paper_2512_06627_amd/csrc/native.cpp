@@ -83,8 +83,7 @@ double guess_run_ms(const Circuit& c, double patterns) {
     return 0.012 + native_run_ms(0.26 * c.plan1.num_ands_tfi + 10, 0, passes_of(patterns));
 }
 
-// Building and loading: a module load takes 0.6 to 1.3 ms.
-double guess_build_ms(const Circuit& c) { return 1.0 + native_build_ms(c.plan1.num_ands_tfi); }
+double guess_build_ms(const Circuit& c) { return native_build_ms(c.plan1.num_ands_tfi); }
 
 void counts(const JitKernel& k, uint32_t* inner, uint32_t* valu, uint32_t* waves) {
     if (inner) *inner = (uint32_t)k.native->bits.size();
@@ -145,115 +144,7 @@ void launch(hipFunction_t fn, const NativeLaunch& L, uint64_t grid, uint32_t lds
     FES_HIP(hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, 64, 1, 1, lds, stream, args, nullptr));
 }
 
-// Kernels of a batch as one code object.  Sets are kept (least recently used dropped) so that a
-// batch of the same kernels loads nothing again.
-struct KernelSet {
-    std::vector<std::shared_ptr<JitKernel>> ks;
-    std::shared_ptr<CodeObject> code;
-    std::vector<uint64_t> at;
-    uint64_t last_use = 0;
-};
-constexpr size_t kMaxSets = 8;
-std::mutex g_sets_mu;
-std::vector<std::shared_ptr<KernelSet>>& sets() {
-    static std::vector<std::shared_ptr<KernelSet>> v;
-    return v;
-}
-uint64_t g_set_clock = 0;
-
-std::shared_ptr<KernelSet> set_of(const std::vector<std::shared_ptr<JitKernel>>& ks) {
-    std::lock_guard<std::mutex> g(g_sets_mu);
-    for (auto& s : sets())
-        if (s->ks == ks) {
-            s->last_use = ++g_set_clock;
-            return s;
-        }
-    auto s = std::make_shared<KernelSet>();
-    s->ks = ks;
-    std::vector<const NativeCode*> codes;
-    for (auto& k : ks) codes.push_back(&k->native->code);
-    s->code = std::make_shared<CodeObject>();
-    s->code->bytes = std::make_shared<const std::vector<char>>(native_code_object(codes, &s->at));
-    s->last_use = ++g_set_clock;
-    auto& v = sets();
-    if (v.size() >= kMaxSets)
-        v.erase(std::min_element(v.begin(), v.end(),
-                                 [](const auto& a, const auto& b) { return a->last_use < b->last_use; }));
-    v.push_back(s);
-    return s;
-}
-
-void run_many(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks, const std::vector<HwRange>& ranges,
-              hipStream_t stream, std::vector<uint64_t>& best, double* ms) {
-    const size_t n = ks.size();
-    best.assign(n, ~0ull);
-    if (ms) *ms = 0;
-    if (!n) return;
-    const std::shared_ptr<KernelSet> set = set_of(ks);
-    // Longest first within a register tier, so that the short ones fill the end of the launch.
-    std::vector<size_t> order(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::vector<double> cost(n);
-    for (size_t i = 0; i < n; ++i) cost[i] = run_ms(*ks[i], 32.0 * (double)(ranges[i].end - ranges[i].begin));
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
-    const size_t best_off = 3 * kClaimBytes, desc_off = (best_off + 8 * n + 63) & ~size_t(63);
-    const size_t total = desc_off + sizeof(NativeDesc) * n;
-    Buffer buf = dev.acquire(total);
-    struct Releaser {
-        Device& d;
-        Buffer b;
-        ~Releaser() { d.release(b); }
-    } rel{dev, buf};
-    uint8_t *host = (uint8_t*)buf.host, *devp = (uint8_t*)buf.dev;
-    std::memset(host, 0, best_off);
-    std::memset(host + best_off, 0xFF, 8 * n);
-    struct Group {
-        NativeLaunch L{};
-        uint64_t grid = 0;
-        uint32_t lds = 0;
-        const char* name = nullptr;
-    } groups[3];
-    size_t at = 0;
-    for (int t = 0; t < 3; ++t) {
-        Group& g = groups[t];
-        const int waves = 4 - t;
-        const uint64_t resident = resident_waves(dev, waves);
-        const size_t from = at;
-        uint64_t items = 0;
-        for (size_t i : order) {
-            const NativeKernel& k = *ks[i]->native;
-            if (k.waves != waves) continue;
-            items = fill(k, set->at[i], ranges[i], 0, resident, items, (uint32_t)i,
-                         ((NativeDesc*)(host + desc_off))[at++]);
-            g.lds = std::max(g.lds, k.code.lds_slots * 256);
-            g.name = ks[i]->name.c_str();
-        }
-        g.L.cones = (const NativeDesc*)(devp + desc_off) + from;
-        g.L.num_cones = (uint32_t)(at - from);
-        g.L.total_items = items;
-        g.L.counters = (unsigned long long*)(devp + t * kClaimBytes);
-        g.L.best = (unsigned long long*)(devp + best_off);
-        g.grid = std::min(items, resident);
-    }
-    ScopedEvent e0, e1;
-    FES_HIP(hipMemcpyAsync(devp, host, total, hipMemcpyHostToDevice, stream));
-    FES_HIP(hipEventRecord(e0.e, stream));
-    for (Group& g : groups) {
-        if (!g.L.num_cones) continue;
-        hipFunction_t fn;
-        FES_HIP(hipModuleGetFunction(&fn, set->code->module(dev.ordinal), g.name));
-        launch(fn, g.L, g.grid, g.lds, stream);
-    }
-    FES_HIP(hipEventRecord(e1.e, stream));
-    FES_HIP(hipMemcpyAsync(host + best_off, devp + best_off, 8 * n, hipMemcpyDeviceToHost, stream));
-    FES_HIP(hipStreamSynchronize(stream));
-    float t = 0;
-    FES_HIP(hipEventElapsedTime(&t, e0.e, e1.e));
-    if (ms) *ms = t;
-    std::memcpy(best.data(), host + best_off, 8 * n);
-}
-
-const NativeTier kTier = {ready, get, run_ms, share_ms, guess_run_ms, guess_build_ms, counts, run_many};
+const NativeTier kTier = {ready, get, run_ms, share_ms, guess_run_ms, guess_build_ms, counts};
 const bool g_registered = (register_native_tier(&kTier), true);
 
 }  // namespace
@@ -282,6 +173,54 @@ void native_enqueue(const JitLaunchPlan& lp, uint64_t* next_item, uint64_t* best
     L.best = (unsigned long long*)best;
     L.one = lp.one;
     launch(lp.fn, L, (uint64_t)lp.grid, lp.lds_bytes, stream);
+}
+
+NativeMany native_many_fill(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks,
+                            const std::vector<HwRange>& ranges, const std::vector<uint32_t>& best_index,
+                            NativeDesc* host_descs, const NativeDesc* dev_descs, uint8_t* claims,
+                            unsigned long long* best) {
+    NativeMany m;
+    std::vector<const NativeCode*> codes;
+    for (auto& k : ks) codes.push_back(&k->native->code);
+    std::vector<uint64_t> at;
+    m.code = std::make_shared<CodeObject>();
+    m.code->bytes = std::make_shared<const std::vector<char>>(native_code_object(codes, &at));
+    // Longest first within a register tier, so that the short ones fill the end of the launch.
+    std::vector<size_t> order(ks.size());
+    std::iota(order.begin(), order.end(), 0);
+    std::vector<double> cost(ks.size());
+    for (size_t i = 0; i < ks.size(); ++i) cost[i] = share_ms(*ks[i], 32.0 * (double)(ranges[i].end - ranges[i].begin));
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+    size_t next = 0;
+    for (int t = 0; t < kNativeTiers; ++t) {
+        NativeManyLaunch& g = m.tier[t];
+        const int waves = 4 - t;
+        const uint64_t resident = resident_waves(dev, waves);
+        const size_t from = next;
+        uint64_t items = 0;
+        const char* name = nullptr;
+        for (size_t i : order) {
+            const NativeKernel& k = *ks[i]->native;
+            if (k.waves != waves) continue;
+            items = fill(k, at[i], ranges[i], 0, resident, items, best_index[i], host_descs[next++]);
+            g.lds = std::max(g.lds, k.code.lds_slots * 256);
+            name = ks[i]->name.c_str();
+        }
+        g.L.cones = dev_descs + from;
+        g.L.num_cones = (uint32_t)(next - from);
+        if (!g.L.num_cones) continue;
+        g.L.total_items = items;
+        g.L.counters = (unsigned long long*)(claims + (size_t)t * kClaimBytes);
+        g.L.best = best;
+        g.grid = std::min(items, resident);
+        FES_HIP(hipModuleGetFunction(&g.fn, m.code->module(dev.ordinal), name));
+    }
+    return m;
+}
+
+void native_many_enqueue(const NativeMany& m, hipStream_t stream) {
+    for (const NativeManyLaunch& g : m.tier)
+        if (g.L.num_cones) launch(g.fn, g.L, g.grid, g.lds, stream);
 }
 
 }  // namespace fes

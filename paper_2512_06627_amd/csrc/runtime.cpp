@@ -41,11 +41,18 @@ double now_ms() {
     return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
 
-// ---- native tier ---------------------------------------------------------------
+// ---- parts that host-only builds of the runtime do without ----------------------
 
 namespace {
 const NativeTier* g_native_tier = nullptr;
-}
+FinishLaunch g_finish = nullptr;
+BatchRunner g_batch_runner = nullptr;
+}  // namespace
+
+void register_finish(FinishLaunch f) { g_finish = f; }
+FinishLaunch finish_launch() { return g_finish; }
+void register_batch_runner(BatchRunner r) { g_batch_runner = r; }
+BatchRunner batch_runner() { return g_batch_runner; }
 
 void register_native_tier(const NativeTier* t) { g_native_tier = t; }
 
@@ -57,11 +64,12 @@ const NativeTier* native_tier() {
     return on ? g_native_tier : nullptr;
 }
 
-bool native_pays(Circuit& c, double interp_ms, double patterns, double build_share) {
+bool native_pays(Circuit& c, double interp_ms, double patterns) {
     const NativeTier* t = native_tier();
     if (!t) return false;
-    // Margin on the building: its estimate is good to about a factor of 1.5.
-    const double cost = t->guess_run_ms(c, patterns) + 1.5 * build_share * t->guess_build_ms(c);
+    // Margin on the building: its estimate is good to about a factor of 1.5.  A module load takes
+    // 0.6 to 1.3 ms.
+    const double cost = t->guess_run_ms(c, patterns) + 1.5 * (t->guess_build_ms(c) + 1.0);
     double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
     if (interp_ms + spent > cost) return true;
     while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + interp_ms, std::memory_order_relaxed)) {
@@ -106,6 +114,13 @@ const Plan& Circuit::plan_for(uint32_t bundle) {
     if (it == bundled.end()) it = bundled.emplace(bundle, std::make_unique<Plan>(make_plan(fused, Order::Auto, bundle))).first;
     return *it->second;
 }
+
+bool Circuit::planned(uint32_t bundle) {
+    std::lock_guard<std::mutex> g(mu);
+    return bundled.count(bundle) != 0;
+}
+
+uint32_t Circuit::interp_rows_guess() { return planned(4) ? interp_rows() : plan1.rows; }
 
 uint32_t Circuit::lut_steps_known() {
     std::lock_guard<std::mutex> g(mu);
@@ -276,6 +291,52 @@ Buffer Device::acquire(size_t dev_bytes, size_t host_bytes) {
 void Device::release(Buffer b) {
     std::lock_guard<std::mutex> g(mu);
     free_bufs.push_back(b);
+}
+
+ControlSlot Device::acquire_slot() {
+    {
+        std::lock_guard<std::mutex> g(mu);
+        if (!free_slots.empty()) {
+            ControlSlot s = free_slots.back();
+            free_slots.pop_back();
+            return s;
+        }
+    }
+    const size_t bytes = kClaimBytes + 8;
+    Buffer b = acquire(bytes);  // stays with the slot
+    std::memset(b.host, 0, kClaimBytes);
+    std::memset((uint8_t*)b.host + kClaimBytes, 0xFF, 8);
+    ControlSlot s;
+    s.dev = (uint8_t*)b.dev;
+    FES_HIP(hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream));
+    FES_HIP(hipStreamSynchronize(stream));
+    s.host_best = (unsigned long long*)b.host;
+    FES_HIP(hipEventCreate(&s.e0));
+    FES_HIP(hipEventCreate(&s.e1));
+    return s;
+}
+
+void Device::release_slot(const ControlSlot& s) {
+    std::lock_guard<std::mutex> g(mu);
+    free_slots.push_back(s);
+}
+
+uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
+                     const std::function<void(const ControlSlot&)>& launch) {
+    // The start of this path cost 28 us around an empty kernel: an upload, a read-back and two events
+    // made and destroyed; with the finish kernel and kept events it costs 18 us.
+    const ControlSlot s = dev.acquire_slot();
+    FES_HIP(hipEventRecord(s.e0, stream));
+    launch(s);
+    FES_HIP(hipEventRecord(s.e1, stream));
+    FES_HIP(g_finish(s.claims(), kClaimBytes / 8, s.best(), 1, s.host_best, stream));
+    FES_HIP(hipStreamSynchronize(stream));
+    float ms = 0;
+    FES_HIP(hipEventElapsedTime(&ms, s.e0, s.e1));
+    if (kernel_ms) *kernel_ms = ms;
+    const uint64_t best = *s.host_best;
+    dev.release_slot(s);
+    return best;
 }
 
 Device& device(int ordinal) {
@@ -558,6 +619,26 @@ void run_interp(Device& dev, const std::vector<Circuit*>& cs, const std::vector<
     const uint32_t rows_max = rows_for(cs, sch.B);
     const size_t waves = (size_t)sch.grid * (sch.block / 64);
     const size_t file_bytes = (sch.lds || sch.regs) ? 0 : waves * rows_max * 64ull * sch.K * 4ull;
+    if (k == 1 && !file_bytes && !mem.ptr && g_finish) {  // nothing but its arguments goes to the kernel
+        InterpLaunch L{};
+        const Instr* prog = sch.regs ? (const Instr*)cs[0]->device_regs_stream(dev.ordinal, stream)
+                                     : cs[0]->device_prog(dev.ordinal, sch.B, stream);
+        L.total_items = fill_desc(cs[0]->plan_for(sch.B), prog, ranges[0], 0, sch, 0, L.one);
+        L.num_cones = 1;
+        L.rows_max = rows_max;
+        L.cancel = cancel;
+        Schedule fit = sch;  // no more workgroups than work items
+        const uint64_t per_block = (uint64_t)(sch.block / 64);
+        fit.grid = (int)std::min<uint64_t>((uint64_t)sch.grid, (L.total_items + per_block - 1) / per_block);
+        trace("interp launch: 1 cone, %llu items, K=%d B=%d %s grid=%d block=%d rows=%u",
+              (unsigned long long)L.total_items, sch.K, sch.B, sch.regs ? "regs" : "lds", fit.grid, sch.block, rows_max);
+        best.assign(1, run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& s) {
+                        L.ctl = (LaunchCtl*)s.claims();
+                        L.best = s.best();
+                        FES_HIP(launch_schedule(L, fit, stream));
+                    }));
+        return;
+    }
     Layout lay = layout(k, file_bytes);
     if (mem.ptr) check_dev_mem(mem, lay.total);
     // With caller memory the pool only supplies the pinned staging of the control block.

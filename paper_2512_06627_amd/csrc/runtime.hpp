@@ -99,6 +99,9 @@ struct Circuit {
     const LutProgram& lut_program();
     // Value-file rows of the interpreter's stream in bundles of 4 (the runtime model's tier).
     uint32_t interp_rows() { return plan_for(4).rows; }
+    // The same without planning that stream if it is not there yet: the sequential plan's rows.
+    uint32_t interp_rows_guess();
+    bool planned(uint32_t bundle);
     // The register tier's stream: the plan in bundles of 4, each bundle kRegsBundleWords words
     // (operand and destination words, complement and XOR masks, output flags; see
     // encode_regs_stream; one bundle of zero padding at the end).  Host copy and per-device
@@ -128,6 +131,16 @@ struct Buffer {
     size_t host_bytes = 0;
 };
 
+// A control block of one check that no caller is using: claim counters zero, best all ones (the
+// finish kernel leaves it so), the result in pinned host memory, and two events.
+struct ControlSlot {
+    uint8_t* dev = nullptr;                  // claim counters, then best
+    unsigned long long* host_best = nullptr;  // pinned
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    unsigned long long* claims() const { return (unsigned long long*)dev; }
+    unsigned long long* best() const { return (unsigned long long*)(dev + kClaimBytes); }
+};
+
 struct Device {
     int ordinal = 0;
     hipDeviceProp_t prop{};
@@ -139,6 +152,11 @@ struct Device {
     Buffer acquire(size_t bytes) { return acquire(bytes, bytes); }
     Buffer acquire(size_t dev_bytes, size_t host_bytes);
     void release(Buffer b);
+    // Control slots (at most one per concurrent check is ever made).  Only a slot whose finish kernel
+    // has run goes back; a slot of a failed call is dropped.
+    std::vector<ControlSlot> free_slots;
+    ControlSlot acquire_slot();
+    void release_slot(const ControlSlot& s);
     // Device address of the no-allocation entry point's static scratch array on this device
     // (looked up once, at set-up, with this device current).
     void* noalloc_scratch = nullptr;
@@ -211,6 +229,27 @@ struct DevMem {
 };
 // Checks that caller memory of `m.bytes` can hold `need` bytes (alignment and size).
 void check_dev_mem(const DevMem& m, size_t need);
+
+// Runs one check's kernel (`launch`, enqueued between the events) on a control slot and returns the
+// lowest failing pattern: no copies, one wait.
+uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
+                     const std::function<void(const ControlSlot&)>& launch);
+
+// One launch of a batch: cones on the interpreter with one schedule, or native kernels.
+struct BatchPart {
+    std::vector<size_t> entries;  // the batch's entries, in the order of the vectors below
+    std::vector<HwRange> ranges;
+    std::vector<Circuit*> cs;
+    Schedule sch;
+    std::vector<std::shared_ptr<JitKernel>> native;  // instead of cs and sch
+};
+// All launches of a batch on one stream, one wait: best[e] for each of its n entries.  Prepared
+// batches (descriptors on the device, control block clean) are kept for calls with the same
+// circuits and kernels.
+using BatchRunner = void (*)(Device& dev, const std::vector<BatchPart>& parts, size_t n, hipStream_t stream,
+                             std::vector<uint64_t>& best, double* ms);
+void register_batch_runner(BatchRunner r);
+BatchRunner batch_runner();  // null in host-only builds
 
 // One interpreter launch over several cones (k = 1 for a plain check).
 void run_interp(Device& dev, const std::vector<Circuit*>& cs, const std::vector<HwRange>& ranges,
@@ -302,6 +341,26 @@ std::string jit_source(const LutProgram& lp, int waves_per_eu, int block, int* w
 // jit_prepare and jit_enqueue of a native kernel.
 JitLaunchPlan native_prepare(Device& dev, JitKernel& k, const HwRange& r, uint64_t tile_hw);
 void native_enqueue(const JitLaunchPlan& lp, uint64_t* next_item, uint64_t* best, hipStream_t stream);
+// Native launches over many kernels: one per register tier.  native_many_fill writes the
+// descriptors of the kernels (host copy; their device addresses will be dev_descs, and
+// best_index[i] is kernel i's entry of best[]) and prepares the launches on the claim counters
+// claims[0..3); `code` keeps their common code object alive.
+struct NativeManyLaunch {
+    NativeLaunch L{};
+    hipFunction_t fn = nullptr;
+    uint64_t grid = 0;
+    uint32_t lds = 0;
+};
+constexpr int kNativeTiers = 3;
+struct NativeMany {
+    std::shared_ptr<CodeObject> code;
+    NativeManyLaunch tier[kNativeTiers];
+};
+NativeMany native_many_fill(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks,
+                            const std::vector<HwRange>& ranges, const std::vector<uint32_t>& best_index,
+                            NativeDesc* host_descs, const NativeDesc* dev_descs, uint8_t* claims,
+                            unsigned long long* best);
+void native_many_enqueue(const NativeMany& m, hipStream_t stream);
 // Machine code that the library encodes itself (native.hpp): a circuit's kernel costs milliseconds
 // of planning and a module load, not a compile.  The library links the tier; host-only builds of
 // its sources do without it (native_tier() is then null) and use the interpreter and hipRTC kernels.
@@ -311,15 +370,13 @@ struct NativeTier {
     // `weight`: what a millisecond of building costs against one of kernel time.
     std::shared_ptr<JitKernel> (*ready)(Circuit& c, uint64_t span);
     std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight);
-    // Expected kernel time over `patterns` patterns, and of get() for a circuit without one.
+    // Expected kernel time over `patterns` patterns, and of get() for a circuit without one (the
+    // module load on the first launch not included).
     double (*run_ms)(const JitKernel& k, double patterns);
     double (*share_ms)(const JitKernel& k, double patterns);  // of a launch that many cones fill
     double (*guess_run_ms)(const Circuit& c, double patterns);
     double (*guess_build_ms)(const Circuit& c);
     void (*counts)(const JitKernel& k, uint32_t* inner, uint32_t* valu, uint32_t* waves);
-    // One launch per register tier over several kernels' ranges.
-    void (*run_many)(Device& dev, const std::vector<std::shared_ptr<JitKernel>>& ks,
-                     const std::vector<HwRange>& ranges, hipStream_t stream, std::vector<uint64_t>& best, double* ms);
 };
 const NativeTier* native_tier();  // null: not linked, or off (FASTLEC_ES_NATIVE=0)
 void register_native_tier(const NativeTier* t);
@@ -327,7 +384,7 @@ void register_native_tier(const NativeTier* t);
 // plus what the interpreter has already taken for this circuit exceeds the native kernel's time
 // and its building.  A circuit checked again and again thus spends at most about twice the better
 // of the two; one checked once is built only when that check alone pays.
-bool native_pays(Circuit& c, double interp_ms, double patterns, double build_share);
+bool native_pays(Circuit& c, double interp_ms, double patterns);
 
 // The per-pass body as one asm statement with planner-assigned registers (v0.., s<sgpr_base>..).
 // Returns false, with the register counts in stats, when it needs more than the limits.

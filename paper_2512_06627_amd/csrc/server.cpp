@@ -51,6 +51,7 @@ struct Job {
     fastlec_es_result res{};
     bool compile_queued = false;     // handed to the compile threads
     bool compiling = false;          // a compile thread is using the circuit
+    bool no_kernel = false;          // the compile threads found none that fits
     std::shared_ptr<JitKernel> jit;  // set when the specialized kernel is ready
 };
 
@@ -123,6 +124,11 @@ struct fastlec_es_server {
     std::condition_variable cv_compile;
     std::vector<std::thread> compilers;
     void compile_loop();
+    // A job whose native kernel is being built runs on the interpreter meanwhile only if its stream is
+    // already planned: planning takes about as long as building.  Call with mu held.
+    bool awaits_kernel(Job* j) const {
+        return jit_mode == 1 && native_tier() && j->compile_queued && !j->jit && !j->no_kernel && !j->c->planned(4);
+    }
     void plan_tiers(const std::vector<Job*>& act);
 
     uint64_t charge_of(const Circuit& c) const {
@@ -207,8 +213,10 @@ void fastlec_es_server::compile_loop() {
             Job* j = group[t];
             j->compiling = false;
             if (ks[t] && ks[t]->code && !j->done) j->jit = ks[t];
+            else j->no_kernel = true;
         }
         cv_done.notify_all();
+        cv_work.notify_all();  // a step may be waiting for these kernels
     }
 }
 
@@ -235,8 +243,9 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
         // A native kernel takes milliseconds to build, on a compile thread, while the job keeps
         // running on the interpreter.
         if (nt && jit_mode == 1) {
-            const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows(), left);
-            if (native_pays(*j->c, share * (double)std::max<size_t>(1, sharing), left, 1.0)) {
+            const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
+            const double plan = j->c->planned(4) ? 0.0 : 0.5e-3 * j->c->plan1.num_ands_tfi;
+            if (native_pays(*j->c, plan + share * (double)std::max<size_t>(1, sharing), left)) {
                 j->compile_queued = true;
                 compile_queue.push_back(j);
                 cv_compile.notify_one();
@@ -309,7 +318,11 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
             jit_jobs.push_back(t);
             continue;
         }
-        const Plan& p = j->c->plan_for(kB);
+        // The register tier's stream is planned in bundles of 4, the other tiers' in bundles of kB.
+        int regs_waves = 0;
+        const bool regs = regs_tier_enabled() && !opts.wg_size && !opts.words_per_thread &&
+                          interp_regs_rows(j->c->interp_rows(), &regs_waves) != 0;
+        const Plan& p = j->c->plan_for(regs ? 4 : kB);
         const double per_hw = 32.0 * std::max<size_t>(1, p.prog.size());
         uint64_t slice = (uint64_t)std::max(16.0 * pass_hw, std::floor(per_job / per_hw));
         slice = (slice + pass_hw - 1) / pass_hw * pass_hw;
@@ -318,9 +331,8 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
         step_np += per_hw * (double)(w.end - w.begin);
         // The first group runs in the register tier (or LDS when the caller fixes the schedule);
         // files too large for registers go to device memory, where more waves per CU fit.
-        int regs_waves = 0;
         const bool fits = regs_tier_enabled() && !opts.wg_size && !opts.words_per_thread
-                              ? interp_regs_rows(j->c->interp_rows(), &regs_waves) != 0
+                              ? regs
                               : interp_lds_bytes(p.rows, kK, 1) <= lds_blk;
         (fits ? lds_c : hbm_c).push_back(j->c);
         (fits ? lds_r : hbm_r).push_back(w);
@@ -489,7 +501,7 @@ void fastlec_es_server::loop() {
                         j->t_admit = now;
                         // The model's ETA: the job's interpreter time alone, times the jobs that
                         // share the device with it at admission (itself included).
-                        j->res.predicted_ms = model_interp_ms(j->c->interp_gates(), j->c->interp_rows(),
+                        j->res.predicted_ms = model_interp_ms(j->c->interp_gates(), j->c->interp_rows_guess(),
                                                               32.0 * (double)(j->range.end - j->range.begin)) *
                                               (double)(active.size() + 1);
                         st.charge_in_use_bytes += j->charge;
@@ -522,6 +534,22 @@ void fastlec_es_server::loop() {
                 FES_HIP(hipMemcpyAsync((uint8_t*)table.dev + off_best + 8ull * s, &hb[s], 8, hipMemcpyHostToDevice, stream));
             }
             plan_tiers(act);
+            {
+                std::unique_lock<std::mutex> g(mu);
+                std::vector<Job*> now;
+                for (Job* j : act)
+                    if (!awaits_kernel(j)) now.push_back(j);
+                if (now.empty()) {
+                    cv_work.wait(g, [&] {
+                        if (stop || !queue.empty()) return true;
+                        for (Job* j : act)
+                            if (!awaits_kernel(j)) return true;
+                        return false;
+                    });
+                    continue;
+                }
+                act.swap(now);
+            }
             step(act);
         }
     } catch (const Error& e) {
