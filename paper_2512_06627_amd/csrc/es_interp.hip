@@ -551,54 +551,107 @@ hipError_t launch_regs(const InterpLaunch& L, int grid, hipStream_t stream) {
 //
 // The logic simulation that opens a sweeping flow (Section 2.3, step 1) with the value file in
 // VGPRs: every variable's word is stored to its signature row, so the kernel is bound by HBM
-// writes rather than by instruction issue.  One pass covers 64 caller words (one per lane).
-// The stream (encode_sim_regs_stream) has the register tier's 28-word bundles with the XOR
-// masks and output flags replaced by the absolute address of each gate's signature row (two
-// words per gate; gates that define no variable point at a dummy row); it is built per call,
-// since the addresses depend on the signature buffer and its row length.  A pass: row 0 (zero)
-// and the n input rows are written to the file and stored, then per bundle the eight operand
-// reads with their complements, four ANDs, four indexed writes and four row stores.  Lanes past
-// the last word are masked off for the whole pass (EXEC), so they neither compute nor store.
-// The stores are non-temporal: the signature matrix is far larger than the caches and is read
-// back by a later kernel (16x16 miter at 2^18 words: 1.87 ms with ordinary stores, 1.45 ms).
-#define FES_RS_BUNDLE(a0, a1, a2, a3, b0, b1, b2, b3, d0, d1, d2, d3, ca0, ca1, ca2, ca3, cb0, cb1, cb2, cb3, P0, P1, \
-                      P2, P3)                                                                                        \
-    FES_RG_READS(a0, b0, a1, b1, a2, b2, a3, b3, ca0, cb0, ca1, cb1, ca2, cb2, ca3, cb3)                               \
-    "s_set_gpr_idx_off\n"                                                                                              \
-    "v_and_b32 v16, v16, v17\n"                                                                                        \
-    "v_and_b32 v18, v18, v19\n"                                                                                        \
-    "v_and_b32 v20, v20, v21\n"                                                                                        \
-    "v_and_b32 v22, v22, v23\n"                                                                                        \
-    FES_RG_WRITES(d0, d1, d2, d3)                                                                                      \
-    "global_store_dword %[off], v16, " P0 " nt\n"                                                                         \
-    "global_store_dword %[off], v18, " P1 " nt\n"                                                                         \
-    "global_store_dword %[off], v20, " P2 " nt\n"                                                                         \
-    "global_store_dword %[off], v22, " P3 " nt\n"
-#define FES_RS_BUF_A                                                                                           \
-    FES_RS_BUNDLE("s36", "s37", "s38", "s39", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", \
-                  "s50", "s51", "s52", "s53", "s54", "s55", "s[56:57]", "s[58:59]", "s[60:61]", "s[62:63]")
-#define FES_RS_BUF_B                                                                                           \
-    FES_RS_BUNDLE("s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77", \
-                  "s78", "s79", "s80", "s81", "s82", "s83", "s[84:85]", "s[86:87]", "s[88:89]", "s[90:91]")
+// writes.  One pass covers 64 caller words (one per lane).
+//
+// The stream (encode_sim_stream) is two words a gate: operand and destination rows with the
+// complement flags, and the variable; it does not depend on the call, so a circuit's is uploaded
+// once.  Lane g of a vector load holds gate g of a block of 64, the next block's records arrive while
+// a block runs, and what is alike for every gate is done for the 64 at once: the destination and the
+// address of the signature row.  v_readlane brings a gate's four words to the scalar unit.  (With
+// scalar loads one bundle of four gates ahead, a wave waited out a scalar-cache miss every four
+// gates: 16x16 miter, 2^18 words, 1.47 ms and 4.0 TB/s, where the same stores without any gates
+// take 1.0 ms; 19 instructions a gate with the address made on the scalar unit, 1.20 ms.)  A gate is 14
+// instructions: four v_readlane, the complement masks and the second operand's index, three changes of
+// the index mode, three vector ones (a's complement, the AND that takes b's, the write to the file)
+// and the store.  Groups of four gates do their scalar part first: v_readlane and a VMEM access
+// stay out of the index mode, and an address is more than five instructions old when a store reads it.
+//
+// Rows of a ragged word count start anywhere in a cache line, so that most 256-byte stores of a
+// wave leave a part of a line at both ends for a neighbour to complete.  The waves of a workgroup hold
+// adjacent columns and meet at a barrier every eight gates, adjacent workgroups sit on one XCD, and
+// the stores are plain, so the parts meet in its L2 (ones that bypass it are written to memory part
+// by part).  16x16 miter, 262,101 words: 3.10 ms with separate waves and non-temporal stores, 2.22 with
+// plain ones, 1.45 (4.0 TB/s) in this form; 262,144 words: 1.12, 1.10 and 1.06 ms (5.5 TB/s); 1,003
+// words (a pass a CU, bound by the chain of instructions): 36 ns a gate, 87 ns with scalar loads.
+//
+// Lanes past the last word are masked off for loads and stores of the caller's words; the records
+// need every lane.
+#define FES_RS_FETCH(W, D, LO, HI, CA, CB, B, G)   \
+    "v_readlane_b32 " LO ", v20, " G "\n"           \
+    "v_readlane_b32 " HI ", v21, " G "\n"           \
+    "v_readlane_b32 " W ", v18, " G "\n"            \
+    "v_readlane_b32 " D ", v19, " G "\n"            \
+    "s_bfe_i32 " CA ", " W ", 0x10018\n"            \
+    "s_bfe_i32 " CB ", " W ", 0x10019\n"            \
+    "s_lshr_b32 " B ", " W ", 8\n"
+#define FES_RS_GATE(W, D, CA, CB, B, V)            \
+    "s_set_gpr_idx_on " W ", gpr_idx(SRC0)\n"       \
+    "v_xor_b32_e64 v16, v24, " CA "\n"              \
+    "s_set_gpr_idx_idx " B "\n"                     \
+    "v_bitop3_b32 " V ", v24, v16, " CB " bitop3:0x48\n" \
+    "s_set_gpr_idx_on " D ", gpr_idx(DST)\n"        \
+    "v_mov_b32 v24, " V "\n"
+#define FES_RS_STORE(V, A) "global_store_dword %[off], " V ", " A "\n"
+// 64 gates of a record block; every eight, out when none are left.
+#define FES_RS_BLOCK                                                    \
+    ".irp h,0,8,16,24,32,40,48,56\n"                                    \
+    ".irp j,0,4\n"                                                      \
+    FES_RS_FETCH("s36", "s40", "s44", "s45", "s52", "s56", "s60", "\\h+\\j")   \
+    FES_RS_FETCH("s37", "s41", "s46", "s47", "s53", "s57", "s61", "\\h+\\j+1") \
+    FES_RS_FETCH("s38", "s42", "s48", "s49", "s54", "s58", "s62", "\\h+\\j+2") \
+    FES_RS_FETCH("s39", "s43", "s50", "s51", "s55", "s59", "s63", "\\h+\\j+3") \
+    FES_RS_GATE("s36", "s40", "s52", "s56", "s60", "%[r0]")              \
+    FES_RS_GATE("s37", "s41", "s53", "s57", "s61", "%[r1]")              \
+    FES_RS_GATE("s38", "s42", "s54", "s58", "s62", "%[r2]")              \
+    FES_RS_GATE("s39", "s43", "s55", "s59", "s63", "%[r3]")              \
+    "s_set_gpr_idx_off\n"                                               \
+    FES_RS_STORE("%[r0]", "s[44:45]")                                   \
+    FES_RS_STORE("%[r1]", "s[46:47]")                                   \
+    FES_RS_STORE("%[r2]", "s[48:49]")                                   \
+    FES_RS_STORE("%[r3]", "s[50:51]")                                   \
+    ".endr\n"                                                           \
+    "s_barrier\n"                                                       \
+    "s_sub_u32 s96, s96, 1\n"                                           \
+    "s_cbranch_scc1 fes_rs_end_%=\n"                                    \
+    ".endr\n"
+// With every lane: the block whose records are there is taken over, the next one's load starts.
+#define FES_RS_LOAD                                    \
+    "global_load_dwordx2 v[22:23], %[lo8], s[94:95]\n" \
+    "s_add_u32 s94, s94, 512\n"                       \
+    "s_addc_u32 s95, s95, 0\n"
+#define FES_RS_TAKE                                    \
+    "s_mov_b64 exec, -1\n"                            \
+    "v_mul_lo_u32 v20, v23, %[wb]\n"                  \
+    "v_mul_hi_u32 v21, v23, %[wb]\n"                  \
+    "v_mov_b32 v17, %[sig_hi]\n"                      \
+    "v_add_co_u32_e32 v20, vcc, %[sig_lo], v20\n"     \
+    "v_mov_b32 v18, v22\n"                            \
+    "v_bfe_u32 v19, v22, 16, 8\n"                     \
+    "s_nop 1\n"                                       \
+    "v_addc_co_u32_e32 v21, vcc, v17, v21, vcc\n"     \
+    FES_RS_LOAD                                        \
+    "s_mov_b64 exec, %[mask]\n"                       \
+    "s_nop 1\n"
 
-// Registers: s[92:93] address of the next input's signature row; s[94:95] stream pointer; s96
-// bundles left after the current one; s[98:99] address of the next input's caller row.  The
-// input loads share one wait (vmcnt also counts the stores still in flight); the last stream
-// prefetch is waited for before the statement ends.
+// Registers: s[92:93] address of the next input's signature row; s[94:95] next record block; s96
+// groups of eight gates left after the current one; s[98:99] address of the next input's caller
+// row; v18..v21 a block's records, destinations and row addresses, v[22:23] the next block.  The
+// input loads share one wait.  vmcnt counts loads and stores in order: at the wait for a block its
+// load is followed by the 64 stores of the block before, so at most 63 outstanding means it is there.
 // Input i (n <= 63) is loaded straight into its file row v(25 + i) and stored to its signature
 // row: all loads of a pass are issued before one wait.
 #define FES_RS_LD(I, V)                              \
     "s_cmp_eq_u32 %[n], " #I "\n"                    \
     "s_cbranch_scc1 fes_rs_ld_done_%=\n"              \
     "global_load_dword " V ", %[off], s[98:99]\n"     \
-    "s_add_u32 s98, s98, %[wb_lo]\n"                 \
-    "s_addc_u32 s99, s99, %[wb_hi]\n"
+    "s_add_u32 s98, s98, %[wb]\n"                 \
+    "s_addc_u32 s99, s99, 0\n"
 #define FES_RS_ST(I, V)                              \
     "s_cmp_eq_u32 %[n], " #I "\n"                    \
     "s_cbranch_scc1 fes_rs_st_done_%=\n"              \
-    "global_store_dword %[off], " V ", s[92:93] nt\n" \
-    "s_add_u32 s92, s92, %[wb_lo]\n"                 \
-    "s_addc_u32 s93, s93, %[wb_hi]\n"
+    "global_store_dword %[off], " V ", s[92:93]\n" \
+    "s_add_u32 s92, s92, %[wb]\n"                 \
+    "s_addc_u32 s93, s93, 0\n"
 #define FES_RS_LOADS \
     FES_RS_LD(0, "v25") FES_RS_LD(1, "v26") FES_RS_LD(2, "v27") FES_RS_LD(3, "v28") \
     FES_RS_LD(4, "v29") FES_RS_LD(5, "v30") FES_RS_LD(6, "v31") FES_RS_LD(7, "v32") \
@@ -637,86 +690,79 @@ hipError_t launch_regs(const InterpLaunch& L, int grid, hipStream_t stream) {
     ""
 
 #define FES_RS_PASS_ASM                                                                                   \
-    "v_mov_b32 v24, 0\n"                                                                                  \
-    "global_store_dword %[off], v24, %[sig] nt\n"                                                         \
-    "s_mov_b64 s[98:99], %[pi]\n"                                                                         \
+    "s_mov_b64 exec, %[mask]\n"                                                                          \
+    "v_mov_b32 v24, 0\n"                                                                                 \
+    "s_mov_b32 s42, %[sig_lo]\n"                                                                         \
+    "s_mov_b32 s43, %[sig_hi]\n"                                                                         \
+    "global_store_dword %[off], v24, s[42:43]\n"                                                         \
+    "s_mov_b64 s[98:99], %[pi]\n"                                                                        \
     FES_RS_LOADS                                                                                          \
-    "fes_rs_ld_done_%=:\n"                                                                                \
+    "fes_rs_ld_done_%=:\n"                                                                               \
+    "s_mov_b64 s[94:95], %[prog]\n"                                                                      \
+    "s_mov_b64 exec, -1\n"                                                                                \
+    FES_RS_LOAD                                                                                           \
+    "s_mov_b64 exec, %[mask]\n"                                                                           \
     "s_waitcnt vmcnt(0)\n"                                                                                \
-    "s_add_u32 s92, %[sig_lo], %[wb_lo]\n"                                                                \
-    "s_addc_u32 s93, %[sig_hi], %[wb_hi]\n"                                                               \
+    "s_add_u32 s92, %[sig_lo], %[wb]\n"                                                                   \
+    "s_addc_u32 s93, %[sig_hi], 0\n"                                                                      \
     FES_RS_STORES                                                                                         \
     "fes_rs_st_done_%=:\n"                                                                                \
-    "s_mov_b64 s[94:95], %[prog]\n"                                                                       \
-    "s_sub_u32 s96, %[nb], 1\n"                                                                           \
-    FES_RG_LOAD_A("0x0", "0x40", "0x60")                                                                  \
+    "s_sub_u32 s96, %[ng], 1\n"                                                                           \
     "fes_rs_loop_%=:\n"                                                                                   \
-    "s_waitcnt lgkmcnt(0)\n"                                                                              \
-    FES_RG_LOAD_B("0x70", "0xb0", "0xd0")                                                                 \
-    FES_RS_BUF_A                                                                                          \
-    "s_sub_u32 s96, s96, 1\n"                                                                             \
-    "s_cbranch_scc1 fes_rs_end_%=\n"                                                                      \
-    "s_waitcnt lgkmcnt(0)\n"                                                                              \
-    FES_RG_LOAD_A("0xe0", "0x120", "0x140")                                                               \
-    FES_RS_BUF_B                                                                                          \
-    "s_add_u32 s94, s94, 224\n"                                                                           \
-    "s_addc_u32 s95, s95, 0\n"                                                                            \
-    "s_sub_u32 s96, s96, 1\n"                                                                             \
-    "s_cbranch_scc0 fes_rs_loop_%=\n"                                                                     \
+    FES_RS_TAKE                                                                                           \
+    FES_RS_BLOCK                                                                                          \
+    "s_waitcnt vmcnt(63)\n"                                                                               \
+    "s_branch fes_rs_loop_%=\n"                                                                           \
     "fes_rs_end_%=:\n"                                                                                    \
-    "s_waitcnt lgkmcnt(0)\n"
+    "s_waitcnt vmcnt(0)\n"                                                                                \
+    "s_mov_b64 exec, -1\n"
 
 template <int R>
-__device__ __forceinline__ void sim_regs_pass(const uint32_t* prog, uint32_t nb, uint32_t n, const uint32_t* pi,
-                                              uint32_t* sig, uint32_t sig_lo, uint32_t sig_hi, uint32_t wb_lo,
-                                              uint32_t wb_hi, uint32_t off) {
+__device__ __forceinline__ void sim_regs_pass(const uint32_t* prog, uint32_t ng, uint32_t n, const uint32_t* pi,
+                                              uint32_t sig_lo, uint32_t sig_hi, uint32_t wb, uint64_t mask,
+                                              uint32_t off, uint32_t lo8) {
+    uint32_t r0, r1, r2, r3;
 #define FES_RS_OPERANDS                                                                                   \
-    :                                                                                                     \
-    : [prog] "s"(prog), [nb] "s"(nb), [n] "s"(n), [pi] "s"(pi), [sig] "s"(sig), [sig_lo] "s"(sig_lo),      \
-      [sig_hi] "s"(sig_hi), [wb_lo] "s"(wb_lo), [wb_hi] "s"(wb_hi), [off] "v"(off)
+    : [r0] "=&v"(r0), [r1] "=&v"(r1), [r2] "=&v"(r2), [r3] "=&v"(r3)                                      \
+    : [prog] "s"(prog), [ng] "s"(ng), [n] "s"(n), [pi] "s"(pi), [sig_lo] "s"(sig_lo), [sig_hi] "s"(sig_hi), \
+      [wb] "s"(wb), [mask] "s"(mask), [off] "v"(off), [lo8] "v"(lo8)
     if constexpr (R == 104) {
-        asm volatile(FES_RS_PASS_ASM FES_RS_OPERANDS : "memory", FES_RG_SCLOB, FES_RG_VCLOB_104);
+        asm volatile(FES_RS_PASS_ASM FES_RS_OPERANDS : "memory", "vcc", FES_RG_SCLOB, FES_RG_VCLOB_104);
     } else if constexpr (R == 144) {
-        asm volatile(FES_RS_PASS_ASM FES_RS_OPERANDS : "memory", FES_RG_SCLOB, FES_RG_VCLOB_144);
+        asm volatile(FES_RS_PASS_ASM FES_RS_OPERANDS : "memory", "vcc", FES_RG_SCLOB, FES_RG_VCLOB_144);
     } else {
-        asm volatile(FES_RS_PASS_ASM FES_RS_OPERANDS : "memory", FES_RG_SCLOB, FES_RG_VCLOB_232);
+        asm volatile(FES_RS_PASS_ASM FES_RS_OPERANDS : "memory", "vcc", FES_RG_SCLOB, FES_RG_VCLOB_232);
     }
 #undef FES_RS_OPERANDS
 }
 
+constexpr uint32_t kXcds = 8;  // workgroup b runs on XCD b % 8
+
 template <int R, int kWaves>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves, kWaves)))
+__global__ void __launch_bounds__(256 * kWaves) __attribute__((amdgpu_waves_per_eu(kWaves, kWaves)))
 es_sim_regs_kernel(InterpLaunch L) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t waves = gridDim.x;
-    const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
-    const uint32_t claim = __builtin_amdgcn_readfirstlane(blockIdx.x % nclaim);
-    unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
     const FES_CONST ConeDesc* c = cones_of(L);
     const uint32_t n = __builtin_amdgcn_readfirstlane(c->n_inputs);
-    const uint32_t nb = __builtin_amdgcn_readfirstlane(c->n_instr / 4u);
+    const uint32_t ng = __builtin_amdgcn_readfirstlane((c->n_instr + 7u) / 8u);
     const uint32_t* prog = (const uint32_t*)c->prog;
-    const uint64_t W = L.sim_words, tile = c->tile_hw;
-    const uint64_t wb = W * 4u;
+    const uint64_t W = L.sim_words;
     const uint64_t sig = (uint64_t)L.sim_sig;
-    const bool one_each = L.total_items <= waves;
-    for (bool more = true; more;) {
-        const uint64_t item = one_each ? blockIdx.x : claim + next_claim(counter) * nclaim;
-        more = !one_each;
-        if (item >= L.total_items) break;
-        const uint64_t hw0 = item * tile, hw_stop = min(hw0 + tile, W);
-        for (uint64_t base = hw0; base < hw_stop; base += 64u) {
-            const uint64_t w = base + lane;
-            if (w < W)
-                sim_regs_pass<R>(prog, nb, n, L.sim_pi, L.sim_sig, (uint32_t)sig, (uint32_t)(sig >> 32), (uint32_t)wb,
-                                 (uint32_t)(wb >> 32), (uint32_t)(w * 4u));
-        }
+    const uint32_t xcds = min(gridDim.x, kXcds), xcd = blockIdx.x % xcds;
+    const uint64_t share = L.total_items / xcds, odd = L.total_items % xcds;
+    const uint64_t first = xcd * share + min((uint64_t)xcd, odd), stop = first + share + (xcd < odd ? 1u : 0u);
+    const uint32_t step = (gridDim.x - xcd + xcds - 1u) / xcds;
+    for (uint64_t item = first + blockIdx.x / xcds; item < stop; item += step) {
+        const uint64_t w = item * blockDim.x + threadIdx.x;
+        sim_regs_pass<R>(prog, ng, n, L.sim_pi, (uint32_t)sig, (uint32_t)(sig >> 32), (uint32_t)(W * 4u),
+                         __ballot(w < W), (uint32_t)(w * 4u), (threadIdx.x & 63u) * 8u);
     }
 }
 
 template <int R, int kWaves>
 hipError_t launch_sim_regs_t(const InterpLaunch& L, int grid, hipStream_t stream) {
-    hipLaunchKernelGGL((es_sim_regs_kernel<R, kWaves>), dim3(grid), dim3(64), 0, stream, L);
+    const uint64_t block = L.one.tile_hw;
+    if (block == 0 || block % 64 || block > 256 * kWaves) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((es_sim_regs_kernel<R, kWaves>), dim3(grid), dim3((uint32_t)block), 0, stream, L);
     return hipGetLastError();
 }
 
@@ -765,7 +811,7 @@ hipError_t launch_interp_regs(const InterpLaunch& L, int regs, int grid, hipStre
 
 hipError_t launch_sim_regs(const InterpLaunch& L, int regs, int grid, hipStream_t stream) {
     if (L.num_cones != 1 || !L.sim_sig || grid <= 0 || L.rows_max > (uint32_t)regs) return hipErrorInvalidValue;
-    if (L.sim_words == 0 || L.sim_words > (1ull << 30)) return hipErrorInvalidValue;  // 32-bit byte offsets
+    if (L.sim_words == 0 || L.sim_words >= (1ull << 30)) return hipErrorInvalidValue;  // 32-bit byte offsets
     switch (regs) {
         case 104: return launch_sim_regs_t<104, 4>(L, grid, stream);
         case 144: return launch_sim_regs_t<144, 3>(L, grid, stream);

@@ -66,7 +66,7 @@ hipError_t launch_interp_sim(const InterpLaunch& L, int K, int B, bool lds, int 
 // complement-normalised hash sum_k word'_k * (fmix32(k) | 1) mod 2^64, where word' is the
 // row complemented when its first bit is 1.  One wave per row, grid-stride over rows.
 hipError_t launch_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
-                                 uint64_t* ones, int grid, hipStream_t stream);
+                                 uint64_t* ones, int cus, hipStream_t stream);
 
 // Register tier's stream: per bundle of 4 gates, 28 words in this order
 //   a[4]   operand rows with the complement flag in bit 31 (the kernel indexes registers by the
@@ -81,13 +81,15 @@ constexpr uint32_t kRegsBundleWords = 28;
 // prefetches one bundle past the one it runs, so the last prefetch stays inside the stream).
 void encode_regs_stream(const Plan& p, std::vector<uint32_t>& out);
 
-// The simulation-mode variant of that layout for one call: words 20..27 hold, per gate, the
-// 64-bit address of the signature row of the variable it defines (sig + variable * words), or
-// `dummy` (a row of `words` words) for instructions that define none; one zero bundle follows.
-void encode_sim_regs_stream(const Plan& p, const uint32_t* sig, uint64_t words, const uint32_t* dummy,
-                            std::vector<uint32_t>& out);
-// Simulation mode in the register tier: one cone, the stream above as the descriptor's prog,
-// columns [0, sim_words) (at most 2^30) simulated once each; `regs` as for launch_interp_regs.
+// Simulation mode in the register tier: two words a gate, in order, of a plan of single instructions
+// (bundle 1): a | b << 8 | d << 16 (rows) | complement of a << 24 | of b << 25, and the variable the gate
+// defines.  Instructions that define none are left out; the last group of eight is filled up with
+// gates that store the last one's value again, and zeros follow up to the end of the block of 64
+// after the last (the kernel reads one block ahead).  *gates = records that hold gates.
+void encode_sim_stream(const Plan& p, std::vector<uint32_t>& out, uint32_t* gates);
+// The launch: one cone with that stream as its prog, n_instr = gates and tile_hw = words per workgroup
+// (64 per wave), total_items = workgroups' worth of words in the columns [0, sim_words) (less than
+// 2^30), simulated once each; `regs` as for launch_interp_regs.
 hipError_t launch_sim_regs(const InterpLaunch& L, int regs, int grid, hipStream_t stream);
 
 // Register tier: value files in VGPRs (one wave per workgroup, bundles of 4, one 32-bit word per

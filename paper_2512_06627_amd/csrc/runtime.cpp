@@ -88,6 +88,14 @@ Circuit::~Circuit() {
             (void)hipSetDevice(cur);
         }
     }
+    for (auto& kv : dev_sim_stream) {
+        if (!kv.second) continue;
+        int cur = 0;
+        if (hipGetDevice(&cur) == hipSuccess && hipSetDevice(kv.first) == hipSuccess) {
+            (void)hipFree(kv.second);
+            (void)hipSetDevice(cur);
+        }
+    }
     for (auto& kv : dev_regs) {
         if (!kv.second) continue;
         int cur = 0;
@@ -172,28 +180,24 @@ void encode_regs_stream(const Plan& p, std::vector<uint32_t>& out) {
     }
 }
 
-void encode_sim_regs_stream(const Plan& p, const uint32_t* sig, uint64_t words, const uint32_t* dummy,
-                            std::vector<uint32_t>& out) {
-    if (p.bundle != 4 || p.prog.size() % 4) throw Error{kErrInvalid, "register-tier stream needs bundles of 4"};
-    out.assign((p.prog.size() / 4 + 1) * kRegsBundleWords, 0u);
-    for (size_t b = 0; b < p.prog.size() / 4; ++b) {
-        uint32_t* w = out.data() + b * kRegsBundleWords;
-        for (int u = 0; u < 4; ++u) {
-            const size_t t = b * 4 + u;
-            const Instr& ins = p.prog[t];
-            w[u] = ins.a;
-            w[4 + u] = ins.b;
-            w[8 + u] = ins.d;
-            w[12 + u] = (ins.a & kCompl) ? ~0u : 0u;
-            w[16 + u] = (ins.b & kCompl) ? ~0u : 0u;
-            // variable defined by the instruction (gates only): its signature row, else the dummy row
-            const uint64_t addr = p.instr_gate[t] == UINT32_MAX
-                                      ? (uint64_t)dummy
-                                      : (uint64_t)(sig + (uint64_t)(p.num_inputs + 1 + p.instr_gate[t]) * words);
-            w[20 + 2 * u] = (uint32_t)addr;
-            w[21 + 2 * u] = (uint32_t)(addr >> 32);
-        }
+void encode_sim_stream(const Plan& p, std::vector<uint32_t>& out, uint32_t* gates) {
+    if (p.bundle != 1 || p.rows > 256) throw Error{kErrInvalid, "simulation stream needs single instructions and byte rows"};
+    out.clear();
+    for (size_t t = 0; t < p.prog.size(); ++t) {
+        if (p.instr_gate[t] == UINT32_MAX) continue;
+        const Instr& ins = p.prog[t];
+        out.push_back((ins.a & kRowMask) | (ins.b & kRowMask) << 8 | ins.d << 16 | (ins.a & kCompl ? 1u << 24 : 0u) |
+                      (ins.b & kCompl ? 1u << 25 : 0u));
+        out.push_back(p.num_inputs + 1 + p.instr_gate[t]);
     }
+    *gates = (uint32_t)(out.size() / 2);
+    if (!*gates) return;
+    const uint32_t d = (out[out.size() - 2] >> 16) & 255u, var = out.back();
+    while ((out.size() / 2) % 8) {
+        out.push_back(d | d << 8 | d << 16);
+        out.push_back(var);
+    }
+    out.resize((out.size() + 127) / 128 * 128 + 128, 0u);
 }
 
 const std::vector<uint32_t>& Circuit::regs_stream() {
@@ -220,7 +224,7 @@ const uint32_t* Circuit::device_regs_stream(int dev, hipStream_t s) {
 
 const Plan& Circuit::sim_plan(uint32_t bundle) {
     std::lock_guard<std::mutex> g(mu);
-    std::unique_ptr<Plan>& sim = this->sim[bundle];  // bundle 4 (register tier), 8 or 16
+    std::unique_ptr<Plan>& sim = this->sim[bundle];  // bundle 1 (register tier), 8 or 16
     if (!sim) {
         Aig all = aig;
         std::vector<uint8_t> read(all.max_var() + 1, 0);
@@ -252,6 +256,25 @@ const Instr* Circuit::device_sim_prog(int dev, uint32_t bundle, hipStream_t s) {
     }
     dev_sim_prog[{dev, bundle}] = d;
     return d;
+}
+
+const uint32_t* Circuit::device_sim_stream(int dev, hipStream_t s, uint32_t* gates) {
+    const Plan& p = sim_plan(1);
+    std::lock_guard<std::mutex> g(mu);
+    auto it = dev_sim_stream.find(dev);
+    if (it == dev_sim_stream.end()) {
+        std::vector<uint32_t> h;
+        encode_sim_stream(p, h, &sim_gates);
+        uint32_t* d = nullptr;
+        FES_HIP(hipMalloc(&d, std::max<size_t>(h.size(), 1) * sizeof(uint32_t)));
+        if (!h.empty()) {
+            FES_HIP(hipMemcpyAsync(d, h.data(), h.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+            FES_HIP(hipStreamSynchronize(s));
+        }
+        it = dev_sim_stream.emplace(dev, d).first;
+    }
+    *gates = sim_gates;
+    return it->second;
 }
 
 // ---- devices ----------------------------------------------------------------
@@ -337,6 +360,18 @@ uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
     const uint64_t best = *s.host_best;
     dev.release_slot(s);
     return best;
+}
+
+void run_timed(Device& dev, hipStream_t stream, double* kernel_ms, const std::function<void()>& launch) {
+    const ControlSlot s = dev.acquire_slot();
+    FES_HIP(hipEventRecord(s.e0, stream));
+    launch();
+    FES_HIP(hipEventRecord(s.e1, stream));
+    FES_HIP(hipStreamSynchronize(stream));
+    float ms = 0;
+    FES_HIP(hipEventElapsedTime(&ms, s.e0, s.e1));
+    if (kernel_ms) *kernel_ms = ms;
+    dev.release_slot(s);
 }
 
 Device& device(int ordinal) {
@@ -703,81 +738,36 @@ namespace {
 // simulation plan does not fit that tier, or the call asks for another schedule.
 bool run_sim_regs(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32_t* sig,
                   const fastlec_es_options* o, hipStream_t stream, double* kernel_ms) {
-    if (!regs_tier_enabled() || words > (1ull << 30)) return false;
+    if (!regs_tier_enabled() || words >= (1ull << 30)) return false;
     if (o && (o->kernel == FASTLEC_KERNEL_INTERP_HBM || o->words_per_thread || o->wg_size)) return false;
-    const Plan& p = c.sim_plan(4);
+    const Plan& p = c.sim_plan(1);
     int waves_per_simd = 0;
     const int regs = interp_regs_rows(p.rows, &waves_per_simd);
-    if (!regs || p.prog.empty()) return false;
-    bool any_dummy = false;
-    for (uint32_t g : p.instr_gate) any_dummy = any_dummy || g == UINT32_MAX;
+    if (!regs || p.order.empty()) return false;
 
-    // One work item per pass of 64 words when passes are few, so the last round of claims is as
-    // full as it can be; a grid no larger than the passes need.
-    const uint64_t passes = (words + 63) / 64;
-    const uint64_t cap = (uint64_t)dev.prop.multiProcessorCount * 4 * waves_per_simd;
-    const uint64_t rounds = (passes + cap - 1) / cap;
-    const uint64_t grid = (passes + rounds - 1) / rounds;
-    uint64_t tile_passes = 1;
-    if (o && o->tile_words) tile_passes = std::max<uint64_t>(1, (2ull * o->tile_words + 63) / 64);
-    else
-        while (tile_passes < 16 && passes / (tile_passes * 2) >= grid * 16) tile_passes *= 2;
+    // One workgroup per CU and round, of as many waves (64 words each) as share the words out evenly;
+    // passes are alike, so nothing is claimed and tile_words has nothing to set.
+    const uint64_t passes = (words + 63) / 64, cus = dev.prop.multiProcessorCount;
+    const uint64_t most = cus * 4 * waves_per_simd, rounds = (passes + most - 1) / most;
+    const uint64_t waves = (passes + cus * rounds - 1) / (cus * rounds);
+    const uint64_t items = (passes + waves - 1) / waves;
+    const uint64_t grid = (items + rounds - 1) / rounds;
 
-    const size_t nbytes_stream = (p.prog.size() / 4 + 1) * kRegsBundleWords * sizeof(uint32_t);
-    Layout lay = layout(1, 0);
-    const size_t stream_off = lay.files_off;
-    const size_t dummy_off = (stream_off + nbytes_stream + 255) & ~size_t(255);
-    const size_t total = dummy_off + (any_dummy ? words * 4ull : 0);
-    Buffer buf = dev.acquire(total, dummy_off);
-    struct Releaser {
-        Device& d;
-        Buffer b;
-        ~Releaser() { d.release(b); }
-    } rel{dev, buf};
-    uint8_t* host = (uint8_t*)buf.host;
-    uint8_t* devp = (uint8_t*)buf.dev;
-    std::memset(host, 0, lay.files_off);
-    std::vector<uint32_t> st;
-    encode_sim_regs_stream(p, sig, words, (const uint32_t*)(devp + dummy_off), st);
-    std::memcpy(host + stream_off, st.data(), st.size() * sizeof(uint32_t));
-
-    ConeDesc& d = *(ConeDesc*)(host + lay.desc_off);
-    d.prog = (const Instr*)(devp + stream_off);
-    d.n_instr = (uint32_t)p.prog.size();
-    d.n_inputs = p.num_inputs;
-    d.rows = p.rows;
-    d.hw_begin = 0;
-    d.hw_end = words;
-    d.hw_first = 0;
-    d.tile_hw = 64ull * tile_passes;
-    d.item_begin = 0;
-    d.item_end = (words + d.tile_hw - 1) / d.tile_hw;
-
-    InterpLaunch L;
-    L.cones = (const ConeDesc*)(devp + lay.desc_off);
+    InterpLaunch L{};
     L.num_cones = 1;
     L.rows_max = p.rows;
-    L.total_items = d.item_end;
-    L.ctl = (LaunchCtl*)devp;
-    L.best = (unsigned long long*)(devp + lay.best_off);
-    L.hbm_rows = nullptr;
-    L.cancel = nullptr;
+    L.one.prog = (const Instr*)c.device_sim_stream(dev.ordinal, stream, &L.one.n_instr);
+    L.one.n_inputs = p.num_inputs;
+    L.one.rows = p.rows;
+    L.one.tile_hw = 64 * waves;
+    L.total_items = items;
     L.sim_pi = pi;
     L.sim_sig = sig;
     L.sim_words = words;
-
-    ScopedEvent e0, e1;
-    trace("sim launch (registers): %llu words, %llu items of %llu passes, file %d rows, grid=%llu",
-          (unsigned long long)words, (unsigned long long)L.total_items, (unsigned long long)tile_passes, regs,
-          (unsigned long long)grid);
-    FES_HIP(hipMemcpyAsync(devp, host, dummy_off, hipMemcpyHostToDevice, stream));
-    FES_HIP(hipEventRecord(e0.e, stream));
-    FES_HIP(launch_sim_regs(L, regs, (int)grid, stream));
-    FES_HIP(hipEventRecord(e1.e, stream));
-    FES_HIP(hipStreamSynchronize(stream));
-    float ms = 0;
-    FES_HIP(hipEventElapsedTime(&ms, e0.e, e1.e));
-    if (kernel_ms) *kernel_ms = ms;
+    trace("sim launch (registers): %llu words, file %d rows, grid=%llu of %llu waves, %llu rounds",
+          (unsigned long long)words, regs, (unsigned long long)grid, (unsigned long long)waves,
+          (unsigned long long)rounds);
+    run_timed(dev, stream, kernel_ms, [&] { FES_HIP(launch_sim_regs(L, regs, (int)grid, stream)); });
     return true;
 }
 

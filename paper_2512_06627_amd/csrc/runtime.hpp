@@ -110,6 +110,10 @@ struct Circuit {
     const uint32_t* device_regs_stream(int device, hipStream_t s);
     std::vector<uint32_t> regs_host;
     std::map<int, uint32_t*> dev_regs;
+    // Simulation stream of the register tier (encode_sim_stream) and its gate records.
+    const uint32_t* device_sim_stream(int device, hipStream_t s, uint32_t* gates);
+    std::map<int, uint32_t*> dev_sim_stream;
+    uint32_t sim_gates = 0;
     // LUT steps of the specialized program if it is built, else the model's estimate (never
     // builds it).
     uint32_t lut_steps_known();
@@ -234,6 +238,9 @@ void check_dev_mem(const DevMem& m, size_t need);
 // lowest failing pattern: no copies, one wait.
 uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
                      const std::function<void(const ControlSlot&)>& launch);
+
+// Runs `launch` between a slot's events and waits; for kernels that need no control words.
+void run_timed(Device& dev, hipStream_t stream, double* kernel_ms, const std::function<void()>& launch);
 
 // One launch of a batch: cones on the interpreter with one schedule, or native kernels.
 struct BatchPart {
