@@ -804,17 +804,9 @@ int fastlec_es_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t num_w
         fastlec_es_options o = opts ? *opts : defaults();
         Device& dev = device(o.device);
         hipStream_t stream = o.hip_stream ? (hipStream_t)o.hip_stream : dev.stream;
-        // One wave per row; enough workgroups of four waves for eight per CU, fewer for few rows.
-        const uint64_t want = (rows + 3) / 4;
-        const int grid = (int)std::min<uint64_t>(want, (uint64_t)dev.prop.multiProcessorCount * 8);
-        ScopedEvent e0, e1;
-        FES_HIP(hipEventRecord(e0.e, stream));
-        FES_HIP(launch_signature_hash(sig, rows, num_words, hash, ones, grid, stream));
-        FES_HIP(hipEventRecord(e1.e, stream));
-        FES_HIP(hipStreamSynchronize(stream));
-        float ms = 0;
-        FES_HIP(hipEventElapsedTime(&ms, e0.e, e1.e));
-        if (kernel_ms) *kernel_ms = ms;
+        run_timed(dev, stream, kernel_ms, [&] {
+            FES_HIP(launch_signature_hash(sig, rows, num_words, hash, ones, dev.prop.multiProcessorCount, stream));
+        });
         return FASTLEC_OK;
     });
 }

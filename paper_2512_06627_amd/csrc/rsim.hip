@@ -12,12 +12,20 @@
 // The row's number of ones (before normalisation) is summed alongside; the
 // paper's stability and entropy features (Section 3.2) derive from it.
 //
-// Work decomposition: one wave per row, rows taken grid-stride.  Each lane
-// reads words lane, lane+64, ... (every wave load is 256 contiguous bytes);
-// four independent loads are in flight per lane per iteration.  The kernel is
-// bound by HBM reads: about 12 vector instructions per 64 words against 256
-// bytes of traffic.
+// Work decomposition: a workgroup takes a group of one or two rows and its waves the 256-word
+// chunks of their columns in turn; a lane reads four consecutive words of each row (1 KB per wave and
+// row), the next chunk's while it works on one.  The keys depend on the column alone and are made
+// once for the group: the finaliser's two multiplications and the 64-bit product run at a quarter of
+// the vector rate, so that one row at a time asks for about 90 issue cycles per 64 words, 60% of the
+// time that HBM takes to deliver them, and two rows for about 55.  The complement is taken out of the
+// sum: sum (~w) * key = (2^32 - 1) * sum key - sum w * key.
+//
+// Bound by HBM reads: 3,111 x 100,003 words 213 us, 5.8 TB/s (a wave per row with 1 KB of loads in
+// flight: 292 us, 4.3 TB/s), 1,870 x 131,706 166 us (308), 300 x 250,000 92 us (473: a row's chain of
+// loads); matrices that stay in the memory-side cache and short rows take what they took.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "kernels.hpp"
 
@@ -33,49 +41,128 @@ __device__ __forceinline__ uint32_t fmix32(uint32_t h) {
     return h;
 }
 
-__global__ void __launch_bounds__(256) signature_hash_kernel(const uint32_t* __restrict__ sig, uint64_t rows,
-                                                             uint64_t W, uint64_t* __restrict__ hash,
-                                                             uint64_t* __restrict__ ones) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
-    for (uint64_t r = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); r < rows; r += waves) {
-        const uint32_t* row = sig + r * W;
-        const uint32_t flip = 0u - (__builtin_amdgcn_readfirstlane(row[0]) & 1u);
-        uint64_t acc = 0, cnt = 0;
-        uint64_t k = lane;
-        for (; k + 192 < W; k += 256) {
-            uint32_t w[4];
+constexpr int kMaxSplit = 16;  // waves a row group's columns are shared among
+
+// Four words of R rows, their keys, into the sums.
+template <int R>
+__device__ __forceinline__ void accumulate(const uint32_t (&w)[R][4], const uint32_t (&key)[4], uint64_t (&sum)[2 * R],
+                                           uint64_t& keys) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) w[u] = row[k + 64 * u];
+    for (int u = 0; u < 4; ++u) keys += key[u];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            sum[j] += (uint64_t)w[j][u] * key[u];
+            bits += (uint32_t)__builtin_popcount(w[j][u]);
+        }
+        sum[R + j] += bits;
+    }
+}
+
+template <int R>
+__device__ __forceinline__ void load_chunk(uint32_t (&w)[R][4], const uint32_t* const (&row)[R], uint64_t k) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) __builtin_memcpy(w[j], row[j] + k, 16);
+}
+
+template <int R>
+__global__ void __launch_bounds__(64 * kMaxSplit) signature_hash_kernel(const uint32_t* __restrict__ sig,
+                                                                        uint64_t rows, uint64_t W,
+                                                                        uint64_t* __restrict__ hash,
+                                                                        uint64_t* __restrict__ ones) {
+    constexpr int N = 2 * R;  // sums of a wave: of w * key for each row, of ones for each row
+    __shared__ uint64_t part[kMaxSplit][N + 1];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), split = blockDim.x >> 6;
+    const uint64_t full = W / 256u;
+    for (uint64_t r0 = (uint64_t)blockIdx.x * R; r0 < rows; r0 += (uint64_t)gridDim.x * R) {
+        const uint32_t* row[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) row[j] = sig + min(r0 + j, rows - 1) * W;  // past the last: again the last
+
+        uint64_t sum[N] = {}, keys = 0;
+        uint32_t next[R][4];
+        if (wave < full) load_chunk<R>(next, row, wave * 256u + 4u * lane);
+        for (uint64_t c = wave; c < full; c += split) {
+            const uint64_t k = c * 256u + 4u * lane;
+            uint32_t w[R][4], key[4];
+            __builtin_memcpy(w, next, sizeof w);
+            if (c + split < full) load_chunk<R>(next, row, k + split * 256u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) key[u] = fmix32((uint32_t)k + u) | 1u;
+            accumulate<R>(w, key, sum, keys);
+        }
+        if (W % 256u && wave == full % split) {
+            const uint64_t k = full * 256u + 4u * lane;
+            uint32_t w[R][4], key[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                acc += (uint64_t)(w[u] ^ flip) * (uint64_t)(fmix32((uint32_t)(k + 64 * u)) | 1u);
-                cnt += (uint32_t)__builtin_popcount(w[u]);
+                const bool in = k + u < W;
+                const uint64_t at = in ? k + u : W - 1;
+#pragma unroll
+                for (int j = 0; j < R; ++j) w[j][u] = row[j][at];
+                key[u] = in ? fmix32((uint32_t)k + u) | 1u : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                for (int j = 0; j < R; ++j) w[j][u] = k + u < W ? w[j][u] : 0u;
+            }
+            accumulate<R>(w, key, sum, keys);
+        }
+
+        // Each step of the first ones leaves a lane half of the sums to go on with.
+        uint32_t off = 32;
+#pragma unroll
+        for (int half = N / 2; half > 0; half >>= 1, off >>= 1) {
+            const bool upper = lane & off;
+#pragma unroll
+            for (int i = 0; i < half; ++i) {
+                const uint64_t give = upper ? sum[i] : sum[i + half];
+                sum[i] = (upper ? sum[i + half] : sum[i]) + __shfl_xor(give, off, 64);
             }
         }
-        for (; k < W; k += 64) {
-            const uint32_t w = row[k];
-            acc += (uint64_t)(w ^ flip) * (uint64_t)(fmix32((uint32_t)k) | 1u);
-            cnt += (uint32_t)__builtin_popcount(w);
-        }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            acc += __shfl_xor(acc, off, 64);
-            cnt += __shfl_xor(cnt, off, 64);
-        }
-        if (lane == 0) {
-            hash[r] = acc;
+        for (; off > 0; off >>= 1) sum[0] += __shfl_xor(sum[0], off, 64);
+#pragma unroll
+        for (uint32_t o = 32; o > 0; o >>= 1) keys += __shfl_xor(keys, o, 64);
+        if (lane % (64u / N) == 0) part[wave][lane / (64u / N)] = sum[0];
+        if (lane == 0) part[wave][N] = keys;
+        __syncthreads();
+        if (threadIdx.x < (uint32_t)R && r0 + threadIdx.x < rows) {
+            const uint64_t r = r0 + threadIdx.x;
+            uint64_t acc = 0, cnt = 0, all = 0;
+            for (uint32_t v = 0; v < split; ++v) {
+                acc += part[v][threadIdx.x];
+                cnt += part[v][R + threadIdx.x];
+                all += part[v][N];
+            }
+            hash[r] = sig[r * W] & 1u ? all * 0xFFFFFFFFu - acc : acc;
             ones[r] = cnt;
         }
+        __syncthreads();
     }
 }
 
 }  // namespace
 
+// Rows per group: two where that leaves a group per CU (600 x 250,000 words: 136 us, one at a time
+// 186; with groups of four the latency of their reduction shows on short rows, 6,000 x 300: 8.7 us
+// against 6.8, and long ones gain nothing).  Then about 16 waves a CU (with a chunk in hand and one
+// on the way that is 64 KB per CU in flight), shared out so that a group's waves end together; 3,055 x
+// 12,511: 29 us, with 32 waves 34.
 hipError_t launch_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
-                                 uint64_t* ones, int grid, hipStream_t stream) {
-    if (!sig || !hash || !ones || rows == 0 || words == 0 || grid <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(signature_hash_kernel, dim3(grid), dim3(256), 0, stream, sig, rows, words, hash, ones);
+                                 uint64_t* ones, int cus, hipStream_t stream) {
+    if (!sig || !hash || !ones || rows == 0 || words == 0 || cus <= 0) return hipErrorInvalidValue;
+    const uint64_t per = rows >= 2ull * cus ? 2 : 1;
+    const uint64_t groups = (rows + per - 1) / per, chunks = (words + 255) / 256;
+    const uint64_t most = std::clamp<uint64_t>(16ull * cus / groups, 1, kMaxSplit);
+    const uint64_t turns = (chunks + most - 1) / most, split = (chunks + turns - 1) / turns;
+    const dim3 grid((uint32_t)std::min<uint64_t>(groups, 1u << 20)), block((uint32_t)(64 * split));
+    if (per == 2) hipLaunchKernelGGL(signature_hash_kernel<2>, grid, block, 0, stream, sig, rows, words, hash, ones);
+    else hipLaunchKernelGGL(signature_hash_kernel<1>, grid, block, 0, stream, sig, rows, words, hash, ones);
     return hipGetLastError();
 }
 
