@@ -54,8 +54,8 @@ __device__ __forceinline__ const FES_CONST T* as_const(const T* p) {
 
 // Next item number of a claim counter.  Each of the wave's 64 lanes adds 1, which the compiler turns
 // into one atomic of 64; an operand that differs by lane (1 from lane 0 only) becomes a scalar loop
-// over the 64 lanes, as long as a pass over a hundred gates.  A launch with a wave for every item
-// claims nothing (wave w takes item w).
+// over the 64 lanes, as long as a pass over a hundred gates.  The register tier's launches with a
+// wave for every item claim nothing (wave w takes item w).
 __device__ __forceinline__ uint64_t next_claim(unsigned long long* counter) {
     return uniform64(atomicAdd(counter, 1ull)) >> 6;
 }
@@ -103,17 +103,15 @@ __global__ void __launch_bounds__(1024) es_interp_kernel(InterpLaunch L) {
     // Control flow stays wave-uniform: every lane takes part in the claim and in the
     // atomicMin (all lanes hold the same value), so no branch depends on the lane and every
     // loop exit is a scalar branch.
-    const uint32_t wave_gid = blockIdx.x * (blockDim.x >> 6) + wave;
+    const uint32_t wave_gid = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + wave);
     // A grid with fewer waves than counters uses one counter per wave, so every counter in
     // use has a wave and every item is claimed.
     const uint32_t waves = gridDim.x * (blockDim.x >> 6);
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
-    const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);  // wave-uniform
+    const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
-    const bool one_each = L.total_items <= waves;
-    for (bool more = true; more;) {
-        const uint64_t item = one_each ? wave_gid : claim + next_claim(counter) * nclaim;
-        more = !one_each;
+    for (;;) {
+        const uint64_t item = claim + next_claim(counter) * nclaim;
         if (item >= L.total_items) break;
         if (L.cancel && __builtin_amdgcn_readfirstlane(
                             __hip_atomic_load(L.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)))
