@@ -12,6 +12,7 @@ fallback implementation.
 """
 import ctypes
 import os
+import struct
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "_lib", "libfastlec_es.so")
@@ -69,7 +70,21 @@ class fastlec_es_result(ctypes.Structure):
                 ("queued_ms", ctypes.c_double), ("latency_ms", ctypes.c_double), ("predicted_ms", ctypes.c_double)]
 
     def as_dict(self):
-        return {f: getattr(self, f) for f, _ in self._fields_ if f != "reserved"}
+        return _result_dicts(self)[0]
+
+
+# The fields of a result in memory; unpacking them together costs a third of reading them one by one.
+_RESULT = struct.Struct("=i4xQQQ6d")
+assert _RESULT.size == ctypes.sizeof(fastlec_es_result)
+
+
+def _result_dicts(results) -> list:
+    """The dicts of a result structure or an array of them."""
+    return [{"verdict": verdict, "cex": cex, "patterns_evaluated": patterns, "next_word": next_word, "plan_ms": plan,
+             "compile_ms": compiled, "kernel_ms": kernel, "queued_ms": queued, "latency_ms": latency,
+             "predicted_ms": predicted}
+            for verdict, cex, patterns, next_word, plan, compiled, kernel, queued, latency, predicted
+            in _RESULT.iter_unpack(bytes(results))]
 
 
 class fastlec_es_server_stats(ctypes.Structure):
@@ -261,8 +276,8 @@ def fastlec_es_check_batch(circuits, **opts) -> list:
     o = options(**opts)
     rc = lib().fastlec_es_check_batch(arr, k, ctypes.byref(o), res)
     if rc:
-        _raise(rc, [r.as_dict() for r in res])
-    return [r.as_dict() for r in res]
+        _raise(rc, _result_dicts(res))
+    return _result_dicts(res)
 
 
 def fastlec_es_compile_specialized(circuit: Circuit, waves_per_eu: int = 2):
@@ -381,13 +396,14 @@ def fastlec_es_submiter_aag(circuit: Circuit, class_of, polarity, target: int):
     pp = pol.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8))
     need = ctypes.c_size_t()
     k = ctypes.c_uint32()
-    rc = L.fastlec_es_submiter_aag(circuit.handle, cp, pp, cls.size, target, None, 0, ctypes.byref(need), None,
+    ins = (ctypes.c_uint32 * 64)()  # a circuit has at most 63 inputs
+    # Most sub-miters fit a first guess; the library says what a longer one needs.
+    buf = ctypes.create_string_buffer(min(32 * (cls.size + 8), 1 << 16))
+    rc = L.fastlec_es_submiter_aag(circuit.handle, cp, pp, cls.size, target, buf, len(buf), ctypes.byref(need), ins,
                                    ctypes.byref(k))
-    if rc:
-        _raise(rc)
-    buf = ctypes.create_string_buffer(need.value)
-    ins = (ctypes.c_uint32 * max(1, circuit.info()["num_pis"]))()
-    rc = L.fastlec_es_submiter_aag(circuit.handle, cp, pp, cls.size, target, buf, need.value, None, ins, None)
+    if rc and need.value > len(buf):
+        buf = ctypes.create_string_buffer(need.value)
+        rc = L.fastlec_es_submiter_aag(circuit.handle, cp, pp, cls.size, target, buf, need.value, None, ins, None)
     if rc:
         _raise(rc)
     return buf.value, list(ins[:k.value])

@@ -371,11 +371,13 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                 nk.push_back(got[j]);
             }
         }
-        // The interpreter's streams of the others, planned on host threads.
+        // The interpreter's streams of the others, planned and encoded on host threads.
         std::vector<Circuit*> plan;
         for (size_t i = 0; i < k; ++i)
             if (!is_nat[i] && !v[i]->planned(4)) plan.push_back(v[i]);
-        parallel_for(plan.size(), [&](size_t j) { (void)plan[j]->plan_for(4); });
+        parallel_for(plan.size(), [&](size_t j) {
+            if (model_interp_tier(plan[j]->interp_rows()) < 3) (void)plan[j]->regs_stream();
+        });
         // Of the others, cones the runtime model gives to the specialized kernel (AUTO only) run as their own
         // launches; the rest share interpreter launches.  Their kernels compile together as
         // hipRTC programs side by side in helper processes, so a cone is a candidate when its

@@ -1,8 +1,6 @@
 #include "plan.hpp"
 
 #include <algorithm>
-#include <functional>
-#include <queue>
 #include <string>
 
 namespace fes {
@@ -78,122 +76,188 @@ std::vector<uint32_t> dfs_order(const Aig& g, const Cone& c, bool by_label) {
     return order;
 }
 
-struct Alloc {
-    std::vector<Instr> prog;
-    uint32_t slots = 0;
-    uint32_t gates = 0;
+// Set of numbers below a bound with its smallest member at hand: one bit each, and one bit per word
+// of the level below.
+class MinSet {
+public:
+    explicit MinSet(uint32_t bound) {
+        do {
+            bound = (bound + 63) / 64;
+            levels_.emplace_back(bound, 0);
+        } while (bound > 1);
+    }
+    void insert(uint32_t x) {
+        for (auto& l : levels_) {
+            const uint64_t was = l[x >> 6];
+            l[x >> 6] |= 1ull << (x & 63);
+            if (was) return;
+            x >>= 6;
+        }
+    }
+    bool empty() const { return levels_.back()[0] == 0; }
+    uint32_t take_min() {
+        uint32_t x = 0;
+        for (size_t i = levels_.size(); i-- > 0;) x = x * 64 + (uint32_t)__builtin_ctzll(levels_[i][x]);
+        uint32_t at = x;
+        for (auto& l : levels_) {
+            l[at >> 6] &= ~(1ull << (at & 63));
+            if (l[at >> 6]) break;
+            at >>= 6;
+        }
+        return x;
+    }
+
+private:
+    std::vector<std::vector<uint64_t>> levels_;
 };
+
+// An order cut into bundles: bundle i holds gates[ends[i - 1] .. ends[i]).
+struct Bundles {
+    std::vector<uint32_t> gates, ends;
+};
+
+// Readers of each gate among the gates of the cone, in the order `order`.
+struct Readers {
+    std::vector<uint32_t> first, gate, missing;  // gate[first[k] .. first[k + 1]): readers of k
+};
+
+Readers readers_of(const Aig& g, const std::vector<uint32_t>& order) {
+    Readers r;
+    const uint32_t A = g.num_ands();
+    r.first.assign(A + 1, 0);
+    r.missing.assign(A, 0);
+    for (uint32_t k : order)
+        for (uint32_t f : {g.and_r0[k] >> 1, g.and_r1[k] >> 1})
+            if (is_and(g, f)) {
+                ++r.missing[k];
+                ++r.first[and_index(g, f) + 1];
+            }
+    for (uint32_t k = 0; k < A; ++k) r.first[k + 1] += r.first[k];
+    r.gate.resize(r.first[A]);
+    std::vector<uint32_t> at(r.first.begin(), r.first.end() - 1);
+    for (uint32_t k : order)
+        for (uint32_t f : {g.and_r0[k] >> 1, g.and_r1[k] >> 1})
+            if (is_and(g, f)) r.gate[at[and_index(g, f)]++] = k;
+    return r;
+}
 
 // Group an order into bundles of independent gates by list scheduling: a gate is ready when
 // its AND fanins were computed in an earlier bundle; each bundle takes up to `B` ready gates
 // in order of their position in `order`.
-std::vector<std::vector<uint32_t>> bundle_order(const Aig& g, const std::vector<uint32_t>& order, uint32_t B) {
-    std::vector<std::vector<uint32_t>> bundles;
+Bundles bundle_order(const Aig& g, std::vector<uint32_t> order, const Readers& readers, uint32_t B) {
+    Bundles out;
     if (B <= 1) {
-        for (uint32_t k : order) bundles.push_back({k});
-        return bundles;
+        out.ends.resize(order.size());
+        for (uint32_t i = 0; i < order.size(); ++i) out.ends[i] = i + 1;
+        out.gates = std::move(order);
+        return out;
     }
-    const uint32_t A = g.num_ands();
-    std::vector<uint32_t> pos(A, UINT32_MAX), missing(A, 0);
+    std::vector<uint32_t> pos(g.num_ands(), UINT32_MAX), missing = readers.missing;
     for (uint32_t i = 0; i < order.size(); ++i) pos[order[i]] = i;
-    std::vector<std::vector<uint32_t>> users(A);
+    MinSet ready((uint32_t)order.size());  // by position
     for (uint32_t k : order)
-        for (uint32_t f : {g.and_r0[k] >> 1, g.and_r1[k] >> 1})
-            if (is_and(g, f)) {
-                ++missing[k];
-                users[and_index(g, f)].push_back(k);
-            }
-    std::priority_queue<uint32_t, std::vector<uint32_t>, std::greater<uint32_t>> ready;  // by position
-    for (uint32_t k : order)
-        if (missing[k] == 0) ready.push(pos[k]);
-    size_t emitted = 0;
-    while (emitted < order.size()) {
-        std::vector<uint32_t> b;
-        while (b.size() < B && !ready.empty()) {
-            b.push_back(order[ready.top()]);
-            ready.pop();
+        if (missing[k] == 0) ready.insert(pos[k]);
+    out.gates.reserve(order.size());
+    while (out.gates.size() < order.size()) {
+        const size_t first = out.gates.size();
+        while (out.gates.size() < first + B && !ready.empty()) out.gates.push_back(order[ready.take_min()]);
+        for (size_t i = first; i < out.gates.size(); ++i) {
+            const uint32_t k = out.gates[i];
+            for (uint32_t j = readers.first[k]; j < readers.first[k + 1]; ++j)
+                if (--missing[readers.gate[j]] == 0) ready.insert(pos[readers.gate[j]]);
         }
-        for (uint32_t k : b)
-            for (uint32_t u : users[k])
-                if (--missing[u] == 0) ready.push(pos[u]);
-        emitted += b.size();
-        bundles.push_back(std::move(b));
+        out.ends.push_back((uint32_t)out.gates.size());
     }
-    return bundles;
+    return out;
 }
 
-Alloc allocate(const Aig& g, const std::vector<std::vector<uint32_t>>& bundles, uint32_t B) {
-    const uint32_t n = g.num_inputs, V = g.max_var();
-    std::vector<uint32_t> rc(V + 1, 0), pos_refs(V + 1, 0), neg_refs(V + 1, 0), slot(V + 1, UINT32_MAX);
-    for (auto& b : bundles)
-        for (uint32_t k : b) {
-            ++rc[g.and_r0[k] >> 1];
-            ++rc[g.and_r1[k] >> 1];
-        }
-    for (uint32_t o : g.outputs) {
-        ++rc[o >> 1];
-        (o & 1 ? neg_refs : pos_refs)[o >> 1]++;
+// Reads of every variable by the cone's gates, and by outputs plain and complemented.
+struct Refs {
+    std::vector<uint32_t> reads, pos, neg;
+};
+
+Refs refs_of(const Aig& g, const std::vector<uint32_t>& cone) {
+    Refs r;
+    const uint32_t V = g.max_var();
+    r.reads.assign(V + 1, 0);
+    r.pos.assign(V + 1, 0);
+    r.neg.assign(V + 1, 0);
+    for (uint32_t k : cone) {
+        ++r.reads[g.and_r0[k] >> 1];
+        ++r.reads[g.and_r1[k] >> 1];
     }
-    std::priority_queue<uint32_t, std::vector<uint32_t>, std::greater<uint32_t>> free_slots;
-    Alloc al;
+    for (uint32_t o : g.outputs) (o & 1 ? r.neg : r.pos)[o >> 1]++;
+    return r;
+}
+
+// Slots an order needs: values alive at once, a bundle's operands given up before its results.
+uint32_t count_slots(const Aig& g, const Bundles& b, const Refs& refs) {
+    std::vector<uint32_t> rc = refs.reads;
+    uint32_t slots = 0, live = 0, at = 0;
+    for (uint32_t end : b.ends) {
+        const uint32_t first = at;
+        for (; at < end; ++at)
+            for (uint32_t f : {g.and_r0[b.gates[at]] >> 1, g.and_r1[b.gates[at]] >> 1})
+                if (is_and(g, f) && --rc[f] == 0) --live;
+        live += end - first;
+        slots = std::max(slots, live);
+        for (uint32_t i = first; i < end; ++i)
+            if (rc[g.num_inputs + 1 + b.gates[i]] == 0) --live;
+    }
+    return slots;
+}
+
+// The stream: every result in the lowest free slot.
+std::vector<Instr> allocate(const Aig& g, const Bundles& bundles, const Refs& refs, uint32_t slots, uint32_t B,
+                            uint32_t* gates) {
+    const uint32_t n = g.num_inputs, V = g.max_var(), sink = n + 1 + slots;
+    std::vector<uint32_t> rc = refs.reads, slot(V + 1, UINT32_MAX);
+    MinSet free_slots(std::max(slots, 1u));
+    for (uint32_t i = 0; i < slots; ++i) free_slots.insert(i);
+    std::vector<Instr> prog;
+    prog.reserve(bundles.ends.size() * B + g.outputs.size() + B);
     auto row_of = [&](uint32_t var) { return is_and(g, var) ? n + 1 + slot[var] : var; };
     auto release = [&](uint32_t var) {
-        if (is_and(g, var) && --rc[var] == 0) free_slots.push(slot[var]);
+        if (is_and(g, var) && --rc[var] == 0) free_slots.insert(slot[var]);
     };
-    const Instr nop = {0u, 0u, UINT32_MAX, 0u};
-    for (auto& b : bundles) {
-        size_t first = al.prog.size();
+    const Instr nop = {0u, 0u, sink, 0u};
+    uint32_t at = 0;
+    for (uint32_t end : bundles.ends) {
+        const size_t first = prog.size();
+        const uint32_t* b = bundles.gates.data() + at;
+        const uint32_t count = end - at;
+        at = end;
         // Operands are read before any result of the bundle is written, so the slots whose
         // last reader is in this bundle are free for the bundle's own results.
-        for (uint32_t k : b) {
-            uint32_t a = g.and_r0[k], c = g.and_r1[k];
-            Instr ins;
-            ins.a = row_of(a >> 1) | ((a & 1) ? kCompl : 0u);
-            ins.b = row_of(c >> 1) | ((c & 1) ? kCompl : 0u);
-            ins.d = 0;
-            ins.flags = 0;
-            al.prog.push_back(ins);
+        for (uint32_t t = 0; t < count; ++t) {
+            const uint32_t a = g.and_r0[b[t]], c = g.and_r1[b[t]];
+            prog.push_back({row_of(a >> 1) | ((a & 1) ? kCompl : 0u), row_of(c >> 1) | ((c & 1) ? kCompl : 0u), 0u, 0u});
         }
-        for (uint32_t k : b) {
-            release(g.and_r0[k] >> 1);
-            release(g.and_r1[k] >> 1);
+        for (uint32_t t = 0; t < count; ++t) {
+            release(g.and_r0[b[t]] >> 1);
+            release(g.and_r1[b[t]] >> 1);
         }
-        for (size_t t = 0; t < b.size(); ++t) {
-            uint32_t v = n + 1 + b[t];
-            if (free_slots.empty()) {
-                slot[v] = al.slots++;
-            } else {
-                slot[v] = free_slots.top();
-                free_slots.pop();
-            }
-            Instr& ins = al.prog[first + t];
+        for (uint32_t t = 0; t < count; ++t) {
+            const uint32_t v = n + 1 + b[t];
+            slot[v] = free_slots.take_min();
+            Instr& ins = prog[first + t];
             ins.d = n + 1 + slot[v];
-            ins.flags = (pos_refs[v] ? kOutPos : 0u) | (neg_refs[v] ? kOutNeg : 0u) | (g.is_xor(b[t]) ? kXor : 0u);
+            ins.flags = (refs.pos[v] ? kOutPos : 0u) | (refs.neg[v] ? kOutNeg : 0u) | (g.is_xor(b[t]) ? kXor : 0u);
         }
-        for (uint32_t k : b) {
-            uint32_t v = n + 1 + k;
-            rc[v] -= pos_refs[v] + neg_refs[v];
-            if (rc[v] == 0) free_slots.push(slot[v]);
-        }
-        al.gates += (uint32_t)b.size();
-        while ((al.prog.size() - first) % B) al.prog.push_back(nop);
+        for (uint32_t t = 0; t < count; ++t)
+            if (rc[n + 1 + b[t]] == 0) free_slots.insert(slot[n + 1 + b[t]]);
+        while ((prog.size() - first) % B) prog.push_back(nop);
     }
+    *gates = (uint32_t)bundles.gates.size();
     // Outputs driven by a constant or a primary input: value AND true, into the sink row.
-    size_t first = al.prog.size();
+    const size_t first = prog.size();
     for (uint32_t o : g.outputs) {
         if (is_and(g, o >> 1)) continue;
-        Instr ins;
-        ins.a = (o >> 1) | ((o & 1) ? kCompl : 0u);
-        ins.b = 0u | kCompl;
-        ins.d = UINT32_MAX;
-        ins.flags = kOutPos;
-        al.prog.push_back(ins);
-        ++al.gates;
+        prog.push_back({(o >> 1) | ((o & 1) ? kCompl : 0u), 0u | kCompl, sink, kOutPos});
+        ++*gates;
     }
-    while ((al.prog.size() - first) % B) al.prog.push_back(nop);
-    for (Instr& ins : al.prog)
-        if (ins.d == UINT32_MAX) ins.d = n + 1 + al.slots;  // sink row
-    return al;
+    while ((prog.size() - first) % B) prog.push_back(nop);
+    return prog;
 }
 
 }  // namespace
@@ -247,20 +311,23 @@ Plan make_plan(const Aig& g, Order order, uint32_t bundle) {
             if (c.in[k]) file.push_back(k);
         cands.push_back({Order::File, std::move(file)});
     }
+    // The first of the candidates that need the fewest slots; only its stream is made.
+    const Refs refs = refs_of(g, cands.front().second);
+    Readers readers;
+    if (bundle > 1) readers = readers_of(g, cands.front().second);
+    Bundles best;
     bool have = false;
     for (auto& cand : cands) {
-        Alloc al = allocate(g, bundle_order(g, cand.second, bundle), bundle);
-        if (!have || al.slots < p.peak_slots) {
-            have = true;
-            p.peak_slots = al.slots;
-            p.prog = std::move(al.prog);
-            p.num_gate_instrs = al.gates;
-            p.order_used = cand.first;
-            p.order.clear();
-            for (auto& b : bundle_order(g, cand.second, bundle))
-                for (uint32_t k : b) p.order.push_back(k);
-        }
+        Bundles b = bundle_order(g, std::move(cand.second), readers, bundle);
+        const uint32_t slots = count_slots(g, b, refs);
+        if (have && slots >= p.peak_slots) continue;
+        have = true;
+        p.peak_slots = slots;
+        p.order_used = cand.first;
+        best = std::move(b);
     }
+    p.prog = allocate(g, best, refs, p.peak_slots, bundle, &p.num_gate_instrs);
+    p.order = std::move(best.gates);
     p.bundle = bundle;
     p.rows = g.num_inputs + p.peak_slots + 2;
     // Gate instructions write a slot row and appear in the stream in evaluation order;

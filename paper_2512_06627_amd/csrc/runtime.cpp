@@ -96,14 +96,6 @@ Circuit::~Circuit() {
             (void)hipSetDevice(cur);
         }
     }
-    for (auto& kv : dev_regs) {
-        if (!kv.second) continue;
-        int cur = 0;
-        if (hipGetDevice(&cur) == hipSuccess && hipSetDevice(kv.first) == hipSuccess) {
-            (void)hipFree(kv.second);
-            (void)hipSetDevice(cur);
-        }
-    }
     for (auto& kv : dev_prog) {
         if (!kv.second) continue;
         int cur = 0;
@@ -208,18 +200,54 @@ const std::vector<uint32_t>& Circuit::regs_stream() {
 }
 
 const uint32_t* Circuit::device_regs_stream(int dev, hipStream_t s) {
-    const std::vector<uint32_t>& h = regs_stream();
-    std::lock_guard<std::mutex> g(mu);
-    auto it = dev_regs.find(dev);
-    if (it != dev_regs.end()) return it->second;
-    uint32_t* d = nullptr;
-    FES_HIP(hipMalloc(&d, std::max<size_t>(h.size(), 1) * sizeof(uint32_t)));
-    if (!h.empty()) {
-        FES_HIP(hipMemcpyAsync(d, h.data(), h.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-        FES_HIP(hipStreamSynchronize(s));
+    {
+        std::lock_guard<std::mutex> g(mu);
+        auto it = dev_regs.find(dev);
+        if (it != dev_regs.end()) return it->second.words;
     }
-    dev_regs[dev] = d;
-    return d;
+    upload_regs_streams({this}, dev, s);
+    std::lock_guard<std::mutex> g(mu);
+    return dev_regs.at(dev).words;
+}
+
+void upload_regs_streams(const std::vector<Circuit*>& cs, int dev, hipStream_t s) {
+    // A block holds at most this much unless one stream is longer, and goes with the last of its circuits.
+    constexpr size_t kBlockWords = 1u << 20;
+    std::vector<Circuit*> missing;
+    for (Circuit* c : cs) {
+        std::lock_guard<std::mutex> g(c->mu);
+        if (!c->dev_regs.count(dev)) missing.push_back(c);
+    }
+    std::vector<uint32_t> words;
+    std::vector<size_t> at;
+    for (size_t i = 0, end; i < missing.size(); i = end) {
+        words.clear();
+        at.clear();
+        for (end = i; end < missing.size(); ++end) {
+            const std::vector<uint32_t>& h = missing[end]->regs_stream();
+            if (end > i && words.size() + h.size() > kBlockWords) break;
+            at.push_back(words.size());
+            words.insert(words.end(), h.begin(), h.end());
+            words.resize((words.size() + 15) & ~size_t(15));  // the kernel's loads: 64-byte lines
+        }
+        void* d = nullptr;
+        FES_HIP(hipMalloc(&d, std::max<size_t>(words.size(), 1) * sizeof(uint32_t)));
+        const std::shared_ptr<void> block(d, [dev](void* p) {
+            int cur = 0;
+            if (hipGetDevice(&cur) == hipSuccess && hipSetDevice(dev) == hipSuccess) {
+                (void)hipFree(p);
+                (void)hipSetDevice(cur);
+            }
+        });
+        if (!words.empty()) {
+            FES_HIP(hipMemcpyAsync(d, words.data(), words.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+            FES_HIP(hipStreamSynchronize(s));
+        }
+        for (size_t j = i; j < end; ++j) {  // another thread may have been faster
+            std::lock_guard<std::mutex> g(missing[j]->mu);
+            missing[j]->dev_regs.emplace(dev, Circuit::DevStream{(const uint32_t*)d + at[j - i], block});
+        }
+    }
 }
 
 const Plan& Circuit::sim_plan(uint32_t bundle) {
@@ -603,6 +631,7 @@ uint64_t build_descs(Device& dev, const std::vector<Circuit*>& cs, const std::ve
         cost[i] = lpt_cost_ms(cs[i]->interp_gates(), cs[i]->interp_rows(),
                               32.0 * (double)(ranges[i].end - ranges[i].begin));
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+    if (sch.regs) upload_regs_streams(cs, dev.ordinal, stream);
     uint64_t item = 0;
     for (size_t t = 0; t < k; ++t) {
         size_t i = order[t];

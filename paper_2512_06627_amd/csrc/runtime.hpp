@@ -109,7 +109,11 @@ struct Circuit {
     const std::vector<uint32_t>& regs_stream();
     const uint32_t* device_regs_stream(int device, hipStream_t s);
     std::vector<uint32_t> regs_host;
-    std::map<int, uint32_t*> dev_regs;
+    struct DevStream {
+        const uint32_t* words = nullptr;
+        std::shared_ptr<void> block;  // device memory that holds it, with other circuits' streams perhaps
+    };
+    std::map<int, DevStream> dev_regs;
     // Simulation stream of the register tier (encode_sim_stream) and its gate records.
     const uint32_t* device_sim_stream(int device, hipStream_t s, uint32_t* gates);
     std::map<int, uint32_t*> dev_sim_stream;
@@ -215,6 +219,8 @@ uint64_t noalloc_check(Device& dev, Circuit& c, const fastlec_es_options& o, con
 // Descriptors of an interpreter launch, written to `out` in longest-processing-time order
 // (most gate evaluations first); cone i reports into best[best_index[i]].  Returns the
 // launch's total number of work items.
+// The register-tier streams of those circuits that have none on the device yet, in few uploads.
+void upload_regs_streams(const std::vector<Circuit*>& cs, int device, hipStream_t s);
 uint64_t build_descs(Device& dev, const std::vector<Circuit*>& cs, const std::vector<HwRange>& ranges,
                      const std::vector<uint32_t>& best_index, const Schedule& sch, hipStream_t stream,
                      ConeDesc* out);

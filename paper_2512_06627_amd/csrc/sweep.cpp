@@ -90,19 +90,36 @@ std::string submiter_aag(const Aig& g, const uint32_t* class_of, const uint8_t* 
     auto lit_of = [&](uint32_t lit) { return 2 * new_var[lit >> 1] + (lit & 1); };
     const uint32_t a = lit_of(2 * target), b = lit_of(2 * rep) ^ ph;
     const uint32_t t1 = next, t2 = next + 1, out = next + 2;
-    std::string s;
-    s.reserve(16 * (num_kept + k + 8));
-    s += "aag " + std::to_string(out) + " " + std::to_string(k) + " 0 1 " + std::to_string(num_kept + 3) + "\n";
-    for (uint32_t i = 1; i <= k; ++i) s += std::to_string(2 * i) + "\n";
-    s += std::to_string(2 * out) + "\n";
-    auto line = [&](uint32_t lhs, uint32_t x, uint32_t y) {
-        s += std::to_string(lhs) + " " + std::to_string(x) + " " + std::to_string(y) + "\n";
+    // Numbers have at most 10 digits; the text is cut to its length at the end.
+    std::string s((3 * 11) * ((size_t)num_kept + k + 8), '\0');
+    char* at = &s[0];
+    auto number = [&](uint32_t x, char end) {
+        char digits[10];
+        int d = 0;
+        do digits[d++] = (char)('0' + x % 10);
+        while (x /= 10);
+        while (d) *at++ = digits[--d];
+        *at++ = end;
     };
+    auto line = [&](uint32_t lhs, uint32_t x, uint32_t y) {
+        number(lhs, ' ');
+        number(x, ' ');
+        number(y, '\n');
+    };
+    for (char c : {'a', 'a', 'g', ' '}) *at++ = c;
+    number(out, ' ');
+    number(k, ' ');
+    number(0, ' ');
+    number(1, ' ');
+    number(num_kept + 3, '\n');
+    for (uint32_t i = 1; i <= k; ++i) number(2 * i, '\n');
+    number(2 * out, '\n');
     for (uint32_t u = n + 1; u <= V; ++u)
         if (kept[u]) line(2 * new_var[u], lit_of(fa[u]), lit_of(fb[u]));
     line(2 * t1, a, b);
     line(2 * t2, a ^ 1, b ^ 1);
     line(2 * out, 2 * t1 + 1, 2 * t2 + 1);
+    s.resize((size_t)(at - s.data()));
     return s;
 }
 
