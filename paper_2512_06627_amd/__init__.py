@@ -178,7 +178,9 @@ def _stream_handle(stream):
         return None
     if isinstance(stream, int):
         return stream
-    return stream.cuda_stream  # torch.cuda.Stream
+    # torch.cuda.Stream.  Its default stream has the handle 0, by which the library means a stream of
+    # its own that does not wait for it: hipStreamLegacy names the default stream.
+    return stream.cuda_stream or 1
 
 
 def options(device=0, stream=None, words_per_thread=0, tile_words=0, wg_size=0, kernel="auto",
