@@ -26,12 +26,9 @@ struct Prepared {
         NativeMany many;
     };
     std::vector<Launch> launches;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
     uint64_t last_use = 0;
     Device* dev = nullptr;
     ~Prepared() {
-        if (e0) (void)hipEventDestroy(e0);
-        if (e1) (void)hipEventDestroy(e1);
         if (dev && buf.dev) dev->release(buf);
     }
 };
@@ -87,7 +84,7 @@ std::shared_ptr<Prepared> prepare(Device& dev, const std::vector<BatchPart>& par
     }
     b->claim_words = sets * (kClaimBytes / 8);
     b->best_off = sets * kClaimBytes;
-    const size_t interp_off = (b->best_off + 8 * n + 63) & ~size_t(63);
+    const size_t interp_off = (b->best_off + 8 * (n + 1) + 63) & ~size_t(63);
     const size_t native_off = (interp_off + sizeof(ConeDesc) * interp_cones + 63) & ~size_t(63);
     const size_t files_off = (native_off + sizeof(NativeDesc) * native_cones + 255) & ~size_t(255);
     b->buf = dev.acquire(files_off + file_bytes, files_off);
@@ -125,8 +122,6 @@ std::shared_ptr<Prepared> prepare(Device& dev, const std::vector<BatchPart>& par
         }
         b->launches.push_back(std::move(l));
     }
-    FES_HIP(hipEventCreate(&b->e0));
-    FES_HIP(hipEventCreate(&b->e1));
     FES_HIP(hipMemcpyAsync(devp, host, files_off, hipMemcpyHostToDevice, stream));
     FES_HIP(hipStreamSynchronize(stream));  // other calls may use it on other streams
     return b;
@@ -160,25 +155,23 @@ void run_batch(Device& dev, const std::vector<BatchPart>& parts, size_t n, hipSt
     }
     std::lock_guard<std::mutex> one(b->mu);
     uint8_t *host = (uint8_t*)b->buf.host, *devp = (uint8_t*)b->buf.dev;
+    unsigned long long* const found = (unsigned long long*)(host + b->best_off);
+    double t = 0;
     try {
-        FES_HIP(hipEventRecord(b->e0, stream));
+        __atomic_store_n(found + n, kPending, __ATOMIC_RELEASE);
         for (const Prepared::Launch& l : b->launches) {
             if (l.native) native_many_enqueue(l.many, stream);
             else if (l.L.num_cones) FES_HIP(launch_schedule(l.L, l.sch, stream));
         }
-        FES_HIP(hipEventRecord(b->e1, stream));
         FES_HIP(launch_finish((unsigned long long*)devp, (uint32_t)b->claim_words,
-                              (unsigned long long*)(devp + b->best_off), (uint32_t)n,
-                              (unsigned long long*)(host + b->best_off), stream));
-        FES_HIP(hipStreamSynchronize(stream));
+                              (unsigned long long*)(devp + b->best_off), (uint32_t)n, found, stream));
+        t = wait_finished(found + n, stream);
     } catch (...) {
         drop(b);  // its control block is no longer known to be clean
         throw;
     }
-    float t = 0;
-    FES_HIP(hipEventElapsedTime(&t, b->e0, b->e1));
     if (ms) *ms = t;
-    best.assign((uint64_t*)(host + b->best_off), (uint64_t*)(host + b->best_off) + n);
+    best.assign((uint64_t*)found, (uint64_t*)found + n);
 }
 
 const bool g_registered = (register_batch_runner(&run_batch), true);

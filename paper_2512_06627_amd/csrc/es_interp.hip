@@ -110,6 +110,7 @@ __global__ void __launch_bounds__(1024) es_interp_kernel(InterpLaunch L) {
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
     const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
+    if (!kSim && wave_gid == 0 && lane == 0) L.ctl->next_item[kStartWord] = __builtin_amdgcn_s_memrealtime();
     for (;;) {
         const uint64_t item = claim + next_claim(counter) * nclaim;
         if (item >= L.total_items) break;
@@ -500,6 +501,7 @@ es_interp_regs_kernel(InterpLaunch L) {
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
     const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
+    if (wave_gid == 0 && lane == 0) L.ctl->next_item[kStartWord] = __builtin_amdgcn_s_memrealtime();
     const bool one_each = L.total_items <= waves;
     for (bool more = true; more;) {
         const uint64_t item = one_each ? wave_gid : claim + next_claim(counter) * nclaim;
@@ -764,27 +766,35 @@ hipError_t launch_sim_regs_t(const InterpLaunch& L, int grid, hipStream_t stream
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) finish_kernel(unsigned long long* __restrict__ claims, uint32_t words,
-                                                     unsigned long long* __restrict__ best, uint32_t n,
-                                                     unsigned long long* __restrict__ host_best) {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i < n) {
+__global__ void __launch_bounds__(1024) finish_kernel(unsigned long long* __restrict__ claims, uint32_t words,
+                                                      unsigned long long* __restrict__ best, uint32_t n,
+                                                      unsigned long long* __restrict__ host_best) {
+    const uint64_t now = __builtin_amdgcn_s_memrealtime();
+    uint64_t start = now;
+    if (threadIdx.x == 0)
+        for (uint32_t i = kStartWord; i < words; i += kClaimCounters * kClaimStride)
+            if (claims[i] && claims[i] < start) start = claims[i];
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
         host_best[i] = best[i];
         best[i] = ~0ull;
     }
-    if (i < words) claims[i] = 0ull;
+    for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) claims[i] = 0ull;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(host_best + n, now - start, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Registers launch_finish with the host runtime.
 const bool g_finish_registered = (register_finish(&launch_finish), true);
 
 }  // namespace
 
 hipError_t launch_finish(unsigned long long* claims, uint32_t words, unsigned long long* best, uint32_t n,
                          unsigned long long* host_best, hipStream_t stream) {
-    const uint32_t threads = words > n ? words : n;
-    hipLaunchKernelGGL(finish_kernel, dim3((threads + 255) / 256), dim3(256), 0, stream, claims, words, best, n,
-                       host_best);
+    if (!claims || !best || !host_best || n == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(n <= 64 ? 64 : n <= 512 ? 256 : 1024), 0, stream, claims, words, best,
+                       n, host_best);
     return hipGetLastError();
 }
 

@@ -770,7 +770,7 @@ void run_jit(Device& dev, Circuit& c, JitKernel& k, const HwRange& r, uint64_t t
     if (!mem.ptr) {
         *best_out = run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& s) {
             jit_enqueue(lp, (uint64_t*)s.claims(), (uint64_t*)s.best(), cancel, stream);
-        });
+        }, k.native != nullptr);
         return;
     }
     check_dev_mem(mem, kClaimBytes + 8);

@@ -100,7 +100,9 @@ hipError_t launch_interp_regs(const InterpLaunch& L, int regs, int grid, hipStre
 
 // After the kernels of a call: best[0..n) goes to pinned host memory, and best[] and the `words`
 // claim words return to their state before a launch (all ones and zero), so that the next call
-// on this control block uploads nothing.
+// on this control block uploads nothing.  Then host_best[n] gets the time since the launch began, in
+// ticks of 10 ns: a caller that has put kPending there knows by it that all is done.
+constexpr unsigned long long kPending = ~0ull;
 hipError_t launch_finish(unsigned long long* claims, uint32_t words, unsigned long long* best, uint32_t n,
                          unsigned long long* host_best, hipStream_t stream);
 

@@ -5,16 +5,18 @@
 namespace fes {
 
 // Fitted on one MI355X by least squares on relative error (plain checks of 35 seeded layered cones
-// and four multiplier and MAC miters, n 12..32; paper_2512_06627_amd/calibrate.py): median (largest)
-// relative error 6% (52%) interpreter, 15% (59%) specialized, 0.7% (2%) compile.  Interpreter gates are
+// and four multiplier and MAC miters, n 12..32; paper_2512_06627_amd/calibrate.py), with the kernels' own
+// times from the first workgroup's start: median (largest) relative error 4% (59%, files above 232 rows
+// in small spaces) interpreter, 18% specialized (up to five times too much where a native kernel shares
+// work between assignments), 0.7% (2%) compile.  Interpreter gates are
 // the instructions of its bundled stream (three-AND XORs count once); its rate depends on the tier
 // that holds the value file.
 namespace model {
-constexpr double kInterpT0Ms = 0.0116;
+constexpr double kInterpT0Ms = 0.003;
 constexpr uint32_t kTierRows[3] = {104, 144, 232};  // register tier files; LDS or device memory above
 constexpr double kInterpRate[4] = {1.958e14, 2.126e14, 1.940e14, 4.04e13};  // gate instructions*patterns/s
-constexpr double kInterpMsPerGateFloor = 2.24e-5; // one wave pass per gate: spaces below a chip's waves
-constexpr double kSpecT0Ms = 0.0062;
+constexpr double kInterpMsPerGateFloor = 1.9e-5; // one wave pass per gate: spaces below a chip's waves
+constexpr double kSpecT0Ms = 0.0032;
 constexpr double kSpecLutPassesPerS = 7.5e11;
 constexpr double kCompileC0Ms = 101.7;
 constexpr double kCompileMsPerLut = 0.00664;

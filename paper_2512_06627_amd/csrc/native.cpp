@@ -71,7 +71,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight) {
 
 double run_ms(const JitKernel& k, double patterns) {
     const NativeKernel& n = *k.native;
-    return 0.012 + native_run_ms(n.code.valu + n.code.lds, (uint32_t)n.bits.size(), passes_of(patterns));
+    return 0.003 + native_run_ms(n.code.valu + n.code.lds, (uint32_t)n.bits.size(), passes_of(patterns));
 }
 
 double share_ms(const JitKernel& k, double patterns) {
@@ -80,7 +80,7 @@ double share_ms(const JitKernel& k, double patterns) {
 }
 
 double guess_run_ms(const Circuit& c, double patterns) {
-    return 0.012 + native_run_ms(0.26 * c.plan1.num_ands_tfi + 10, 0, passes_of(patterns));
+    return 0.003 + native_run_ms(0.26 * c.plan1.num_ands_tfi + 10, 0, passes_of(patterns));
 }
 
 double guess_build_ms(const Circuit& c) { return native_build_ms(c.plan1.num_ands_tfi); }

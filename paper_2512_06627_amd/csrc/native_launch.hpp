@@ -12,6 +12,9 @@ namespace fes {
 // parallel, and the items still start in roughly ascending order.
 constexpr uint32_t kClaimCounters = 16;
 constexpr uint32_t kClaimStride = 16;  // 64-bit words from one counter to the next (128 bytes)
+// Word of the claim block where a launch's first workgroup notes when it starts (realtime counter,
+// 100 MHz); the finish kernel makes the launch's time of it.
+constexpr uint32_t kStartWord = 1;
 
 constexpr uint32_t kMaxInner = 5;  // inner inputs of a native pass: up to 2^5 assignments
 

@@ -143,7 +143,7 @@ struct Buffer {
 // finish kernel leaves it so), the result in pinned host memory, and two events.
 struct ControlSlot {
     uint8_t* dev = nullptr;                  // claim counters, then best
-    unsigned long long* host_best = nullptr;  // pinned
+    unsigned long long* host_best = nullptr;  // pinned; best, then the finish kernel's ticks
     hipEvent_t e0 = nullptr, e1 = nullptr;
     unsigned long long* claims() const { return (unsigned long long*)dev; }
     unsigned long long* best() const { return (unsigned long long*)(dev + kClaimBytes); }
@@ -240,10 +240,12 @@ struct DevMem {
 // Checks that caller memory of `m.bytes` can hold `need` bytes (alignment and size).
 void check_dev_mem(const DevMem& m, size_t need);
 
-// Runs one check's kernel (`launch`, enqueued between the events) on a control slot and returns the
-// lowest failing pattern: no copies, one wait.
+// Runs one check's kernel on a control slot and returns the lowest failing pattern: no copies, one
+// wait.  `stamped`: the kernel notes its start (kStartWord); else events take the time.
 uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
-                     const std::function<void(const ControlSlot&)>& launch);
+                     const std::function<void(const ControlSlot&)>& launch, bool stamped = true);
+// Waits for the finish kernel that puts its ticks there (kPending before); the launch's ms.
+double wait_finished(unsigned long long* ticks, hipStream_t stream);
 
 // Runs `launch` between a slot's events and waits; for kernels that need no control words.
 void run_timed(Device& dev, hipStream_t stream, double* kernel_ms, const std::function<void()>& launch);

@@ -38,6 +38,7 @@ namespace {
 
 using fes::kClaimCounters;
 using fes::kClaimStride;
+using fes::kStartWord;
 using fes::NativeDesc;
 using fes::NativeLaunch;
 
@@ -111,6 +112,7 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
     // A claim adds 1 from each of the 64 lanes, which the compiler turns into one atomic of 64; a
     // value that differs by lane (1 from lane 0 only) becomes a 64-step scalar prefix loop.
     // A launch with a wave for every item claims nothing: wave w takes item w.
+    if (blockIdx.x == 0 && lane == 0) L.counters[kStartWord] = __builtin_amdgcn_s_memrealtime();
     const bool one_each = L.total_items <= waves;
     for (bool more = true; more;) {
         uint64_t item = blockIdx.x;
