@@ -79,6 +79,8 @@ void fill_result(const Circuit& c, const HwRange& r, uint64_t best, fastlec_es_r
 // compile model's largest error here is 4%.  The LUT program (needed for the specialized
 // prediction) is only built when the interpreter's time could pay for a compile.
 constexpr double kCompileMargin = 1.2;
+// What a millisecond of building a single check's native kernel costs against one of its run.
+constexpr double kCheckBuildWeight = 0.5;
 // Planning a cone's interpreter stream, per AND gate, and loading a module of native kernels.
 constexpr double kPlanMsPerGate = 0.5e-3, kLoadMs = 1.2;
 
@@ -115,19 +117,103 @@ bool native_allowed() {
     return true;
 }
 
-// The native kernel that a check of `span` half-words at a time (out of `patterns` patterns) runs
-// on, or null.  SPECIALIZED always takes it.  AUTO takes one that is built when it is expected to
-// be faster than the interpreter, and builds one when that pays (native_pays); a caller that
-// fixes the interpreter's schedule keeps the interpreter until a kernel is built.
-std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o, uint64_t span, double patterns) {
+// The native kernel that a check of `r` runs on, in pieces of `span` half-words, or null.  AUTO takes one
+// that is built when it is expected to be faster than the interpreter, and builds one when that
+// pays (native_pays; *later = true: the caller sees to it); a caller that fixes the interpreter's
+// schedule keeps the interpreter until a kernel is built.  SPECIALIZED takes the best kernel there is, a
+// native one made for other spans or the hipRTC one (then null), until what it costs beyond a kernel
+// for this span has paid for building that (MAC8, three fifths of the space after compile_specialized:
+// first check 1.6 ms on the whole space's kernel, 7.9 with one more build); without any it builds one.
+std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o, const HwRange& r, uint64_t span,
+                                         bool* later) {
     if (o.kernel != FASTLEC_KERNEL_SPECIALIZED && o.kernel != FASTLEC_KERNEL_AUTO) return nullptr;
     if (!native_allowed()) return nullptr;
     const NativeTier* t = native_tier();
-    if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) return t->get(c, span, 0.0);
+    const bool whole = span >= r.end - r.begin;
+    const double patterns = 32.0 * (double)(r.end - r.begin);
+    if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) {
+        double have = 0;
+        bool fits = false;
+        std::shared_ptr<JitKernel> k = whole ? t->best(c, r, &have, &fits) : nullptr;
+        const bool rtc = jit_ready(c, specialized_waves_per_eu()) != nullptr;
+        if (fits) return k;
+        if (!whole || (!k && !rtc)) return t->get(c, span, 0.0, nullptr);
+        const double aim = k ? t->run_ms(*k, patterns) : t->guess_run_ms(c, patterns);
+        const double by_rtc = rtc ? model_specialized_ms(c.lut_steps_known(), patterns) : 1e300;
+        if (!k || by_rtc < have) {
+            k = nullptr;
+            have = by_rtc;
+        }
+        if (have > 1.1 * aim && native_pays(c, have, patterns)) return t->get(c, span, 0.0, nullptr);
+        return k;
+    }
     if (o.words_per_thread || o.wg_size) return nullptr;
     const double interp = model_interp_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
     if (auto k = t->ready(c, span)) return t->run_ms(*k, patterns) < interp ? k : nullptr;
-    return native_pays(c, interp, patterns) ? t->get(c, span, 0.5) : nullptr;
+    if (!native_pays(c, interp, patterns)) return nullptr;
+    if (later) {
+        *later = true;
+        return nullptr;
+    }
+    return t->get(c, span, kCheckBuildWeight, nullptr);
+}
+
+// Builds a native kernel on a thread of its own.
+struct NativeBuilder {
+    std::atomic<bool> stop{false}, done{false};
+    std::shared_ptr<JitKernel> kernel;
+    std::thread t;
+    NativeBuilder(Circuit& c, uint64_t span) {
+        t = std::thread([this, &c, span] {
+            try {
+                kernel = native_tier()->get(c, span, kCheckBuildWeight, &stop);
+            } catch (...) {  // the interpreter goes on without it
+            }
+            done.store(true, std::memory_order_release);
+        });
+    }
+    void wait() { t.join(); }
+    ~NativeBuilder() {
+        stop.store(true, std::memory_order_relaxed);
+        if (t.joinable()) t.join();
+    }
+};
+
+// The beginning of a check of `full` on the interpreter, in ascending pieces of about half a
+// millisecond, while the native kernel for it is built: a counterexample that lies there is found
+// without the kernel (MAC8, words 12345677 to 54321011 with the first difference 1 ms into them: 1.9 ms
+// in place of 8.4), and otherwise the device has not waited.  Ends with the kernel (null if there can be
+// none), or with a pattern in *best, or at the end; *lo = first half-word not covered.  What is spent on the interpreter counts towards the kernel, as in native_pays: a
+// circuit whose checks keep ending early gets it once they have taken as long as building it.
+std::shared_ptr<JitKernel> check_while_building(Device& dev, Circuit& c, const fastlec_es_options& o,
+                                                const HwRange& full, hipStream_t stream, uint64_t* lo, uint64_t* best,
+                                                double* kernel_ms) {
+    const double patterns = 32.0 * (double)(full.end - full.begin);
+    NativeBuilder b(c, full.end - full.begin);
+    const double t0 = now_ms();
+    std::vector<Circuit*> one{&c};
+    const double total = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
+    const uint64_t piece = ((uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total)) + 4095) / 4096 * 4096;
+    Schedule sch = default_schedule(dev, one, &o, std::min(piece, full.end - full.begin));
+    if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
+    while (*lo < full.end && *best == ~0ull && !b.done.load(std::memory_order_acquire)) {
+        const uint64_t end = std::min(full.end, *lo + piece);
+        std::vector<uint64_t> found;
+        double ms = 0;
+        run_interp(dev, one, {HwRange{*lo, end}}, sch, stream, nullptr, found, &ms,
+                   DevMem{o.dev_scratch, o.dev_scratch ? o.dev_scratch_bytes : 0});
+        *kernel_ms += ms;
+        *best = found[0];
+        *lo = end;
+    }
+    const double here = now_ms() - t0, spent = c.interp_ms_spent.load(std::memory_order_relaxed);
+    if (*lo == full.end || *best != ~0ull) {
+        if (spent + here > 1.5 * (native_tier()->guess_build_ms(c) + 1.0)) b.wait();
+        else c.interp_ms_spent.store(spent + here, std::memory_order_relaxed);
+        return nullptr;
+    }
+    b.wait();
+    return b.kernel;
 }
 
 void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) {
@@ -145,9 +231,14 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
     const double t_start = now_ms();
     const double patterns = 32.0 * (double)(full.end - full.begin);
     double compile_ms = 0;
-    std::shared_ptr<JitKernel> jk = native_kernel(c, o, std::min(chunk, full.end - full.begin), patterns);
+    bool build = false;
+    std::shared_ptr<JitKernel> jk =
+        native_kernel(c, o, full, std::min(chunk, full.end - full.begin), chunked ? nullptr : &build);
+    double kernel_ms = 0;
+    uint64_t best = ~0ull, first = full.begin;
+    if (build) jk = check_while_building(dev, c, o, full, stream, &first, &best, &kernel_ms);
     const bool native = jk != nullptr;
-    const bool spec = native || use_specialized(c, o, full);
+    const bool spec = native || (first < full.end && best == ~0ull && use_specialized(c, o, full));
     if (spec && !native) jk = jit_kernel(c, specialized_waves_per_eu(), &compile_ms);
     Schedule sch;
     if (!spec) {
@@ -155,11 +246,9 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
         sch = default_schedule(dev, one, &o, full.end - full.begin);
         if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
     }
-    double kernel_ms = 0;
-    uint64_t best = ~0ull;
     uint64_t done_to = full.begin;
     int status = FASTLEC_OK;
-    for (uint64_t lo = full.begin; lo < full.end && best == ~0ull; lo += chunk) {
+    for (uint64_t lo = first; lo < full.end && best == ~0ull; lo += chunk) {
         if (chunked) {
             if (o.cancel_flag && *o.cancel_flag) { status = FASTLEC_CANCELLED; break; }
             if (o.deadline_s > 0 && now_ms() - t_start >= o.deadline_s * 1e3) { status = FASTLEC_TIMEOUT; break; }
@@ -362,7 +451,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             }
             parallel_for(build.size(), [&](size_t b) {
                 const size_t j = build[b];
-                got[j] = t->get(*v[want[j]], rs[want[j]].end - rs[want[j]].begin, forced ? 0.0 : 0.2);
+                got[j] = t->get(*v[want[j]], rs[want[j]].end - rs[want[j]].begin, forced ? 0.0 : 0.2, nullptr);
             });
             for (size_t j = 0; j < want.size(); ++j) {
                 if (!got[j]) continue;  // its values fit neither registers nor LDS
@@ -661,7 +750,7 @@ int fastlec_es_compile_specialized(const fastlec_es_circuit* c, int waves_per_eu
         std::shared_ptr<JitKernel> k;
         if (native_allowed()) {
             k = native_tier()->ready(cc, whole);
-            if (!k) native_tier()->get(cc, whole, 0.0);
+            if (!k) native_tier()->get(cc, whole, 0.0, nullptr);
         }
         if (!k) k = jit_kernel(cc, waves_per_eu, &ms);
         if (compile_ms) *compile_ms = ms;
@@ -675,7 +764,7 @@ int fastlec_es_native_info(const fastlec_es_circuit* c, uint32_t* inner, uint32_
         if (!c) throw Error{kErrInvalid, "null circuit"};
         Circuit& cc = const_cast<Circuit&>(c->c);
         std::shared_ptr<JitKernel> k;
-        if (const NativeTier* t = native_tier()) k = t->get(cc, range_of(cc.plan1.num_inputs, 0, 0).end, 0.0);
+        if (const NativeTier* t = native_tier()) k = t->get(cc, range_of(cc.plan1.num_inputs, 0, 0).end, 0.0, nullptr);
         if (!k) throw Error{kErrUnsupported, "no native kernel for this circuit"};
         native_tier()->counts(*k, inner, valu, waves);
         return FASTLEC_OK;

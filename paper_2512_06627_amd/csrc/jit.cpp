@@ -121,8 +121,8 @@ std::string jit_source(const LutProgram& lp, int waves_per_eu, int block, int* w
           << "  const u32 spill_addr = (u32)(unsigned long)(__attribute__((address_space(3))) u32*)(fes_spill + (threadIdx.x >> 6) * "
           << lds_slots * 64 << "u + lane);\n";
     }
-    // Control flow stays wave-uniform: every lane takes part in the claim (lane 0 adds 1, the
-    // others 0) and in the atomicMin (all lanes hold the same value), so no branch depends on
+    // Control flow stays wave-uniform: every lane takes part in the claim (each adds 1,
+    // one atomic of 64) and in the atomicMin (all lanes hold the same value), so no branch depends on
     // the lane and every loop exit is a scalar branch.
     // Claims are spread over several counters on separate 128-byte lines (counter s hands out
     // items s, s + C, s + 2C, ...), so short work items are not serialised at one atomic.
@@ -132,8 +132,9 @@ std::string jit_source(const LutProgram& lp, int waves_per_eu, int block, int* w
          "  const u32 nclaim = waves < " << kClaimCounters << "u ? waves : " << kClaimCounters << "u;\n"
          "  const u32 claim = __builtin_amdgcn_readfirstlane((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % nclaim);\n"
          "  u64* const counter = next_item + claim * " << kClaimStride << "u;\n"
+         "  if (blockIdx.x == 0u && threadIdx.x == 0u) next_item[" << kStartWord << "] = __builtin_amdgcn_s_memrealtime();\n"
          "  for (;;) {\n"
-         "    const u64 claimed = atomicAdd(counter, lane == 0u ? 1ull : 0ull);\n"
+         "    const u64 claimed = atomicAdd(counter, 1ull) >> 6;\n"
          "    const u64 k = ((u64)__builtin_amdgcn_readfirstlane((u32)(claimed >> 32)) << 32) |\n"
          "                  __builtin_amdgcn_readfirstlane((u32)claimed);\n"
          "    const u64 item = claim + k * nclaim;\n"
@@ -770,7 +771,7 @@ void run_jit(Device& dev, Circuit& c, JitKernel& k, const HwRange& r, uint64_t t
     if (!mem.ptr) {
         *best_out = run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& s) {
             jit_enqueue(lp, (uint64_t*)s.claims(), (uint64_t*)s.best(), cancel, stream);
-        }, k.native != nullptr);
+        });
         return;
     }
     check_dev_mem(mem, kClaimBytes + 8);

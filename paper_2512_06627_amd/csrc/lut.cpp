@@ -147,10 +147,12 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
     auto ref_of = [](uint64_t key) { return LutRef{(LutRef::Kind)((key >> 32) & 0xFF), (uint32_t)key}; };
     struct Cut {
         uint64_t keys[3];  // ascending; entries past n are unused
+        uint64_t sig;      // one bit per key (bit_of): two cuts with more than three together do not merge
         double af;
         uint8_t n;
         uint8_t tt;        // over keys in order (position j = bit 2-j)
     };
+    auto bit_of = [](uint64_t key) { return 1ull << ((key * 0x9E3779B97F4A7C15ull) >> 58); };
     std::vector<uint32_t> fanout(V + 1, 0);
     for (uint32_t k : plan.order) {
         ++fanout[g.and_r0[k] >> 1];
@@ -187,6 +189,7 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
             t.keys[0] = key_ref(l.ref);
             t.af = is_scalar_ref(l.ref) ? 0.25 : 0.0;  // a second scalar leaf costs a copy
         }
+        t.sig = bit_of(t.keys[0]);
         side[s][m++] = t;
         nside[s] = m;
     };
@@ -201,7 +204,11 @@ LutProgram make_lut_program(const Aig& g, const Plan& plan, int scalar_policy) {
         for (uint32_t xi = 0; xi < nside[0]; ++xi)
             for (uint32_t yi = 0; yi < nside[1]; ++yi) {
                 const Cut &x = side[0][xi], &y = side[1][yi];
+                uint64_t more = x.sig | y.sig;
+                for (int b = 0; b < 3; ++b) more &= more - 1;
+                if (more) continue;
                 Cut c;
+                c.sig = x.sig | y.sig;
                 c.n = 0;  // sorted union of the two leaf lists
                 uint32_t i = 0, j = 0;
                 bool fits = true;

@@ -43,7 +43,7 @@ std::shared_ptr<JitKernel> find(Circuit& c, uint64_t span, bool exact) {
 
 std::shared_ptr<JitKernel> ready(Circuit& c, uint64_t span) { return find(c, span, false); }
 
-std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight) {
+std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop) {
     if (auto k = find(c, span, true)) return k;
     std::lock_guard<std::mutex> build(c.native_mu);
     if (auto k = find(c, span, true)) return k;
@@ -52,7 +52,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight) {
     std::shared_ptr<NativeKernel> n;
     const int inner = forced_inner();
     if (inner >= 0) n = build_native(c.aig, c.plan1.order, limit, passes_of(patterns), 0, inner);
-    if (!n) n = build_native(c.aig, c.plan1.order, limit, passes_of(patterns), weight);
+    if (!n) n = build_native(c.aig, c.plan1.order, limit, passes_of(patterns), weight, -1, stop);
     if (!n) return nullptr;
     auto k = std::make_shared<JitKernel>();
     k->native = n;
@@ -72,6 +72,23 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight) {
 double run_ms(const JitKernel& k, double patterns) {
     const NativeKernel& n = *k.native;
     return 0.003 + native_run_ms(n.code.valu + n.code.lds, (uint32_t)n.bits.size(), passes_of(patterns));
+}
+
+std::shared_ptr<JitKernel> best(Circuit& c, const HwRange& r, double* ms, bool* fits) {
+    const uint32_t limit = inner_limit(c, r.end - r.begin);
+    std::shared_ptr<JitKernel> pick;
+    std::lock_guard<std::mutex> g(c.mu);
+    for (auto& kv : c.native) {
+        // A range is covered in whole blocks of patterns up to the highest inner input.
+        const uint32_t block = kv.second->native->bits.empty() ? 0 : kv.second->native->bits.back() + 1;
+        const uint64_t covered = (((r.end + ((1ull << block) - 1)) >> block) - (r.begin >> block)) << block;
+        const double t = run_ms(*kv.second, 32.0 * (double)covered);
+        if (pick && t >= *ms) continue;
+        pick = kv.second;
+        *ms = t;
+        *fits = kv.first == limit;
+    }
+    return pick;
 }
 
 double share_ms(const JitKernel& k, double patterns) {
@@ -144,7 +161,7 @@ void launch(hipFunction_t fn, const NativeLaunch& L, uint64_t grid, uint32_t lds
     FES_HIP(hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, 64, 1, 1, lds, stream, args, nullptr));
 }
 
-const NativeTier kTier = {ready, get, run_ms, share_ms, guess_run_ms, guess_build_ms, counts};
+const NativeTier kTier = {ready, get, best, run_ms, share_ms, guess_run_ms, guess_build_ms, counts};
 const bool g_registered = (register_native_tier(&kTier), true);
 
 }  // namespace

@@ -5,6 +5,7 @@
 // encode    native_emit.cpp  registers and machine words
 // run       native.cpp       code object, module, launches
 #pragma once
+#include <atomic>
 #include <cstdint>
 #include <memory>
 #include <vector>
@@ -67,9 +68,10 @@ std::vector<char> native_code_object(const std::vector<const NativeCode*>& codes
 // `limit`: as plan_inner.  `passes`: passes of 2,048 patterns that the kernel is built for.
 // `weight`: what a millisecond of building costs against one of kernel time (0: nothing).
 // `inner`: the number of inner inputs, or -1 for the one expected to be fastest.  Null when no
-// choice fits the registers and LDS.
+// choice fits the registers and LDS, or when *stop is set meanwhile.
 std::shared_ptr<NativeKernel> build_native(const Aig& g, const std::vector<uint32_t>& cone, uint32_t limit,
-                                           double passes, double weight, int inner = -1);
+                                           double passes, double weight, int inner = -1,
+                                           const std::atomic<bool>* stop = nullptr);
 
 // Expected kernel time of a pass of `valu` instructions with j inner inputs over `passes` passes.
 double native_run_ms(double valu, uint32_t j, double passes);

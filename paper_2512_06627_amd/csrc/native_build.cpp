@@ -61,7 +61,8 @@ double native_run_ms(double valu, uint32_t j, double passes) {
 double native_build_ms(double gates) { return 0.05 + kBuildMsPerGate * gates; }
 
 std::shared_ptr<NativeKernel> build_native(const Aig& g, const std::vector<uint32_t>& cone, uint32_t limit,
-                                           double passes, double weight, int inner) {
+                                           double passes, double weight, int inner, const std::atomic<bool>* stop) {
+    auto stopped = [&] { return stop && stop->load(std::memory_order_relaxed); };
     const double t0 = clock_ms();
     struct Option {
         double ms;
@@ -85,6 +86,7 @@ std::shared_ptr<NativeKernel> build_native(const Aig& g, const std::vector<uint3
     for (Option& o : options) {
         const uint32_t j = (uint32_t)o.c.inputs.size();
         if (tried.size() >= most && j) continue;
+        if (stopped()) return nullptr;
         o.s = share_cofactors(g, cone, o.c.inputs);
         const double vgprs = kVgprsPerLive * o.s.peak_live;
         const double luts = kLutsPerSharedGate * (double)o.s.order.size();
@@ -96,7 +98,9 @@ std::shared_ptr<NativeKernel> build_native(const Aig& g, const std::vector<uint3
     for (Option& o : tried) {
         Plan p;
         p.order = std::move(o.s.order);
+        if (stopped()) return nullptr;
         LutProgram lp = make_lut_program(o.s.aig, p, 2);
+        if (stopped()) return nullptr;
         order_for_registers(lp);
         auto k = std::make_shared<NativeKernel>();
         k->bits = o.s.bits;

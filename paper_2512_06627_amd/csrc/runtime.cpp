@@ -388,22 +388,15 @@ double wait_finished(unsigned long long* ticks, hipStream_t stream) {
 }
 
 uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
-                     const std::function<void(const ControlSlot&)>& launch, bool stamped) {
+                     const std::function<void(const ControlSlot&)>& launch) {
     // Around an empty kernel: uploads, read-backs and two events made and destroyed 28 us; the finish
     // kernel and kept events 22; the kernels' own start time and polling 8.5.
     const ControlSlot s = dev.acquire_slot();
     unsigned long long* const ticks = s.host_best + 1;
     __atomic_store_n(ticks, kPending, __ATOMIC_RELEASE);
-    if (!stamped) FES_HIP(hipEventRecord(s.e0, stream));
     launch(s);
-    if (!stamped) FES_HIP(hipEventRecord(s.e1, stream));
     FES_HIP(g_finish(s.claims(), kClaimBytes / 8, s.best(), 1, s.host_best, stream));
-    double ms = wait_finished(ticks, stream);
-    if (!stamped) {
-        float t = 0;
-        FES_HIP(hipEventElapsedTime(&t, s.e0, s.e1));
-        ms = t;
-    }
+    const double ms = wait_finished(ticks, stream);
     if (kernel_ms) *kernel_ms = ms;
     const uint64_t best = *s.host_best;
     dev.release_slot(s);

@@ -241,9 +241,9 @@ struct DevMem {
 void check_dev_mem(const DevMem& m, size_t need);
 
 // Runs one check's kernel on a control slot and returns the lowest failing pattern: no copies, one
-// wait.  `stamped`: the kernel notes its start (kStartWord); else events take the time.
+// wait.  The kernel notes its start (kStartWord).
 uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
-                     const std::function<void(const ControlSlot&)>& launch, bool stamped = true);
+                     const std::function<void(const ControlSlot&)>& launch);
 // Waits for the finish kernel that puts its ticks there (kPending before); the launch's ms.
 double wait_finished(unsigned long long* ticks, hipStream_t stream);
 
@@ -382,9 +382,13 @@ void native_many_enqueue(const NativeMany& m, hipStream_t stream);
 struct NativeTier {
     // The circuit's kernel for checks that cover `span` half-words at a time of its space, if one is
     // built (get: build it if not; null when the circuit's values fit neither registers nor LDS).
-    // `weight`: what a millisecond of building costs against one of kernel time.
+    // `weight`: what a millisecond of building costs against one of kernel time.  `stop`: set by another
+    // thread to give the building up (null then, too).
     std::shared_ptr<JitKernel> (*ready)(Circuit& c, uint64_t span);
-    std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight);
+    std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop);
+    // The built kernel that is expected to be fastest over `r`, whichever spans it was built for (*ms: its
+    // time there, *fits: whether get() would return it); null when none is built.
+    std::shared_ptr<JitKernel> (*best)(Circuit& c, const HwRange& r, double* ms, bool* fits);
     // Expected kernel time over `patterns` patterns, and of get() for a circuit without one (the
     // module load on the first launch not included).
     double (*run_ms)(const JitKernel& k, double patterns);

@@ -182,7 +182,7 @@ void fastlec_es_server::compile_loop() {
         std::vector<std::shared_ptr<JitKernel>> ks;
         try {
             if (const NativeTier* t = native_tier())
-                for (Circuit* c : cs) ks.push_back(t->get(*c, slice_span(*c), kServerBuildWeight));
+                for (Circuit* c : cs) ks.push_back(t->get(*c, slice_span(*c), kServerBuildWeight, nullptr));
             else ks.assign(cs.size(), nullptr);
             // what has no native kernel is compiled
             std::vector<Circuit*> rest;
