@@ -82,7 +82,7 @@ constexpr double kCompileMargin = 1.2;
 // What a millisecond of building a single check's native kernel costs against one of its run.
 constexpr double kCheckBuildWeight = 0.5;
 // Planning a cone's interpreter stream, per AND gate, and loading a module of native kernels.
-constexpr double kPlanMsPerGate = 0.5e-3, kLoadMs = 1.2;
+constexpr double kPlanMsPerGate = 0.15e-3, kLoadMs = 1.2;
 
 // Specialized kernels in batches under AUTO (FASTLEC_ES_BATCH_JIT): 0 never, 1 by the runtime
 // model (default), 2 every cone whose kernel already exists (a test hook).

@@ -88,6 +88,8 @@ bool server_occupancy() {
     return !(v && std::atoi(v) == 0);
 }
 constexpr uint32_t kCapacity = 1024;
+// Planning a cone's interpreter stream, per AND gate, and a kernel launch beside others.
+constexpr double kPlanMsPerGate = 0.15e-3, kLaunchMs = 0.006;
 
 }  // namespace
 
@@ -109,9 +111,11 @@ struct fastlec_es_server {
     std::string fatal;
     int fatal_code = 0;
 
-    // device job table: [ctl lds][ctl hbm][best x capacity][desc lds x capacity][desc hbm x capacity]
+    // device job table: [ctl lds][ctl hbm][ctl specialized x capacity][best x capacity][ticks]
+    // [desc lds x capacity][desc hbm x capacity].  Between steps every control word is zero and every best
+    // all ones: each step ends with the finish kernel (in host-only builds with copies).
     Buffer table;
-    size_t off_best = 2 * sizeof(LaunchCtl), off_desc_lds = 0, off_desc_hbm = 0;
+    size_t off_ctl_jit = 2 * sizeof(LaunchCtl), off_best = 0, off_desc_lds = 0, off_desc_hbm = 0;
     Buffer files;  // value files of the device-memory tier
     std::vector<uint32_t> free_slots;
     double rate = 1e14;  // node*patterns per second, running estimate
@@ -119,7 +123,6 @@ struct fastlec_es_server {
     // specialized tier
     int jit_mode = 1;        // 0 off, 1 by estimate, 2 every job (test hook)
     double jit_rate = 2e15;  // node*patterns per second of the specialized kernel, estimate
-    size_t off_ctl_jit = 0;  // per-slot claim counters of specialized launches
     std::deque<Job*> compile_queue;
     std::condition_variable cv_compile;
     std::vector<std::thread> compilers;
@@ -233,7 +236,12 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
         const NativeTier* nt = native_tier();
         if (nt)
             if (auto k = nt->ready(*j->c, slice_span(*j->c))) {
-                j->jit = k;
+                // Its launch is its own, while the jobs on the interpreter share one: 28 jobs of 16 to 20
+                // inputs took 175 us of a step as launches of native kernels, 95 together.
+                const double alone = model_interp_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
+                const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
+                const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
+                if (nt->run_ms(*k, left) + kLaunchMs < plan + std::max(share, alone / (double)act.size())) j->jit = k;
                 continue;
             }
         if (auto k = jit_ready(*j->c, specialized_waves_per_eu())) {
@@ -244,7 +252,7 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
         // running on the interpreter.
         if (nt && jit_mode == 1) {
             const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
-            const double plan = j->c->planned(4) ? 0.0 : 0.5e-3 * j->c->plan1.num_ands_tfi;
+            const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
             if (native_pays(*j->c, plan + share * (double)std::max<size_t>(1, sharing), left)) {
                 j->compile_queued = true;
                 compile_queue.push_back(j);
@@ -340,7 +348,7 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
     }
     uint8_t* host = (uint8_t*)table.host;
     uint8_t* devp = (uint8_t*)table.dev;
-    std::memset(host, 0, 2 * sizeof(LaunchCtl));
+    const FinishLaunch finish_kernel = finish_launch();
     struct Group {
         std::vector<Circuit*>* c;
         std::vector<HwRange>* r;
@@ -407,14 +415,20 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
             }
         }
     }
-    // Upload the control words and this step's descriptors (best[] stays on the device).
-    FES_HIP(hipMemcpyAsync(devp, host, 2 * sizeof(LaunchCtl), hipMemcpyHostToDevice, stream));
+    // Upload this step's descriptors (best[] stays on the device), without a finish kernel also the control words.
+    const size_t ctl_bytes = off_ctl_jit + kClaimBytes * jit_jobs.size();
+    if (!finish_kernel) {
+        std::memset(host, 0, ctl_bytes);
+        FES_HIP(hipMemcpyAsync(devp, host, ctl_bytes, hipMemcpyHostToDevice, stream));
+    }
     for (Group& g : groups)
         if (!g.c->empty())
             FES_HIP(hipMemcpyAsync(devp + g.desc_off, host + g.desc_off, sizeof(ConeDesc) * g.c->size(),
                                    hipMemcpyHostToDevice, stream));
-    ScopedEvent e0, e1, e2;
-    FES_HIP(hipEventRecord(e0.e, stream));
+    // The finish kernel times a step of one kind; events tell the kinds of a mixed one apart.
+    const bool events = !finish_kernel || (n_interp && !jit_jobs.empty());
+    std::vector<ScopedEvent> ev(events ? 3 : 0);
+    if (events) FES_HIP(hipEventRecord(ev[0].e, stream));
     for (Group& g : groups) {
         if (g.c->empty()) continue;
         InterpLaunch L;
@@ -428,26 +442,35 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
         L.cancel = nullptr;
         FES_HIP(launch_schedule(L, g.sch, stream));
     }
-    FES_HIP(hipEventRecord(e1.e, stream));
-    // Specialized slices: own claim counter per slot (zeroed first), shared best[] entry.
+    if (events) FES_HIP(hipEventRecord(ev[1].e, stream));
+    // Specialized slices: claim counters of their own, the job's best[] entry.
     double jit_np = 0;
     if (!jit_jobs.empty()) {
-        for (size_t t : jit_jobs) {
+        for (size_t i = 0; i < jit_jobs.size(); ++i) {
+            const size_t t = jit_jobs[i], off = off_ctl_jit + kClaimBytes * i;
             Job* j = act[t];
-            const size_t off = off_ctl_jit + kClaimBytes * j->slot;
-            std::memset(host + off, 0, kClaimBytes);
-            FES_HIP(hipMemcpyAsync(devp + off, host + off, kClaimBytes, hipMemcpyHostToDevice, stream));
             const JitLaunchPlan lp = jit_prepare(*dev, *jk[t], windows[t], 0);
             jit_enqueue(lp, (uint64_t*)(devp + off), (uint64_t*)(devp + off_best + 8ull * j->slot), nullptr, stream);
             jit_np += 32.0 * std::max<uint32_t>(1, j->c->plan1.num_gate_instrs) * (double)(windows[t].end - windows[t].begin);
         }
-        FES_HIP(hipEventRecord(e2.e, stream));
+        if (events) FES_HIP(hipEventRecord(ev[2].e, stream));
     }
-    FES_HIP(hipMemcpyAsync(host + off_best, devp + off_best, 8ull * kCapacity, hipMemcpyDeviceToHost, stream));
-    FES_HIP(hipStreamSynchronize(stream));
     float ms = 0, jit_ms = 0;
-    FES_HIP(hipEventElapsedTime(&ms, e0.e, e1.e));
-    if (!jit_jobs.empty()) FES_HIP(hipEventElapsedTime(&jit_ms, e1.e, e2.e));
+    if (finish_kernel) {
+        uint32_t n = 0;
+        for (Job* j : act) n = std::max(n, j->slot + 1);
+        unsigned long long* const found = (unsigned long long*)(host + off_best);
+        __atomic_store_n(found + n, kPending, __ATOMIC_RELEASE);
+        FES_HIP(finish_kernel((unsigned long long*)devp, (uint32_t)(ctl_bytes / 8), (unsigned long long*)(devp + off_best),
+                              n, found, stream));
+        (n_interp ? ms : jit_ms) = (float)wait_finished(found + n, stream);
+        if (events) FES_HIP(hipStreamSynchronize(stream));
+    } else {
+        FES_HIP(hipMemcpyAsync(host + off_best, devp + off_best, 8ull * kCapacity, hipMemcpyDeviceToHost, stream));
+        FES_HIP(hipStreamSynchronize(stream));
+    }
+    if (events) FES_HIP(hipEventElapsedTime(&ms, ev[0].e, ev[1].e));
+    if (events && !jit_jobs.empty()) FES_HIP(hipEventElapsedTime(&jit_ms, ev[1].e, ev[2].e));
     if (n_interp && ms > 0.5f) rate = 0.7 * rate + 0.3 * (step_np / (ms / 1e3));
     if (jit_np > 0 && jit_ms > 0.5f) jit_rate = 0.7 * jit_rate + 0.3 * (jit_np / (jit_ms / 1e3));
 
@@ -484,6 +507,12 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
 void fastlec_es_server::loop() {
     try {
         FES_HIP(hipSetDevice(dev->ordinal));
+        if (finish_launch()) {  // the table as every step leaves it
+            std::memset(table.host, 0, off_best);
+            std::memset((uint8_t*)table.host + off_best, 0xFF, off_desc_lds - off_best);
+            FES_HIP(hipMemcpyAsync(table.dev, table.host, off_desc_lds, hipMemcpyHostToDevice, stream));
+            FES_HIP(hipStreamSynchronize(stream));
+        }
         for (;;) {
             std::vector<Job*> act;
             std::vector<uint32_t> fresh;
@@ -527,8 +556,9 @@ void fastlec_es_server::loop() {
                 if (stop) return;
                 act = active;
             }
-            // Reset the best value of newly assigned slots on the device.
+            // Without a finish kernel: reset the best value of newly assigned slots on the device.
             uint64_t* hb = (uint64_t*)((uint8_t*)table.host + off_best);
+            if (finish_launch()) fresh.clear();
             for (uint32_t s : fresh) {
                 hb[s] = ~0ull;
                 FES_HIP(hipMemcpyAsync((uint8_t*)table.dev + off_best + 8ull * s, &hb[s], 8, hipMemcpyHostToDevice, stream));
@@ -598,10 +628,10 @@ int fastlec_es_server_create(const fastlec_es_options* opts, size_t budget_bytes
         s->dev = &device(s->opts.device);
         s->stream = s->opts.hip_stream ? (hipStream_t)s->opts.hip_stream : s->dev->stream;
         s->jit_mode = (int)std::min<uint64_t>(2, env_u64("FASTLEC_ES_SERVER_JIT", 1));
-        s->off_desc_lds = (s->off_best + 8ull * kCapacity + 255) & ~size_t(255);
+        s->off_best = s->off_ctl_jit + kClaimBytes * kCapacity;
+        s->off_desc_lds = (s->off_best + 8ull * (kCapacity + 1) + 255) & ~size_t(255);
         s->off_desc_hbm = s->off_desc_lds + sizeof(ConeDesc) * kCapacity;
-        s->off_ctl_jit = (s->off_desc_hbm + sizeof(ConeDesc) * kCapacity + 255) & ~size_t(255);
-        s->table = s->dev->acquire(s->off_ctl_jit + kClaimBytes * kCapacity);
+        s->table = s->dev->acquire(s->off_desc_hbm + sizeof(ConeDesc) * kCapacity);
         if (s->table.bytes >= budget_bytes) {
             s->dev->release(s->table);
             return FASTLEC_ERR_INVALID;  // the budget must exceed the job table
