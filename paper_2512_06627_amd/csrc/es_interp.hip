@@ -227,7 +227,8 @@ __global__ void __launch_bounds__(1024) es_interp_kernel(InterpLaunch L) {
                 if (bal) p = 32ull * (base + (uint64_t)(j * 64) + l) + (uint32_t)__builtin_ctz(ml);
             }
             if (p != ~0ull) {
-                atomicMin(best, (unsigned long long)p);
+                if (p < uniform64(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                    atomicMin(best, (unsigned long long)p);
                 break;
             }
         }
@@ -534,7 +535,11 @@ es_interp_regs_kernel(InterpLaunch L) {
             if (bal) {
                 const uint32_t l = (uint32_t)__builtin_ctzll(bal);
                 const uint32_t ml = __builtin_amdgcn_readlane(mj, l);
-                atomicMin(best, 32ull * (base + l) + (uint32_t)__builtin_ctz(ml));
+                // Where most patterns fail every wave comes here in its first pass, and an atomic on one
+                // address takes 25 ns: those that come after a lower pattern leave it out.
+                const uint64_t p = 32ull * (base + l) + (uint32_t)__builtin_ctz(ml);
+                if (p < uniform64(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                    atomicMin(best, (unsigned long long)p);
                 break;
             }
         }

@@ -285,7 +285,8 @@ std::string jit_source(const LutProgram& lp, int waves_per_eu, int block, int* w
          "        if (bal) {\n"
          "          const u32 l = (u32)__builtin_ctzll(bal);\n"
          "          const u32 ml = __builtin_amdgcn_readlane(m0, l);\n"
-         "          atomicMin(best, 32ull * (base + l) + (u32)__builtin_ctz(ml));\n"
+         "          const u64 p = 32ull * (base + l) + (u32)__builtin_ctz(ml);\n"
+         "          if (p < __hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(best, p);\n"
          "          break;\n"
          "        }\n"
          "      }\n";

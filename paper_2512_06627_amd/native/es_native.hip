@@ -146,7 +146,10 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
                 const uint64_t low = (1ull << at) - 1u;
                 real = ((real & ~low) << 1) | (real & low);
             }
-            if (32u * real >= limit) break;  // nothing at or above here can lower best
+            if (32u * real >= limit) {  // nothing at or above here can lower best
+                more = more && (L.num_cones > 1 || base > u0);
+                break;
+            }
             uint64_t found = ~0ull;
             if constexpr (R == 128)
                 asm volatile("s_swappc_b64 s[36:37], s[50:51]" PASS_OPERANDS
@@ -161,7 +164,10 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
                 // Later passes of the item may still hold a lower failing pattern (another inner
                 // assignment): they stop at the bound above.
                 if (found < limit) limit = found;
-                atomicMin(best, (unsigned long long)found);
+                // Where most patterns fail every wave comes here in its first pass, and an atomic
+                // on one address takes 25 ns: those that come after a lower pattern leave it out.
+                const uint64_t now = uniform64(__hip_atomic_load(best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                if (found < now) atomicMin(best, (unsigned long long)found);
             }
         }
     }
