@@ -624,6 +624,32 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             }
             groups[3 + b].push_back(i);
         }
+        // The launches run one after the other, so a tier with few passes, all of them at once, joins the
+        // next one where its chain of gates costs more than the waves that the larger files take away
+        // (511 small cones of up to 104 rows and one of more: 124 us as two launches, 108 as one; 72 and 5
+        // cones of 15 to 18 inputs 121 and 70).
+        auto launch_ms = [&](const std::vector<size_t>& a, const std::vector<size_t>& b, uint32_t rows) {
+            double chain = 0, work = 0;
+            for (const std::vector<size_t>* g : {&a, &b})
+                for (size_t i : *g) {
+                    const double patterns = 32.0 * (double)(rs[i].end - rs[i].begin);
+                    chain = std::max(chain, model_interp_ms(v[i]->interp_gates(), rows, 0.0));
+                    work += model_interp_share_ms(v[i]->interp_gates(), rows, patterns);
+                }
+            return std::max(chain, work);
+        };
+        const uint32_t tier_rows[3] = {104, 144, 232};
+        for (uint32_t t = 0; t < 2; ++t) {
+            auto from = groups.find(t), to = groups.upper_bound(t);
+            if (from == groups.end() || to == groups.end() || to->first > 2) continue;
+            const std::vector<size_t> none;
+            const uint32_t large = tier_rows[to->first];
+            if (launch_ms(from->second, to->second, large) >
+                launch_ms(from->second, none, tier_rows[t]) + launch_ms(to->second, none, large))
+                continue;
+            to->second.insert(to->second.end(), from->second.begin(), from->second.end());
+            groups.erase(from);
+        }
         std::vector<BatchPart> parts;
         for (auto& gi : groups) {
             BatchPart p;

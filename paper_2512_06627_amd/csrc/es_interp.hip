@@ -490,15 +490,16 @@ __device__ __forceinline__ uint32_t regs_pass(const Instr* prog, uint32_t nb, ui
     return m;
 }
 
-// One wave per workgroup; waves_per_eu pins the occupancy the file size allows.
+// waves_per_eu pins the occupancy the file size allows.
 template <int R, int kWaves>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves, kWaves)))
+__global__ void __launch_bounds__(256 * kWaves) __attribute__((amdgpu_waves_per_eu(kWaves, kWaves)))
 es_interp_regs_kernel(InterpLaunch L) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t x5 = 0u - (lane & 1u), x6 = 0u - ((lane >> 1) & 1u), x7 = 0u - ((lane >> 2) & 1u);
     const uint32_t x8 = 0u - ((lane >> 3) & 1u), x9 = 0u - ((lane >> 4) & 1u), x10 = 0u - ((lane >> 5) & 1u);
-    const uint32_t wave_gid = blockIdx.x;
-    const uint32_t waves = gridDim.x;
+    const uint32_t group = blockDim.x >> 6;
+    const uint32_t wave_gid = __builtin_amdgcn_readfirstlane(blockIdx.x * group + (threadIdx.x >> 6));
+    const uint32_t waves = gridDim.x * group;
     const uint32_t nclaim = waves < kClaimCounters ? waves : kClaimCounters;
     const uint32_t claim = __builtin_amdgcn_readfirstlane(wave_gid % nclaim);
     unsigned long long* const counter = &L.ctl->next_item[claim * kClaimStride];
@@ -548,7 +549,14 @@ es_interp_regs_kernel(InterpLaunch L) {
 
 template <int R, int kWaves>
 hipError_t launch_regs(const InterpLaunch& L, int grid, hipStream_t stream) {
-    hipLaunchKernelGGL((es_interp_regs_kernel<R, kWaves>), dim3(grid), dim3(64), 0, stream, L);
+    // The scalar cache that two CUs share keeps up with one cone's stream, not with a different one for
+    // every wave: waves of a workgroup take adjacent items, mostly of one cone.  512 cones of 8 to 16
+    // inputs at three waves per SIMD: 138 us alone, 137 in fours, 108 in eights (at four waves 193, 151
+    // and 91); 179 cones of a sweep 5.72, 5.71 and 5.66 ms; 77 cones of 15 to 18 inputs the other way
+    // 70, 69 and 76 us.  A launch of one cone reads one stream.
+    const int group = L.num_cones > 1 ? 8 : 1;
+    hipLaunchKernelGGL((es_interp_regs_kernel<R, kWaves>), dim3((grid + group - 1) / group), dim3(64 * group), 0, stream,
+                       L);
     return hipGetLastError();
 }
 
