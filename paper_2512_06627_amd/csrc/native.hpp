@@ -53,6 +53,11 @@ struct NativeCode {
 // False when the pass needs more than that.
 bool emit_native(const LutProgram& lp, const std::vector<uint64_t>& offset, int vgprs, int lds_slots, NativeCode& out);
 
+// A simulation pass (native_sim.cpp, sim_body in native/es_native.hip): every variable's word, in order,
+// to its row of the signature matrix.  vgprs: registers from v16 up.  False when the values alive at
+// once need more.
+bool emit_sim(const Aig& g, int vgprs, NativeCode& out);
+
 // A circuit's pass, ready to run.  Immutable once built.
 struct NativeKernel {
     NativeCode code;

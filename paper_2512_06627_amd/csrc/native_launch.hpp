@@ -43,4 +43,14 @@ struct NativeLaunch {
     NativeDesc one;
 };
 
+// A native simulation pass (native_sim.cpp): columns [0, words) of the caller's input words, in items of
+// one column per thread of a workgroup.
+struct SimLaunch {
+    uint64_t code_offset;
+    const uint32_t* pi;
+    uint32_t* sig;
+    uint64_t words;  // below 2^30
+    uint64_t items;
+};
+
 }  // namespace fes

@@ -47,6 +47,7 @@ namespace {
 const NativeTier* g_native_tier = nullptr;
 FinishLaunch g_finish = nullptr;
 BatchRunner g_batch_runner = nullptr;
+SimRunner g_sim_runner = nullptr;
 }  // namespace
 
 void register_finish(FinishLaunch f) { g_finish = f; }
@@ -54,6 +55,7 @@ FinishLaunch finish_launch() { return g_finish; }
 void register_batch_runner(BatchRunner r) { g_batch_runner = r; }
 BatchRunner batch_runner() { return g_batch_runner; }
 
+void register_sim_runner(SimRunner r) { g_sim_runner = r; }
 void register_native_tier(const NativeTier* t) { g_native_tier = t; }
 
 const NativeTier* native_tier() {
@@ -782,6 +784,9 @@ bool run_sim_regs(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, u
                   const fastlec_es_options* o, hipStream_t stream, double* kernel_ms) {
     if (!regs_tier_enabled() || words >= (1ull << 30)) return false;
     if (o && (o->kernel == FASTLEC_KERNEL_INTERP_HBM || o->words_per_thread || o->wg_size)) return false;
+    if ((!o || o->kernel != FASTLEC_KERNEL_INTERP) && native_tier() && g_sim_runner &&
+        g_sim_runner(dev, c, pi, words, sig, stream, kernel_ms))
+        return true;
     const Plan& p = c.sim_plan(1);
     int waves_per_simd = 0;
     const int regs = interp_regs_rows(p.rows, &waves_per_simd);

@@ -57,6 +57,7 @@ struct CodeObject {
 };
 
 struct NativeKernel;  // native.hpp
+struct NativeSim;     // native_sim.cpp
 
 struct JitKernel {
     std::shared_ptr<const NativeKernel> native;  // machine code of the native tier, else null
@@ -114,6 +115,9 @@ struct Circuit {
         std::shared_ptr<void> block;  // device memory that holds it, with other circuits' streams perhaps
     };
     std::map<int, DevStream> dev_regs;
+    // Native simulation pass, and what the interpreter's simulations have taken (see native_sim.cpp).
+    std::shared_ptr<NativeSim> native_sim;
+    std::atomic<double> sim_ms_spent{0};
     // Simulation stream of the register tier (encode_sim_stream) and its gate records.
     const uint32_t* device_sim_stream(int device, hipStream_t s, uint32_t* gates);
     std::map<int, uint32_t*> dev_sim_stream;
@@ -399,6 +403,11 @@ struct NativeTier {
 };
 const NativeTier* native_tier();  // null: not linked, or off (FASTLEC_ES_NATIVE=0)
 void register_native_tier(const NativeTier* t);
+// Runs a simulation on the circuit's native pass if there is one or one pays, else returns false;
+// null in host-only builds.
+using SimRunner = bool (*)(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32_t* sig,
+                           hipStream_t stream, double* kernel_ms);
+void register_sim_runner(SimRunner r);
 // Whether a native kernel pays for a circuit that has none: the interpreter's time for this check
 // plus what the interpreter has already taken for this circuit exceeds the native kernel's time
 // and its building.  A circuit checked again and again thus spends at most about twice the better

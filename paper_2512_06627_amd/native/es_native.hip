@@ -41,6 +41,9 @@ using fes::kClaimStride;
 using fes::kStartWord;
 using fes::NativeDesc;
 using fes::NativeLaunch;
+using fes::SimLaunch;
+
+constexpr uint32_t kXcds = 8;  // workgroup b runs on XCD b % 8
 
 #define FES_CONST __attribute__((address_space(4)))
 
@@ -173,6 +176,37 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
     }
 }
 
+// Simulation: the generated code loads the input words of the wave's 64 columns, stores row 0 and the
+// input rows, then evaluates and stores gate by gate, rows ascending.  It has the registers from v15 up,
+// the lane's byte offset in a row in v2, the addresses of the first input row and of row 0 in s[38:39]
+// and s[40:41] (which it moves), the bytes of a row in s42 and the lanes that have a column in s[44:45].
+// Adjacent workgroups share an XCD, and the code holds barriers that every wave of a workgroup reaches,
+// so that the parts of cache lines at the ends of a ragged row's stores meet in L2.
+template <int R>
+__device__ __forceinline__ void sim_body(const SimLaunch& L) {
+    const uint64_t code = uniform64(code_base()) + L.code_offset;
+    const uint32_t xcds = min(gridDim.x, kXcds), xcd = blockIdx.x % xcds;
+    const uint64_t share = L.items / xcds, odd = L.items % xcds;
+    const uint64_t first = xcd * share + min((uint64_t)xcd, odd), stop = first + share + (xcd < odd ? 1u : 0u);
+    const uint32_t step = (gridDim.x - xcd + xcds - 1u) / xcds;
+    for (uint64_t item = first + blockIdx.x / xcds; item < stop; item += step) {
+        const uint64_t w = item * blockDim.x + threadIdx.x;
+        const uint64_t lanes = __ballot(w < L.words);
+        const uint32_t off = (uint32_t)(w * 4u), row_bytes = (uint32_t)(L.words * 4u);
+        uint64_t in = (uint64_t)L.pi, out = (uint64_t)L.sig;
+#define SIM_OPERANDS                                                                              \
+    : "+{s[38:39]}"(in), "+{s[40:41]}"(out)                                                       \
+    : "{s42}"(row_bytes), "{s[44:45]}"(lanes), "{s[50:51]}"(code), "{v2}"(off)
+        if constexpr (R == 128)
+            asm volatile("s_swappc_b64 s[36:37], s[50:51]" SIM_OPERANDS : SCLOB, "vcc", "scc", "memory", VCLOB_128);
+        else if constexpr (R == 168)
+            asm volatile("s_swappc_b64 s[36:37], s[50:51]" SIM_OPERANDS : SCLOB, "vcc", "scc", "memory", VCLOB_168);
+        else
+            asm volatile("s_swappc_b64 s[36:37], s[50:51]" SIM_OPERANDS : SCLOB, "vcc", "scc", "memory", VCLOB_256);
+#undef SIM_OPERANDS
+    }
+}
+
 }  // namespace
 
 // 128 registers per lane: four waves per SIMD; 168: three; 256: two.  The pass has those from v16 up.
@@ -187,6 +221,19 @@ fes_native_168(NativeLaunch L) {
 extern "C" __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 fes_native_256(NativeLaunch L) {
     native_body<256>(L);
+}
+
+extern "C" __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
+fes_sim_128(SimLaunch L) {
+    sim_body<128>(L);
+}
+extern "C" __global__ void __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3)))
+fes_sim_168(SimLaunch L) {
+    sim_body<168>(L);
+}
+extern "C" __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+fes_sim_256(SimLaunch L) {
+    sim_body<256>(L);
 }
 
 // Never launched: it holds the report routine and the place holder of the generated code.
