@@ -921,9 +921,16 @@ int fastlec_es_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t num_w
         fastlec_es_options o = opts ? *opts : defaults();
         Device& dev = device(o.device);
         hipStream_t stream = o.hip_stream ? (hipStream_t)o.hip_stream : dev.stream;
-        run_timed(dev, stream, kernel_ms, [&] {
-            FES_HIP(launch_signature_hash(sig, rows, num_words, hash, ones, dev.prop.multiProcessorCount, stream));
-        });
+        const int cus = dev.prop.multiProcessorCount;
+        if (const HashLaunch launch = hash_launch()) {
+            run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& slot) {
+                FES_HIP(launch(sig, rows, num_words, hash, ones, cus, slot.claims() + kStartWord, stream));
+            });
+        } else {  // host-only builds
+            FES_HIP(launch_signature_hash(sig, rows, num_words, hash, ones, cus, stream));
+            FES_HIP(hipStreamSynchronize(stream));
+            if (kernel_ms) *kernel_ms = 0;
+        }
         return FASTLEC_OK;
     });
 }

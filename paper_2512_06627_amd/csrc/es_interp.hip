@@ -760,6 +760,7 @@ es_sim_regs_kernel(InterpLaunch L) {
     const uint32_t* prog = (const uint32_t*)c->prog;
     const uint64_t W = L.sim_words;
     const uint64_t sig = (uint64_t)L.sim_sig;
+    if (blockIdx.x == 0 && threadIdx.x == 0) L.ctl->next_item[kStartWord] = __builtin_amdgcn_s_memrealtime();
     const uint32_t xcds = min(gridDim.x, kXcds), xcd = blockIdx.x % xcds;
     const uint64_t share = L.total_items / xcds, odd = L.total_items % xcds;
     const uint64_t first = xcd * share + min((uint64_t)xcd, odd), stop = first + share + (xcd < odd ? 1u : 0u);
@@ -793,8 +794,10 @@ __global__ void __launch_bounds__(1024) finish_kernel(unsigned long long* __rest
         best[i] = ~0ull;
     }
     for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) claims[i] = 0ull;
-    __threadfence_system();
-    __syncthreads();
+    if (blockDim.x > 64u) {  // one wave's own stores are covered by its release
+        __threadfence_system();
+        __syncthreads();
+    }
     if (threadIdx.x == 0)
         __hip_atomic_store(host_best + n, now - start, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -831,7 +834,7 @@ hipError_t launch_interp_regs(const InterpLaunch& L, int regs, int grid, hipStre
 }
 
 hipError_t launch_sim_regs(const InterpLaunch& L, int regs, int grid, hipStream_t stream) {
-    if (L.num_cones != 1 || !L.sim_sig || grid <= 0 || L.rows_max > (uint32_t)regs) return hipErrorInvalidValue;
+    if (L.num_cones != 1 || !L.sim_sig || !L.ctl || grid <= 0 || L.rows_max > (uint32_t)regs) return hipErrorInvalidValue;
     if (L.sim_words == 0 || L.sim_words >= (1ull << 30)) return hipErrorInvalidValue;  // 32-bit byte offsets
     switch (regs) {
         case 104: return launch_sim_regs_t<104, 4>(L, grid, stream);

@@ -106,6 +106,13 @@ constexpr unsigned long long kPending = ~0ull;
 hipError_t launch_finish(unsigned long long* claims, uint32_t words, unsigned long long* best, uint32_t n,
                          unsigned long long* host_best, hipStream_t stream);
 
+// launch_signature_hash that notes its start at `start` (not null) for the finish kernel.
+hipError_t launch_signature_hash_from(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
+                                      uint64_t* ones, int cus, unsigned long long* start, hipStream_t stream);
+using HashLaunch = decltype(&launch_signature_hash_from);
+void register_hash(HashLaunch f);
+HashLaunch hash_launch();  // null in host-only builds
+
 using FinishLaunch = decltype(&launch_finish);
 // The library's launch_finish; null in host-only builds of the runtime, which then upload and read
 // back the control block around every call.

@@ -51,6 +51,7 @@ struct SimLaunch {
     uint32_t* sig;
     uint64_t words;  // below 2^30
     uint64_t items;
+    unsigned long long* counters;  // claim block, for kStartWord only
 };
 
 }  // namespace fes

@@ -94,7 +94,8 @@ bool run(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32_t* 
     const uint64_t grid = (L.items + rounds - 1) / rounds;
     trace("native simulation: %llu words, grid=%llu of %llu waves, %llu rounds", (unsigned long long)words,
           (unsigned long long)grid, (unsigned long long)waves, (unsigned long long)rounds);
-    run_timed(dev, stream, kernel_ms, [&] {
+    run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& s) {
+        L.counters = s.claims();
         void* args[] = {&L};
         FES_HIP(hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, (unsigned)(64 * waves), 1, 1, 0, stream, args, nullptr));
     });

@@ -71,7 +71,9 @@ template <int R>
 __global__ void __launch_bounds__(64 * kMaxSplit) signature_hash_kernel(const uint32_t* __restrict__ sig,
                                                                         uint64_t rows, uint64_t W,
                                                                         uint64_t* __restrict__ hash,
-                                                                        uint64_t* __restrict__ ones) {
+                                                                        uint64_t* __restrict__ ones,
+                                                                        unsigned long long* __restrict__ start) {
+    if (start && blockIdx.x == 0 && threadIdx.x == 0) *start = __builtin_amdgcn_s_memrealtime();
     constexpr int N = 2 * R;  // sums of a wave: of w * key for each row, of ones for each row
     __shared__ uint64_t part[kMaxSplit][N + 1];
     const uint32_t lane = threadIdx.x & 63u;
@@ -153,17 +155,26 @@ __global__ void __launch_bounds__(64 * kMaxSplit) signature_hash_kernel(const ui
 // against 6.8, and long ones gain nothing).  Then about 16 waves a CU (with a chunk in hand and one
 // on the way that is 64 KB per CU in flight), shared out so that a group's waves end together; 3,055 x
 // 12,511: 29 us, with 32 waves 34.
-hipError_t launch_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
-                                 uint64_t* ones, int cus, hipStream_t stream) {
+hipError_t launch_signature_hash_from(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
+                                      uint64_t* ones, int cus, unsigned long long* start, hipStream_t stream) {
     if (!sig || !hash || !ones || rows == 0 || words == 0 || cus <= 0) return hipErrorInvalidValue;
     const uint64_t per = rows >= 2ull * cus ? 2 : 1;
     const uint64_t groups = (rows + per - 1) / per, chunks = (words + 255) / 256;
     const uint64_t most = std::clamp<uint64_t>(16ull * cus / groups, 1, kMaxSplit);
     const uint64_t turns = (chunks + most - 1) / most, split = (chunks + turns - 1) / turns;
     const dim3 grid((uint32_t)std::min<uint64_t>(groups, 1u << 20)), block((uint32_t)(64 * split));
-    if (per == 2) hipLaunchKernelGGL(signature_hash_kernel<2>, grid, block, 0, stream, sig, rows, words, hash, ones);
-    else hipLaunchKernelGGL(signature_hash_kernel<1>, grid, block, 0, stream, sig, rows, words, hash, ones);
+    if (per == 2) hipLaunchKernelGGL(signature_hash_kernel<2>, grid, block, 0, stream, sig, rows, words, hash, ones, start);
+    else hipLaunchKernelGGL(signature_hash_kernel<1>, grid, block, 0, stream, sig, rows, words, hash, ones, start);
     return hipGetLastError();
+}
+
+hipError_t launch_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash, uint64_t* ones,
+                                 int cus, hipStream_t stream) {
+    return launch_signature_hash_from(sig, rows, words, hash, ones, cus, nullptr, stream);
+}
+
+namespace {
+const bool g_registered = (register_hash(&launch_signature_hash_from), true);
 }
 
 }  // namespace fes

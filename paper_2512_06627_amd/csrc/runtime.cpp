@@ -47,11 +47,14 @@ namespace {
 const NativeTier* g_native_tier = nullptr;
 FinishLaunch g_finish = nullptr;
 BatchRunner g_batch_runner = nullptr;
+HashLaunch g_hash = nullptr;
 SimRunner g_sim_runner = nullptr;
 }  // namespace
 
 void register_finish(FinishLaunch f) { g_finish = f; }
 FinishLaunch finish_launch() { return g_finish; }
+void register_hash(HashLaunch f) { g_hash = f; }
+HashLaunch hash_launch() { return g_hash; }
 void register_batch_runner(BatchRunner r) { g_batch_runner = r; }
 BatchRunner batch_runner() { return g_batch_runner; }
 
@@ -365,8 +368,6 @@ ControlSlot Device::acquire_slot() {
     FES_HIP(hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream));
     FES_HIP(hipStreamSynchronize(stream));
     s.host_best = (unsigned long long*)b.host;
-    FES_HIP(hipEventCreate(&s.e0));
-    FES_HIP(hipEventCreate(&s.e1));
     return s;
 }
 
@@ -392,7 +393,9 @@ double wait_finished(unsigned long long* ticks, hipStream_t stream) {
 uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
                      const std::function<void(const ControlSlot&)>& launch) {
     // Around an empty kernel: uploads, read-backs and two events made and destroyed 28 us; the finish
-    // kernel and kept events 22; the kernels' own start time and polling 8.5.
+    // kernel and kept events 22; the kernels' own start time and polling 8.5 (waiting for
+    // the stream 13.5).  What earlier kernels of the call wrote is visible with that store: the finish
+    // kernel comes after them on the stream, and its release is at system scope.
     const ControlSlot s = dev.acquire_slot();
     unsigned long long* const ticks = s.host_best + 1;
     __atomic_store_n(ticks, kPending, __ATOMIC_RELEASE);
@@ -403,18 +406,6 @@ uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
     const uint64_t best = *s.host_best;
     dev.release_slot(s);
     return best;
-}
-
-void run_timed(Device& dev, hipStream_t stream, double* kernel_ms, const std::function<void()>& launch) {
-    const ControlSlot s = dev.acquire_slot();
-    FES_HIP(hipEventRecord(s.e0, stream));
-    launch();
-    FES_HIP(hipEventRecord(s.e1, stream));
-    FES_HIP(hipStreamSynchronize(stream));
-    float ms = 0;
-    FES_HIP(hipEventElapsedTime(&ms, s.e0, s.e1));
-    if (kernel_ms) *kernel_ms = ms;
-    dev.release_slot(s);
 }
 
 Device& device(int ordinal) {
@@ -437,7 +428,6 @@ Device& device(int ordinal) {
     if (std::strncmp(d->prop.gcnArchName, "gfx950", 6) != 0)
         throw Error{kErrDevice, std::string("built for gfx950, device is ") + d->prop.gcnArchName};
     FES_HIP(hipStreamCreateWithFlags(&d->stream, hipStreamNonBlocking));
-    FES_HIP(hipStreamCreateWithFlags(&d->capture_stream, hipStreamNonBlocking));
     noalloc_setup(*d);
     trace("device %d: %s, %d CUs, LDS %zu per block / %zu per CU", ordinal, d->prop.gcnArchName,
           d->prop.multiProcessorCount, (size_t)d->prop.sharedMemPerBlock, (size_t)d->prop.maxSharedMemoryPerMultiProcessor);
@@ -814,7 +804,11 @@ bool run_sim_regs(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, u
     trace("sim launch (registers): %llu words, file %d rows, grid=%llu of %llu waves, %llu rounds",
           (unsigned long long)words, regs, (unsigned long long)grid, (unsigned long long)waves,
           (unsigned long long)rounds);
-    run_timed(dev, stream, kernel_ms, [&] { FES_HIP(launch_sim_regs(L, regs, (int)grid, stream)); });
+    if (!g_finish) return false;
+    run_on_slot(dev, stream, kernel_ms, [&](const ControlSlot& s) {
+        L.ctl = (LaunchCtl*)s.claims();
+        FES_HIP(launch_sim_regs(L, regs, (int)grid, stream));
+    });
     return true;
 }
 

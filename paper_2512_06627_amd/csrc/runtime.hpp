@@ -144,11 +144,10 @@ struct Buffer {
 };
 
 // A control block of one check that no caller is using: claim counters zero, best all ones (the
-// finish kernel leaves it so), the result in pinned host memory, and two events.
+// finish kernel leaves it so), the result in pinned host memory.
 struct ControlSlot {
     uint8_t* dev = nullptr;                  // claim counters, then best
     unsigned long long* host_best = nullptr;  // pinned; best, then the finish kernel's ticks
-    hipEvent_t e0 = nullptr, e1 = nullptr;
     unsigned long long* claims() const { return (unsigned long long*)dev; }
     unsigned long long* best() const { return (unsigned long long*)(dev + kClaimBytes); }
 };
@@ -157,7 +156,6 @@ struct Device {
     int ordinal = 0;
     hipDeviceProp_t prop{};
     hipStream_t stream = nullptr;          // library stream
-    hipStream_t capture_stream = nullptr;  // used only to record hipGraphs
     std::mutex mu;
     std::vector<Buffer> free_bufs;
     size_t pool_device_bytes = 0, pool_pinned_bytes = 0;  // held by the pool (in use or free)
@@ -250,9 +248,6 @@ uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
                      const std::function<void(const ControlSlot&)>& launch);
 // Waits for the finish kernel that puts its ticks there (kPending before); the launch's ms.
 double wait_finished(unsigned long long* ticks, hipStream_t stream);
-
-// Runs `launch` between a slot's events and waits; for kernels that need no control words.
-void run_timed(Device& dev, hipStream_t stream, double* kernel_ms, const std::function<void()>& launch);
 
 // One launch of a batch: cones on the interpreter with one schedule, or native kernels.
 struct BatchPart {

@@ -185,6 +185,7 @@ __device__ __forceinline__ void native_body(const NativeLaunch& L) {
 template <int R>
 __device__ __forceinline__ void sim_body(const SimLaunch& L) {
     const uint64_t code = uniform64(code_base()) + L.code_offset;
+    if (blockIdx.x == 0 && threadIdx.x == 0) L.counters[kStartWord] = __builtin_amdgcn_s_memrealtime();
     const uint32_t xcds = min(gridDim.x, kXcds), xcd = blockIdx.x % xcds;
     const uint64_t share = L.items / xcds, odd = L.items % xcds;
     const uint64_t first = xcd * share + min((uint64_t)xcd, odd), stop = first + share + (xcd < odd ? 1u : 0u);
