@@ -20,9 +20,9 @@
 // time that HBM takes to deliver them, and two rows for about 55.  The complement is taken out of the
 // sum: sum (~w) * key = (2^32 - 1) * sum key - sum w * key.
 //
-// Bound by HBM reads: 3,111 x 100,003 words 213 us, 5.8 TB/s (a wave per row with 1 KB of loads in
-// flight: 292 us, 4.3 TB/s), 1,870 x 131,706 166 us (308), 300 x 250,000 92 us (473: a row's chain of
-// loads); matrices that stay in the memory-side cache and short rows take what they took.
+// Bound by HBM reads: 3,111 x 100,003 words 209 us, 6.0 TB/s (a wave per row with 1 KB of loads in
+// flight: 292 us, 4.3 TB/s), 1,870 x 131,706 165 us (308), 1,631 x 155,733 174 (369), 300 x 250,000 74 us
+// (473: a row's chain of loads); matrices that stay in the memory-side cache 3,055 x 12,511 24 (27).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -152,15 +152,17 @@ __global__ void __launch_bounds__(64 * kMaxSplit) signature_hash_kernel(const ui
 
 // Rows per group: two where that leaves a group per CU (600 x 250,000 words: 136 us, one at a time
 // 186; with groups of four the latency of their reduction shows on short rows, 6,000 x 300: 8.7 us
-// against 6.8, and long ones gain nothing).  Then about 16 waves a CU (with a chunk in hand and one
-// on the way that is 64 KB per CU in flight), shared out so that a group's waves end together; 3,055 x
-// 12,511: 29 us, with 32 waves 34.
+// against 6.8, and long ones gain nothing).  Then up to 16 waves a CU (with a chunk in hand and one on
+// the way that is 64 KB per CU in flight; 3,055 x 12,511: 29 us, with 32 waves 34), the same number on
+// each SIMD where a group has more than four: 1,631 x 155,733 in groups of five waves 251 us, of four
+// 174; 600 x 250,000 in thirteens 134, in eights 107.  A group's waves share its chunks out evenly.
 hipError_t launch_signature_hash_from(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
                                       uint64_t* ones, int cus, unsigned long long* start, hipStream_t stream) {
     if (!sig || !hash || !ones || rows == 0 || words == 0 || cus <= 0) return hipErrorInvalidValue;
     const uint64_t per = rows >= 2ull * cus ? 2 : 1;
     const uint64_t groups = (rows + per - 1) / per, chunks = (words + 255) / 256;
-    const uint64_t most = std::clamp<uint64_t>(16ull * cus / groups, 1, kMaxSplit);
+    const uint64_t room = std::clamp<uint64_t>(16ull * cus / groups, 1, kMaxSplit);
+    const uint64_t most = room >= 16 ? 16 : room >= 8 ? 8 : std::min<uint64_t>(room, 4);
     const uint64_t turns = (chunks + most - 1) / most, split = (chunks + turns - 1) / turns;
     const dim3 grid((uint32_t)std::min<uint64_t>(groups, 1u << 20)), block((uint32_t)(64 * split));
     if (per == 2) hipLaunchKernelGGL(signature_hash_kernel<2>, grid, block, 0, stream, sig, rows, words, hash, ones, start);
