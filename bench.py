@@ -94,10 +94,9 @@ def batch_leg(es, stream, seed: int = 4, count: int = 256, faulty: int = 26, n_r
               size_range=(200, 5000)):
     """`count` XOR-dense layered cones (n ~ U{n_range}, ~U[size_range] AND gates, `faulty` of them
     with an injected fault), checked four ways with identical answers: one plain check per cone on
-    the interpreter; one batched call on the interpreter (persistent grouped launches, autotuned,
-    hipGraph); one batched call with the runtime model's routing (large cones on their compiled
-    specialized kernels, compiled in helper processes on the first call while the other cones run
-    on the interpreter); one plain check per cone with the model's kernel choice once those
+    the interpreter; one batched call on the interpreter (persistent grouped launches, autotuned);
+    one batched call with the runtime model's routing (native kernels where they pay, the other
+    cones on the interpreter); one plain check per cone with the model's kernel choice once those
     kernels exist."""
     import miters
     t0 = time.perf_counter()
@@ -407,7 +406,7 @@ def main():
                     "waves_per_simd": counts["waves_per_simd"],
                     "peak_spec": PEAK_WAVE_INSTR, "peak_probe": probe["best_instr_per_s"],
                     "note": "achieved = VALU instructions of the generated pass x its 2^(n-11-inner) calls / mean "
-                            "kernel time (HIP events); peak = max(256 CU x 2 wave64 instr/clk x 2.4 GHz, v_bitop3 probe)"}
+                            "kernel time (from its first workgroup's start); peak = max(256 CU x 2 wave64 instr/clk x 2.4 GHz, v_bitop3 probe)"}
     else:
         roofline = {"bound": "alu", "achieved": achieved_np, "peak": PEAK_NODE_PATTERNS, "unit": "node*patterns/s",
                     "frac": achieved_np / PEAK_NODE_PATTERNS, "traffic": None, "kernel_ms_mean": k_mean_s * 1e3,

@@ -77,7 +77,8 @@ typedef struct {
 
 typedef struct {
     int device;                /* HIP device ordinal */
-    void *hip_stream;          /* hipStream_t to run on; NULL = the library's stream for the device */
+    void *hip_stream;          /* hipStream_t to run on; NULL = the library's own stream for the device, which
+                                  does not wait for the default stream (that one is hipStreamLegacy) */
     uint32_t words_per_thread; /* interpreter: 32-bit pattern words per lane per slot (1, 2, 4); 0 = tuned */
     uint32_t tile_words;       /* 64-pattern words claimed per work unit; 0 = tuned */
     uint32_t wg_size;          /* threads per workgroup (64..1024, multiple of 64); 0 = tuned */
@@ -137,19 +138,19 @@ int fastlec_es_info_get(const fastlec_es_circuit *c, fastlec_es_info *info);
 int fastlec_es_check(const fastlec_es_circuit *c, const fastlec_es_options *opts, fastlec_es_result *out);
 
 /* Exact simulation of k circuits of different sizes and input counts (whole space each; the
- * option's word range is ignored).  With kernel AUTO, circuits that the runtime model
- * (fastlec_es_predict) gives to the specialized kernel are compiled together (up to 64 kernels
- * per hipRTC program) and run as their own launches (kernel_ms their own, compile_ms their
- * share of their program's compile); a circuit whose kernel does not compile runs on the
- * interpreter instead.  With kernel SPECIALIZED every circuit runs on its specialized kernel
- * that way.  Of the others, those predicted to take at least 1 ms on the interpreter run as
- * their own launches with their own schedule (unless the options fix words_per_thread or
- * wg_size); the rest are grouped by value-file size (the register tier's 104, 144 and 232 rows,
- * above that powers of two of the row count); each group
- * is one persistent interpreter launch over all its cones, in longest-processing-time order by
- * the runtime model's time, with a tuned schedule (or the option's schedule fields) and recorded
- * once as a hipGraph; their kernel_ms is the sum over the groups.  cs: k handles; out: k
- * results.  An entry's own error (a null handle) is reported in that entry: its verdict is the
+ * option's word range is ignored).  With kernel SPECIALIZED every circuit runs on its native
+ * kernel (machine code that the library writes), under AUTO those for which one exists or pays;
+ * they are built on host threads and run as one launch per register tier.  What fits no native kernel
+ * is compiled with hipRTC as far as the runtime model (fastlec_es_predict) finds that worth it, with
+ * kernel_ms of its own and compile_ms its share of its program's compile; a circuit whose kernel does
+ * not compile runs on the interpreter instead.  Of the others, those predicted to take at least 1 ms on
+ * the interpreter run as their own launches with their own schedule (unless the options fix
+ * words_per_thread or wg_size); the rest are grouped by value-file size (the register tier's 104,
+ * 144 and 232 rows, a group of few passes with the next one; above that powers of two of the row
+ * count); each group is one persistent interpreter launch over all its cones, in
+ * longest-processing-time order by the runtime model's time, with a tuned schedule (or the option's
+ * schedule fields).  All launches share one wait; kernel_ms is the time of all of them.  cs: k
+ * handles; out: k results.  An entry's own error (a null handle) is reported in that entry: its verdict is the
  * negative status (FASTLEC_ERR_INVALID) and its other fields are zero; the other entries are
  * checked and valid, and the call returns the first entry's status.  A device or runtime failure
  * fails the whole call with its status; the out entries are then not valid. */
@@ -260,7 +261,7 @@ void fastlec_es_server_destroy(fastlec_es_server *s);
  *   opts      device, stream, words_per_thread (default 1; 4 uses 8-gate bundles, else 16),
  *             wg_size and kernel (FASTLEC_KERNEL_INTERP_HBM forces value files in device memory)
  *             are honoured; may be NULL.
- *   kernel_ms if not NULL, the kernel's time (HIP events on the launch stream).
+ *   kernel_ms if not NULL, the kernel's time (from its first workgroup's start).
  * Runs on the option's stream (or the library's own stream): the caller's device buffers must
  * be ready in that stream's order, so pass the stream that produced them (e.g. torch's current
  * stream for tensors torch just filled).  Blocks until sig is written.  FASTLEC_ERR_INVALID for

@@ -18,7 +18,7 @@ fixed launch cost:
 * hipRTC compile of the specialized kernel: t = c0 + c1 * L.
 
 This script times plain checks of seeded layered cones and multiplier miters
-with each kernel (kernel times from the library's HIP events; compile time as
+with each kernel (kernel times as the library reports them; compile time as
 the library reports it), fits the constants by least squares on relative
 error, and prints one JSON object with the fitted constants, the data and the
 fit's errors.  Run it on the GPU:  python -m paper_2512_06627_amd.calibrate

@@ -20,7 +20,7 @@ constexpr double kSpecT0Ms = 0.0032;
 constexpr double kSpecLutPassesPerS = 7.5e11;
 constexpr double kCompileC0Ms = 101.7;
 constexpr double kCompileMsPerLut = 0.00664;
-// Multi-kernel programs (GPU machine host, comgr's cache off): 16 kernels of about 500 LUT steps
+// Multi-kernel programs (16-core host, comgr's cache off): 16 kernels of about 500 LUT steps
 // 0.39 s as one program, 8 of about 4,000 0.45 s, 2 small ones 0.14-0.16 s in helpers against
 // the fixed 0.10 s in the process: each kernel adds about 12 ms besides its LUT steps, and a
 // helper's start-up about 45 ms.

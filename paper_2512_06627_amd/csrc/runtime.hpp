@@ -302,8 +302,7 @@ void run_sim(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32
 // cone's range and cached per device and batch shape.
 Schedule autotune(Device& dev, const std::vector<Circuit*>& cs, const std::vector<HwRange>& ranges, hipStream_t stream,
                   bool hbm);
-// One persistent interpreter launch over whole spaces, captured once as a hipGraph
-// (descriptor upload, kernel, result readback) and replayed for identical batches.
+// A batch of one interpreter launch.
 void run_batch_graph(Device& dev, const std::vector<Circuit*>& cs, const std::vector<HwRange>& ranges,
                      const Schedule& sch, hipStream_t stream, std::vector<uint64_t>& best, double* ms);
 

@@ -10,19 +10,18 @@
 // running estimate of the interpreter's node*pattern rate, and every job in
 // flight gets the same amount of gate evaluations per step.
 //
-// Device-resident job table: best-so-far value per slot (written by the
-// kernels' atomicMin, read back after each step, reset when a slot is reused)
-// and the slot's descriptors, which the host refreshes each step with the
-// job's next slice.
+// Device-resident job table: best value per slot (written by the kernels' atomicMin, handed over and
+// reset by the finish kernel after each step) and the slot's descriptors, which the host refreshes
+// each step with the job's next slice.
 //
 // Specialized tier: pattern spaces differ by many orders of magnitude (2^n), so a
 // few large jobs carry most of the work.  A job whose remaining interpreter time is
-// estimated well above the cost of compiling its specialized kernel is handed to the
-// compile threads (one per compile helper process) while it keeps running on the
-// interpreter; from the step after the kernel is ready, the job's slices run on the
-// specialized kernel instead (same
+// estimated above the cost of building its native kernel is handed to the compile
+// threads (one per compile helper process; what has no native kernel is compiled with hipRTC
+// there) while it keeps running on the interpreter, or waits where its stream is not planned
+// yet; from the step after the kernel is ready, the job's slices run on it instead (same
 // ascending slices, same best[] entry, so the answer cannot change).  Circuits
-// submitted again reuse their compiled kernel at once.
+// submitted again use their kernel at once where it beats a share of the interpreter's launch.
 #include <algorithm>
 #include <cmath>
 #include <condition_variable>
