@@ -233,7 +233,8 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
     double compile_ms = 0;
     bool build = false;
     std::shared_ptr<JitKernel> jk =
-        native_kernel(c, o, full, std::min(chunk, full.end - full.begin), chunked ? nullptr : &build);
+        native_kernel(c, o, full, std::min(chunk, full.end - full.begin),
+                      chunked || o.dev_scratch ? nullptr : &build);  // the interpreter needs more of the caller's memory
     double kernel_ms = 0;
     uint64_t best = ~0ull, first = full.begin;
     if (build) jk = check_while_building(dev, c, o, full, stream, &first, &best, &kernel_ms);
