@@ -1,4 +1,4 @@
-"""The hash kernel's row groups (1, 2 or 4 rows, by how many rows there are) and its column
+"""The hash kernel's row groups (1 or 2 rows, by how many rows there are) and its column
 chunks of 256 words shared among 1 to 16 waves: rows and words at their edges, rows at every
 alignment, both polarities and extreme words, exact against the plain CPU oracle.
 """
