@@ -193,7 +193,8 @@ std::shared_ptr<JitKernel> check_while_building(Device& dev, Circuit& c, const f
     const double t0 = now_ms();
     std::vector<Circuit*> one{&c};
     const double total = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
-    const uint64_t piece = ((uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total)) + 4095) / 4096 * 4096;
+    const uint64_t want = (uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total));
+    const uint64_t piece = std::max<uint64_t>(1, (want + 4095) / 4096) * 4096;  // a half-word may take longer
     Schedule sch = default_schedule(dev, one, &o, std::min(piece, full.end - full.begin));
     if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
     while (*lo < full.end && *best == ~0ull && !b.done.load(std::memory_order_acquire)) {

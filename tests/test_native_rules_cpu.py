@@ -1,0 +1,67 @@
+"""When native kernels are built, waited for and used: checks, batches and the server on the host
+stand-in of a GPU (tests/standin.py), driven through the package.
+
+Each test runs a script in a process of its own, with the library's trace switched on.
+"""
+import os
+import subprocess
+import sys
+
+import pytest
+
+import standin
+
+HEAD = """
+import sys, time
+sys.path.insert(0, {root!r})
+import miters, paper_2512_06627_amd as es
+es.LIB_PATH = {lib!r}
+
+def load(g):
+    return es.fastlec_es_load_aig(g.to_aig())
+
+def chain(steps, n=12):
+    "Rounds of s[i] ^= s[i+1] & s[i+5]: four gates a step, few values alive."
+    g = miters.Aig(n)
+    s = [g.input(i) for i in range(n)]
+    for k in range(steps):
+        i = k % n
+        s[i] = g.XOR(s[i], g.AND(s[(i + 1) % n] ^ (k // n & 1), s[(i + 5) % n] ^ (k // (2 * n) & 1)))
+    g.add_output(g.AND(s[0], s[1]))
+    return g
+
+def chain_value(steps, pattern, n=12):
+    s = [(pattern >> i) & 1 for i in range(n)]
+    for k in range(steps):
+        i = k % n
+        s[i] ^= (s[(i + 1) % n] ^ (k // n & 1)) & (s[(i + 5) % n] ^ (k // (2 * n) & 1))
+    return s[0] & s[1]
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if not os.path.exists(standin.CLANG):
+        pytest.skip("clang++ not found")
+    return standin.build(tmp_path_factory.mktemp("native_rules"))
+
+
+def run(lib, script, **env):
+    env = dict(os.environ, FASTLEC_ES_TRACE="1", **env)
+    r = subprocess.run([sys.executable, "-c", HEAD.format(root=standin.ROOT, lib=lib) + script], capture_output=True,
+                       text=True, timeout=300, env=env)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
+    return r
+
+
+def test_one_word_of_a_long_circuit(lib):
+    """A word that takes the interpreter more than a millisecond is still one piece of a check while the
+    kernel is being built."""
+    r = run(lib, """
+steps, want = 32000, [p for p in range(64) if chain_value(32000, p)]
+c = load(chain(steps))
+for i in range(160):
+    r = es.fastlec_es_check(c, begin_word=0, end_word=1)
+    assert (r["verdict"], r["cex"]) == ((1, want[0]) if want else (0, 0)), r
+""")
+    assert "native: 0 inner inputs" in r.stderr, r.stderr[-2000:]
