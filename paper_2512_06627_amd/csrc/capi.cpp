@@ -81,6 +81,8 @@ void fill_result(const Circuit& c, const HwRange& r, uint64_t best, fastlec_es_r
 constexpr double kCompileMargin = 1.2;
 // What a millisecond of building a single check's native kernel costs against one of its run.
 constexpr double kCheckBuildWeight = 0.5;
+// The same for the kernels of a batch, which are built on all host threads.
+constexpr double kBatchBuildWeight = 0.2;
 // Planning a cone's interpreter stream, per AND gate, and loading a module of native kernels.
 constexpr double kPlanMsPerGate = 0.15e-3, kLoadMs = 1.2;
 
@@ -144,13 +146,14 @@ std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o
             k = nullptr;
             have = by_rtc;
         }
-        if (have > 1.1 * aim && native_pays(c, have, patterns)) return t->get(c, span, 0.0, nullptr);
+        if (have > 1.1 * aim && native_pays(c, span, have, patterns))
+            if (auto exact = t->get(c, span, 0.0, nullptr)) return exact;
         return k;
     }
     if (o.words_per_thread || o.wg_size) return nullptr;
     const double interp = model_interp_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
     if (auto k = t->ready(c, span)) return t->run_ms(*k, patterns) < interp ? k : nullptr;
-    if (!native_pays(c, interp, patterns)) return nullptr;
+    if (!native_pays(c, span, interp, patterns)) return nullptr;
     if (later) {
         *later = true;
         return nullptr;
@@ -423,6 +426,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                         if (t->share_ms(*have, patterns) < interp) want.push_back(i);
                         continue;
                     }
+                    if (t->refused(c, span, kBatchBuildWeight)) continue;
                     const double plan = c.planned(4) ? 0.0 : kPlanMsPerGate * c.plan1.num_ands_tfi;
                     const double net = interp + c.interp_ms_spent.load(std::memory_order_relaxed) +
                                        (plan - 1.5 * t->guess_build_ms(c)) / threads;
@@ -453,7 +457,7 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
             }
             parallel_for(build.size(), [&](size_t b) {
                 const size_t j = build[b];
-                got[j] = t->get(*v[want[j]], rs[want[j]].end - rs[want[j]].begin, forced ? 0.0 : 0.2, nullptr);
+                got[j] = t->get(*v[want[j]], rs[want[j]].end - rs[want[j]].begin, forced ? 0.0 : kBatchBuildWeight, nullptr);
             });
             for (size_t j = 0; j < want.size(); ++j) {
                 if (!got[j]) continue;  // its values fit neither registers nor LDS

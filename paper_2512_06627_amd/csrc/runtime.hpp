@@ -91,6 +91,7 @@ struct Circuit {
     std::map<std::pair<int, uint32_t>, Instr*> dev_prog;                  // (device, bundle) -> stream
     std::map<int, std::shared_ptr<JitKernel>> jit;                       // waves_per_eu -> kernel
     std::map<uint32_t, std::shared_ptr<JitKernel>> native;               // inner-input limit -> native kernel
+    std::map<uint32_t, bool> native_refused;                             // limits without one (see native.cpp)
     std::mutex native_mu;                                                 // one native build at a time
     std::atomic<double> interp_ms_spent{0};                               // see native_pays
     std::unique_ptr<LutProgram> lut;                                      // specialized-kernel program
@@ -384,6 +385,8 @@ struct NativeTier {
     // thread to give the building up (null then, too).
     std::shared_ptr<JitKernel> (*ready)(Circuit& c, uint64_t span);
     std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop);
+    // Whether get() is known to return null for this span.
+    bool (*refused)(Circuit& c, uint64_t span, double weight);
     // The built kernel that is expected to be fastest over `r`, whichever spans it was built for (*ms: its
     // time there, *fits: whether get() would return it); null when none is built.
     std::shared_ptr<JitKernel> (*best)(Circuit& c, const HwRange& r, double* ms, bool* fits);
@@ -405,8 +408,9 @@ void register_sim_runner(SimRunner r);
 // Whether a native kernel pays for a circuit that has none: the interpreter's time for this check
 // plus what the interpreter has already taken for this circuit exceeds the native kernel's time
 // and its building.  A circuit checked again and again thus spends at most about twice the better
-// of the two; one checked once is built only when that check alone pays.
-bool native_pays(Circuit& c, double interp_ms, double patterns);
+// of the two; one checked once is built only when that check alone pays.  Never for a span that get()
+// is known to refuse.
+bool native_pays(Circuit& c, uint64_t span, double interp_ms, double patterns);
 
 // The per-pass body as one asm statement with planner-assigned registers (v0.., s<sgpr_base>..).
 // Returns false, with the register counts in stats, when it needs more than the limits.

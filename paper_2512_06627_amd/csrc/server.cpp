@@ -252,7 +252,7 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
         if (nt && jit_mode == 1) {
             const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
             const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
-            if (native_pays(*j->c, plan + share * (double)std::max<size_t>(1, sharing), left)) {
+            if (native_pays(*j->c, slice_span(*j->c), plan + share * (double)std::max<size_t>(1, sharing), left)) {
                 j->compile_queued = true;
                 compile_queue.push_back(j);
                 cv_compile.notify_one();

@@ -65,3 +65,37 @@ for i in range(160):
     assert (r["verdict"], r["cex"]) == ((1, want[0]) if want else (0, 0)), r
 """)
     assert "native: 0 inner inputs" in r.stderr, r.stderr[-2000:]
+
+
+def test_a_circuit_without_kernel_is_tried_once(lib):
+    """A cone too wide for registers and LDS: AUTO checks, batches and explicit builds all end in no kernel, and
+    only the first of each weight goes through the planning, mapping and encoding (some 20 ms)."""
+    r = run(lib, """
+c = load(miters.layered_cone_miter(1, 14, 27000))
+def spent(f, times):
+    t = time.perf_counter()
+    for _ in range(times):
+        f()
+    return time.perf_counter() - t
+def auto():
+    assert es.fastlec_es_check(c, begin_word=0, end_word=1)["verdict"] == 0
+def batch():
+    assert [x["verdict"] for x in es.fastlec_es_check_batch([c, c])] == [0, 0]
+def info():
+    try:
+        es.fastlec_es_native_info(c)
+        assert False
+    except es.EsError:
+        pass
+spent(auto, 200)   # more than a build's time on the interpreter
+late = min(spent(auto, 20) / 20 for _ in range(3))
+whole = min(spent(info, 1) for _ in range(3))
+print("late", late, "info", whole)
+assert late < 5e-3 and whole < 1e-3
+for _ in range(3):
+    batch()
+for _ in range(3):
+    assert es.fastlec_es_check(c, kernel="specialized", begin_word=0, end_word=1)["verdict"] == 0
+""")
+    # one word, under AUTO and SPECIALIZED; the whole space for info, which tries every choice
+    assert r.stderr.count("native: no kernel") == 3, r.stdout + r.stderr[-3000:]
