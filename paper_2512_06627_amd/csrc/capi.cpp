@@ -2,6 +2,7 @@
 // every entry point catches, stores a thread-local message and returns a status.
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -120,9 +121,9 @@ bool native_allowed() {
 }
 
 // The native kernel that a check of `r` runs on, in pieces of `span` half-words, or null.  AUTO takes one
-// that is built when it is expected to be faster than the interpreter, and builds one when that
+// that is built when it is expected to be faster than the interpreter, and has one built when that
 // pays (native_pays; *later = true: the caller sees to it); a caller that fixes the interpreter's
-// schedule keeps the interpreter until a kernel is built.  SPECIALIZED takes the best kernel there is, a
+// schedule keeps the interpreter.  SPECIALIZED takes the best kernel there is, a
 // native one made for other spans or the hipRTC one (then null), until what it costs beyond a kernel
 // for this span has paid for building that (MAC8, three fifths of the space after compile_specialized:
 // first check 1.6 ms on the whole space's kernel, 7.9 with one more build); without any it builds one.
@@ -154,11 +155,8 @@ std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o
     const double interp = model_interp_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
     if (auto k = t->ready(c, span)) return t->run_ms(*k, patterns) < interp ? k : nullptr;
     if (!native_pays(c, span, interp, patterns)) return nullptr;
-    if (later) {
-        *later = true;
-        return nullptr;
-    }
-    return t->get(c, span, kCheckBuildWeight, nullptr);
+    *later = true;
+    return nullptr;
 }
 
 // Builds a native kernel on a thread of its own.
@@ -175,49 +173,74 @@ struct NativeBuilder {
             done.store(true, std::memory_order_release);
         });
     }
-    void wait() { t.join(); }
+    std::shared_ptr<JitKernel> result() {
+        t.join();
+        return kernel;
+    }
     ~NativeBuilder() {
         stop.store(true, std::memory_order_relaxed);
         if (t.joinable()) t.join();
     }
 };
 
+// Whether a check that started at t_start has to stop: its cancel flag is up or its deadline has passed.
+int interrupted(const fastlec_es_options& o, double t_start) {
+    if (o.cancel_flag && *o.cancel_flag) return FASTLEC_CANCELLED;
+    if (o.deadline_s > 0 && now_ms() - t_start >= o.deadline_s * 1e3) return FASTLEC_TIMEOUT;
+    return FASTLEC_OK;
+}
+
 // The beginning of a check of `full` on the interpreter, in ascending pieces of about half a
-// millisecond, while the native kernel for it is built: a counterexample that lies there is found
-// without the kernel (MAC8, words 12345677 to 54321011 with the first difference 1 ms into them: 1.9 ms
-// in place of 8.4), and otherwise the device has not waited.  Ends with the kernel (null if there can be
-// none), or with a pattern in *best, or at the end; *lo = first half-word not covered.  What is spent on the interpreter counts towards the kernel, as in native_pays: a
+// millisecond, while the native kernel for checks of `span` half-words is built: a counterexample that lies
+// there is found without the kernel (MAC8, words 12345677 to 54321011 with the first difference 1 ms into
+// them: 1.9 ms in place of 8.4), and otherwise the device has not waited.  Ends with the kernel (null if
+// there can be none), or with a pattern in *best, or at the end, or interrupted (*status); *lo = first
+// half-word not covered.  In the caller's device memory nothing is interpreted meanwhile: that may need more
+// of it than the kernel.  What is spent on the interpreter counts towards the kernel, as in native_pays: a
 // circuit whose checks keep ending early gets it once they have taken as long as building it.
 std::shared_ptr<JitKernel> check_while_building(Device& dev, Circuit& c, const fastlec_es_options& o,
-                                                const HwRange& full, hipStream_t stream, uint64_t* lo, uint64_t* best,
-                                                double* kernel_ms) {
-    const double patterns = 32.0 * (double)(full.end - full.begin);
-    NativeBuilder b(c, full.end - full.begin);
+                                                const HwRange& full, uint64_t span, double t_start,
+                                                hipStream_t stream, uint64_t* lo, uint64_t* best, double* kernel_ms,
+                                                int* status) {
+    *status = interrupted(o, t_start);
+    if (*status != FASTLEC_OK) return nullptr;
+    const double patterns = 32.0 * (double)(full.end - full.begin), build_ms = native_tier()->guess_build_ms(c) + 1.0;
+    // A kernel that would come after the deadline is not started.
+    if (o.deadline_s > 0 && !o.dev_scratch && now_ms() - t_start + 1.5 * build_ms > o.deadline_s * 1e3) return nullptr;
+    NativeBuilder b(c, span);
     const double t0 = now_ms();
-    std::vector<Circuit*> one{&c};
-    const double total = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
-    const uint64_t want = (uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total));
-    const uint64_t piece = std::max<uint64_t>(1, (want + 4095) / 4096) * 4096;  // a half-word may take longer
-    Schedule sch = default_schedule(dev, one, &o, std::min(piece, full.end - full.begin));
-    if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
-    while (*lo < full.end && *best == ~0ull && !b.done.load(std::memory_order_acquire)) {
-        const uint64_t end = std::min(full.end, *lo + piece);
-        std::vector<uint64_t> found;
-        double ms = 0;
-        run_interp(dev, one, {HwRange{*lo, end}}, sch, stream, nullptr, found, &ms,
-                   DevMem{o.dev_scratch, o.dev_scratch ? o.dev_scratch_bytes : 0});
-        *kernel_ms += ms;
-        *best = found[0];
-        *lo = end;
+    auto built = [&] { return b.done.load(std::memory_order_acquire); };
+    auto wait = [&] {  // for the kernel, until interrupted
+        while (!built() && (*status = interrupted(o, t_start)) == FASTLEC_OK)
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
+    };
+    if (o.dev_scratch) {
+        wait();
+    } else {
+        std::vector<Circuit*> one{&c};
+        const double total = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
+        const uint64_t want = (uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total));
+        const uint64_t piece = std::max<uint64_t>(1, (want + 4095) / 4096) * 4096;  // a half-word may take longer
+        Schedule sch = default_schedule(dev, one, &o, std::min(piece, full.end - full.begin));
+        if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
+        while (*lo < full.end && *best == ~0ull && !built() && (*status = interrupted(o, t_start)) == FASTLEC_OK) {
+            const uint64_t end = std::min(full.end, *lo + piece);
+            std::vector<uint64_t> found;
+            double ms = 0;
+            run_interp(dev, one, {HwRange{*lo, end}}, sch, stream, nullptr, found, &ms);
+            *kernel_ms += ms;
+            *best = found[0];
+            *lo = end;
+        }
+        if (*lo == full.end || *best != ~0ull) {
+            const double here = now_ms() - t0, spent = c.interp_ms_spent.load(std::memory_order_relaxed);
+            if (spent + here > 1.5 * build_ms) wait();
+            else c.interp_ms_spent.store(spent + here, std::memory_order_relaxed);
+            *status = FASTLEC_OK;  // the answer is there
+            return nullptr;
+        }
     }
-    const double here = now_ms() - t0, spent = c.interp_ms_spent.load(std::memory_order_relaxed);
-    if (*lo == full.end || *best != ~0ull) {
-        if (spent + here > 1.5 * (native_tier()->guess_build_ms(c) + 1.0)) b.wait();
-        else c.interp_ms_spent.store(spent + here, std::memory_order_relaxed);
-        return nullptr;
-    }
-    b.wait();
-    return b.kernel;
+    return *status == FASTLEC_OK ? b.result() : nullptr;
 }
 
 void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) {
@@ -236,14 +259,15 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
     const double patterns = 32.0 * (double)(full.end - full.begin);
     double compile_ms = 0;
     bool build = false;
-    std::shared_ptr<JitKernel> jk =
-        native_kernel(c, o, full, std::min(chunk, full.end - full.begin),
-                      chunked || o.dev_scratch ? nullptr : &build);  // the interpreter needs more of the caller's memory
+    const uint64_t span = std::min(chunk, full.end - full.begin);
+    std::shared_ptr<JitKernel> jk = native_kernel(c, o, full, span, &build);
     double kernel_ms = 0;
     uint64_t best = ~0ull, first = full.begin;
-    if (build) jk = check_while_building(dev, c, o, full, stream, &first, &best, &kernel_ms);
+    int status = FASTLEC_OK;
+    if (build) jk = check_while_building(dev, c, o, full, span, t_start, stream, &first, &best, &kernel_ms, &status);
     const bool native = jk != nullptr;
-    const bool spec = native || (first < full.end && best == ~0ull && use_specialized(c, o, full));
+    const bool more = status == FASTLEC_OK && first < full.end && best == ~0ull;
+    const bool spec = native || (more && use_specialized(c, o, full));
     if (spec && !native) jk = jit_kernel(c, specialized_waves_per_eu(), &compile_ms);
     Schedule sch;
     if (!spec) {
@@ -251,13 +275,10 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
         sch = default_schedule(dev, one, &o, full.end - full.begin);
         if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
     }
-    uint64_t done_to = full.begin;
-    int status = FASTLEC_OK;
-    for (uint64_t lo = first; lo < full.end && best == ~0ull; lo += chunk) {
-        if (chunked) {
-            if (o.cancel_flag && *o.cancel_flag) { status = FASTLEC_CANCELLED; break; }
-            if (o.deadline_s > 0 && now_ms() - t_start >= o.deadline_s * 1e3) { status = FASTLEC_TIMEOUT; break; }
-        }
+    uint64_t done_to = first;
+    for (uint64_t lo = first; more && lo < full.end && best == ~0ull; lo += chunk) {
+        status = interrupted(o, t_start);
+        if (status != FASTLEC_OK) break;
         HwRange r{lo, std::min(full.end, lo + chunk)};
         double ms = 0;
         const DevMem mem{o.dev_scratch, o.dev_scratch ? o.dev_scratch_bytes : 0};

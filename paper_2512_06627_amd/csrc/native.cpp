@@ -1,9 +1,11 @@
 // Native tier on the device: kernels per circuit, modules and launches.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
+#include <thread>
 
 #include "native.hpp"
 #include "runtime.hpp"
@@ -55,7 +57,12 @@ bool refused(Circuit& c, uint64_t span, double weight) {
 std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop) {
     if (auto k = find(c, span, true)) return k;
     if (refused(c, span, weight)) return nullptr;
-    std::lock_guard<std::mutex> build(c.native_mu);
+    std::unique_lock<std::mutex> build(c.native_mu, std::defer_lock);
+    while (stop && !build.try_lock()) {  // another thread's build of this circuit
+        if (stop->load(std::memory_order_relaxed)) return nullptr;
+        std::this_thread::sleep_for(std::chrono::microseconds(50));
+    }
+    if (!stop) build.lock();
     if (auto k = find(c, span, true)) return k;
     if (refused(c, span, weight)) return nullptr;
     const uint32_t limit = inner_limit(c, span);

@@ -107,6 +107,7 @@ std::shared_ptr<NativeKernel> build_native(const Aig& g, const std::vector<uint3
         k->limit = limit;
         bool ok = false;
         for (const Tier& t : kTiers) {
+            if (stopped()) return nullptr;
             k->waves = t.waves;
             ok = emit_native(lp, o.s.offset, t.vgprs, t.slots, k->code);
             // The third wave pays for a few LDS operations (one in twenty instructions), shared work

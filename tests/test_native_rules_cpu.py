@@ -99,3 +99,53 @@ for _ in range(3):
 """)
     # one word, under AUTO and SPECIALIZED; the whole space for info, which tries every choice
     assert r.stderr.count("native: no kernel") == 3, r.stdout + r.stderr[-3000:]
+
+
+def test_a_deadline_holds_while_a_kernel_is_built(lib):
+    """Checks of a word, a fraction of a millisecond on the interpreter, with deadlines that are shorter than
+    building the kernel (about 0.1 s): none runs into its deadline.  With time enough the kernel is built."""
+    r = run(lib, """
+word = 64 * 7
+want = next((p for p in range(word, word + 64) if chain_value(32000, p)), None)
+c = load(chain(32000))
+def check(**kw):
+    t = time.perf_counter()
+    r = es.fastlec_es_check(c, begin_word=7, end_word=8, **kw)
+    assert (r["verdict"], r["cex"]) == ((0, 0) if want is None else (1, want)), r
+    return time.perf_counter() - t
+for i in range(200):
+    took = check(deadline_s=0.04)
+    assert took < 0.2, (i, took)
+print("no kernel yet", flush=True)
+print("no kernel yet", file=sys.stderr, flush=True)
+for i in range(3):
+    check(deadline_s=60.0)
+""")
+    before, after = r.stderr.split("no kernel yet")
+    assert "inner inputs" not in before and "native: 0 inner inputs" in after, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("how", ["cancel", "deadline"])
+def test_a_check_is_stopped_while_its_kernel_is_built(lib, how):
+    """In the caller's device memory nothing is interpreted meanwhile: cancelled, or at its deadline, in the middle
+    of the building, a check ends without the kernel and says that it has covered nothing."""
+    r = run(lib, """
+import ctypes, threading
+c = load(chain(40000, 32))
+how, flag = %r, ctypes.c_int(0)
+class Scratch:
+    mem = ctypes.create_string_buffer(1 << 16)
+    def data_ptr(self): return (ctypes.addressof(self.mem) + 255) // 256 * 256
+    def numel(self): return 4096
+    def element_size(self): return 1
+kw = {"cancel_flag": flag} if how == "cancel" else {"deadline_s": 0.03}
+if how == "cancel":
+    threading.Timer(0.02, lambda: setattr(flag, "value", 1)).start()
+try:
+    es.fastlec_es_check(c, scratch=Scratch(), **kw)
+    assert False
+except es.EsError as e:
+    assert e.code == (es.FASTLEC_CANCELLED if how == "cancel" else es.FASTLEC_TIMEOUT), e
+    assert e.result["patterns_evaluated"] == 0 and e.result["next_word"] == 0, e.result
+""" % how)
+    assert "inner inputs" not in r.stderr, r.stderr[-2000:]
