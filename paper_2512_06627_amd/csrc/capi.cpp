@@ -11,6 +11,7 @@
 #include <fstream>
 #include <map>
 #include <sstream>
+#include <system_error>
 #include <thread>
 #include <unordered_map>
 
@@ -165,16 +166,20 @@ struct NativeBuilder {
     std::shared_ptr<JitKernel> kernel;
     std::thread t;
     NativeBuilder(Circuit& c, uint64_t span) {
-        t = std::thread([this, &c, span] {
-            try {
-                kernel = native_tier()->get(c, span, kCheckBuildWeight, &stop);
-            } catch (...) {  // the interpreter goes on without it
-            }
+        try {
+            t = std::thread([this, &c, span] {
+                try {
+                    kernel = native_tier()->get(c, span, kCheckBuildWeight, &stop);
+                } catch (...) {  // the interpreter goes on without it
+                }
+                done.store(true, std::memory_order_release);
+            });
+        } catch (const std::system_error&) {  // no thread to be had: no kernel either
             done.store(true, std::memory_order_release);
-        });
+        }
     }
     std::shared_ptr<JitKernel> result() {
-        t.join();
+        if (t.joinable()) t.join();
         return kernel;
     }
     ~NativeBuilder() {

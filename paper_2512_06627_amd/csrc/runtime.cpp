@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <numeric>
+#include <system_error>
 
 namespace fes {
 
@@ -487,7 +488,10 @@ void parallel_for(size_t n, const std::function<void(size_t)>& f) {
         }
     };
     std::vector<std::thread> th;
-    for (size_t t = 1; t < workers; ++t) th.emplace_back(run);
+    try {
+        for (size_t t = 1; t < workers; ++t) th.emplace_back(run);
+    } catch (const std::system_error&) {  // no more threads to be had: those there are do it
+    }
     run();
     for (auto& t : th) t.join();
     if (first) std::rethrow_exception(first);

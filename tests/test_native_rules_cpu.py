@@ -149,3 +149,24 @@ except es.EsError as e:
     assert e.result["patterns_evaluated"] == 0 and e.result["next_word"] == 0, e.result
 """ % how)
     assert "inner inputs" not in r.stderr, r.stderr[-2000:]
+
+
+def test_no_thread_to_be_had(lib, tmp_path):
+    """A process at its limit of threads: checks go on without a kernel built beside them, batches plan and
+    build on the calling thread."""
+    pre = tmp_path / "no_threads.so"
+    subprocess.run(["g++", "-shared", "-fPIC", os.path.join(standin.SAN, "no_threads.cpp"), "-o", str(pre), "-ldl"],
+                   check=True)
+    run(lib, """
+import ctypes
+es.lib()
+cs = [load(miters.layered_cone_miter(40 + i, 12, 1500, fault_seed=i or None)) for i in range(3)]
+want = [es.fastlec_es_check(c, kernel="interp") for c in cs]
+fresh = [load(miters.layered_cone_miter(40 + i, 12, 1500, fault_seed=i or None)) for i in range(3)]
+ctypes.CDLL(None).refuse_threads(1)
+same = lambda r, w: (r["verdict"], r["cex"]) == (w["verdict"], w["cex"])
+for i in range(150):  # more than a kernel's building on the interpreter
+    assert same(es.fastlec_es_check(cs[0]), want[0])
+for kernel in ("auto", "interp", "specialized"):
+    assert all(map(same, es.fastlec_es_check_batch(fresh, kernel=kernel), want)), kernel
+""", LD_PRELOAD=str(pre))
