@@ -121,43 +121,45 @@ bool native_allowed() {
     return true;
 }
 
-// The native kernel that a check of `r` runs on, in pieces of `span` half-words, or null.  AUTO takes one
-// that is built when it is expected to be faster than the interpreter, and has one built when that
-// pays (native_pays; *later = true: the caller sees to it); a caller that fixes the interpreter's
-// schedule keeps the interpreter.  SPECIALIZED takes the best kernel there is, a
-// native one made for other spans or the hipRTC one (then null), until what it costs beyond a kernel
-// for this span has paid for building that (MAC8, three fifths of the space after compile_specialized:
-// first check 1.6 ms on the whole space's kernel, 7.9 with one more build); without any it builds one.
+// The native kernel that a check of `r` runs on, in pieces of `span` half-words, or null.  Both kinds take the
+// best one there is, also one made for other spans, until what it costs beyond the kernel for this span
+// has paid for building that (MAC8, three fifths of the space after compile_specialized: first check 1.6 ms on
+// the whole space's kernel, 7.9 with one more build; 16x16 miter 2.96 ms on the kernel of a few words, without
+// inner inputs, 0.68 on its own).  AUTO takes a kernel when it is expected to be faster than the interpreter,
+// and has one built when that pays (native_pays; *later = true: the caller sees to it, with *have = the time of
+// what is returned); a caller that fixes the interpreter's schedule keeps the interpreter.  SPECIALIZED
+// takes the hipRTC kernel where that is the best there is (then null); without any it builds one.
 std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o, const HwRange& r, uint64_t span,
-                                         bool* later) {
+                                         bool* later, double* have) {
     if (o.kernel != FASTLEC_KERNEL_SPECIALIZED && o.kernel != FASTLEC_KERNEL_AUTO) return nullptr;
     if (!native_allowed()) return nullptr;
     const NativeTier* t = native_tier();
-    const bool whole = span >= r.end - r.begin;
     const double patterns = 32.0 * (double)(r.end - r.begin);
+    double aim = 0;
+    std::shared_ptr<JitKernel> k = t->best(c, r, span, have, &aim);
+    const bool exact = k && aim >= *have;
     if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) {
-        double have = 0;
-        bool fits = false;
-        std::shared_ptr<JitKernel> k = whole ? t->best(c, r, &have, &fits) : nullptr;
+        if (exact) return k;
         const bool rtc = jit_ready(c, specialized_waves_per_eu()) != nullptr;
-        if (fits) return k;
-        if (!whole || (!k && !rtc)) return t->get(c, span, 0.0, nullptr);
-        const double aim = k ? t->run_ms(*k, patterns) : t->guess_run_ms(c, patterns);
+        if (!k && !rtc) return t->get(c, span, 0.0, nullptr);
+        if (!k) aim = t->guess_run_ms(c, patterns);
         const double by_rtc = rtc ? model_specialized_ms(c.lut_steps_known(), patterns) : 1e300;
-        if (!k || by_rtc < have) {
+        if (!k || by_rtc < *have) {
             k = nullptr;
-            have = by_rtc;
+            *have = by_rtc;
         }
-        if (have > 1.1 * aim && native_pays(c, span, have, patterns))
-            if (auto exact = t->get(c, span, 0.0, nullptr)) return exact;
+        if (*have > 1.1 * aim && native_pays(c, span, *have, patterns))
+            if (auto built = t->get(c, span, 0.0, nullptr)) return built;
         return k;
     }
     if (o.words_per_thread || o.wg_size) return nullptr;
     const double interp = model_interp_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
-    if (auto k = t->ready(c, span)) return t->run_ms(*k, patterns) < interp ? k : nullptr;
-    if (!native_pays(c, span, interp, patterns)) return nullptr;
-    *later = true;
-    return nullptr;
+    if (!k || *have >= interp) {
+        k = nullptr;
+        *have = interp;
+    }
+    *later = !exact && *have > 1.1 * aim && native_pays(c, span, *have, patterns);
+    return k;
 }
 
 // Builds a native kernel on a thread of its own.
@@ -195,23 +197,26 @@ int interrupted(const fastlec_es_options& o, double t_start) {
     return FASTLEC_OK;
 }
 
-// The beginning of a check of `full` on the interpreter, in ascending pieces of about half a
-// millisecond, while the native kernel for checks of `span` half-words is built: a counterexample that lies
-// there is found without the kernel (MAC8, words 12345677 to 54321011 with the first difference 1 ms into
-// them: 1.9 ms in place of 8.4), and otherwise the device has not waited.  Ends with the kernel (null if
-// there can be none), or with a pattern in *best, or at the end, or interrupted (*status); *lo = first
-// half-word not covered.  In the caller's device memory nothing is interpreted meanwhile: that may need more
-// of it than the kernel.  What is spent on the interpreter counts towards the kernel, as in native_pays: a
-// circuit whose checks keep ending early gets it once they have taken as long as building it.
+// The beginning of a check of `full` on the interpreter, or on the kernel `now` (made for other spans), in
+// ascending pieces of about half a millisecond of the total_ms that it would take there, while the native
+// kernel for checks of `span` half-words is built: a counterexample that lies there is found without the
+// kernel (MAC8, words 12345677 to 54321011 with the first difference 1 ms into them: 1.9 ms in place of 8.4),
+// and otherwise the device has not waited.  Ends with the kernel (`now` if there can be none), or with a pattern
+// in *best, or at the end, or interrupted (*status); *lo = first half-word not covered.  In the caller's device
+// memory nothing is interpreted meanwhile: that may need more of it than the kernel.  What is spent
+// counts towards the kernel, as in native_pays: a circuit whose checks keep ending early gets it once they
+// have taken as long as building it.
 std::shared_ptr<JitKernel> check_while_building(Device& dev, Circuit& c, const fastlec_es_options& o,
                                                 const HwRange& full, uint64_t span, double t_start,
-                                                hipStream_t stream, uint64_t* lo, uint64_t* best, double* kernel_ms,
+                                                hipStream_t stream, const std::shared_ptr<JitKernel>& now,
+                                                double total_ms, uint64_t* lo, uint64_t* best, double* kernel_ms,
                                                 int* status) {
     *status = interrupted(o, t_start);
-    if (*status != FASTLEC_OK) return nullptr;
-    const double patterns = 32.0 * (double)(full.end - full.begin), build_ms = native_tier()->guess_build_ms(c) + 1.0;
+    if (*status != FASTLEC_OK) return now;
+    const double build_ms = native_tier()->guess_build_ms(c) + 1.0;
+    const bool wait_only = o.dev_scratch && !now;
     // A kernel that would come after the deadline is not started.
-    if (o.deadline_s > 0 && !o.dev_scratch && now_ms() - t_start + 1.5 * build_ms > o.deadline_s * 1e3) return nullptr;
+    if (o.deadline_s > 0 && !wait_only && now_ms() - t_start + 1.5 * build_ms > o.deadline_s * 1e3) return now;
     NativeBuilder b(c, span);
     const double t0 = now_ms();
     auto built = [&] { return b.done.load(std::memory_order_acquire); };
@@ -219,33 +224,38 @@ std::shared_ptr<JitKernel> check_while_building(Device& dev, Circuit& c, const f
         while (!built() && (*status = interrupted(o, t_start)) == FASTLEC_OK)
             std::this_thread::sleep_for(std::chrono::microseconds(50));
     };
-    if (o.dev_scratch) {
+    if (wait_only) {
         wait();
     } else {
         std::vector<Circuit*> one{&c};
-        const double total = model_interp_ms(c.interp_gates(), c.interp_rows(), patterns);
-        const uint64_t want = (uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total));
+        const uint64_t want = (uint64_t)((double)(full.end - full.begin) * std::min(1.0, 0.5 / total_ms));
         const uint64_t piece = std::max<uint64_t>(1, (want + 4095) / 4096) * 4096;  // a half-word may take longer
-        Schedule sch = default_schedule(dev, one, &o, std::min(piece, full.end - full.begin));
-        if (o.tile_words) sch.tile_hw = 2ull * o.tile_words;
+        const uint64_t tile = 2ull * o.tile_words;
+        const DevMem mem{o.dev_scratch, o.dev_scratch ? o.dev_scratch_bytes : 0};
+        Schedule sch;
+        if (!now) sch = default_schedule(dev, one, &o, std::min(piece, full.end - full.begin));
+        if (tile) sch.tile_hw = tile;
         while (*lo < full.end && *best == ~0ull && !built() && (*status = interrupted(o, t_start)) == FASTLEC_OK) {
             const uint64_t end = std::min(full.end, *lo + piece);
-            std::vector<uint64_t> found;
+            std::vector<uint64_t> found{~0ull};
             double ms = 0;
-            run_interp(dev, one, {HwRange{*lo, end}}, sch, stream, nullptr, found, &ms);
+            if (now) run_jit(dev, c, *now, HwRange{*lo, end}, tile, stream, nullptr, &found[0], &ms, mem);
+            else run_interp(dev, one, {HwRange{*lo, end}}, sch, stream, nullptr, found, &ms);
             *kernel_ms += ms;
             *best = found[0];
             *lo = end;
         }
         if (*lo == full.end || *best != ~0ull) {
-            const double here = now_ms() - t0, spent = c.interp_ms_spent.load(std::memory_order_relaxed);
-            if (spent + here > 1.5 * build_ms) wait();
-            else c.interp_ms_spent.store(spent + here, std::memory_order_relaxed);
+            const double here = now_ms() - t0;
+            if (c.interp_ms_spent.load(std::memory_order_relaxed) + here > 1.5 * build_ms) wait();
+            else note_spent(c, here);
             *status = FASTLEC_OK;  // the answer is there
-            return nullptr;
+            return now;
         }
     }
-    return *status == FASTLEC_OK ? b.result() : nullptr;
+    if (*status != FASTLEC_OK) return now;
+    auto k = b.result();
+    return k ? k : now;
 }
 
 void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) {
@@ -265,11 +275,14 @@ void check_one(Circuit& c, const fastlec_es_options& o, fastlec_es_result* out) 
     double compile_ms = 0;
     bool build = false;
     const uint64_t span = std::min(chunk, full.end - full.begin);
-    std::shared_ptr<JitKernel> jk = native_kernel(c, o, full, span, &build);
+    double now_takes = 0;
+    std::shared_ptr<JitKernel> jk = native_kernel(c, o, full, span, &build, &now_takes);
     double kernel_ms = 0;
     uint64_t best = ~0ull, first = full.begin;
     int status = FASTLEC_OK;
-    if (build) jk = check_while_building(dev, c, o, full, span, t_start, stream, &first, &best, &kernel_ms, &status);
+    if (build)
+        jk = check_while_building(dev, c, o, full, span, t_start, stream, jk, now_takes, &first, &best, &kernel_ms,
+                                  &status);
     const bool native = jk != nullptr;
     const bool more = status == FASTLEC_OK && first < full.end && best == ~0ull;
     const bool spec = native || (more && use_specialized(c, o, full));
@@ -431,65 +444,60 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                                  (o.kernel == FASTLEC_KERNEL_AUTO && !o.words_per_thread && !o.wg_size &&
                                   batch_jit_mode() == 1))) {
             const NativeTier* t = native_tier();
-            std::vector<size_t> want;
-            if (o.kernel == FASTLEC_KERNEL_SPECIALIZED) {
-                for (size_t i = 0; i < k; ++i) want.push_back(i);
-            } else {
-                // A cone's gain is its share of a grouped interpreter launch against its share of a
-                // native one; where the interpreter's stream is not planned yet, that planning
-                // (about as long as building a kernel) is saved too.  Building and planning run on
-                // all host threads.  A module load on top has to be paid by all new kernels together.
-                const double threads = (double)std::min<size_t>({k, 16, std::max(1u, std::thread::hardware_concurrency())});
-                double gain = 0;
-                std::vector<size_t> fresh;
-                std::vector<double> fresh_ms;
-                for (size_t i = 0; i < k; ++i) {
-                    Circuit& c = *v[i];
-                    const uint64_t span = rs[i].end - rs[i].begin;
-                    const double patterns = 32.0 * (double)span;
-                    const double interp = model_interp_share_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
-                    if (const std::shared_ptr<JitKernel> have = t->ready(c, span)) {
-                        if (t->share_ms(*have, patterns) < interp) want.push_back(i);
-                        continue;
-                    }
-                    if (t->refused(c, span, kBatchBuildWeight)) continue;
-                    const double plan = c.planned(4) ? 0.0 : kPlanMsPerGate * c.plan1.num_ands_tfi;
-                    const double net = interp + c.interp_ms_spent.load(std::memory_order_relaxed) +
-                                       (plan - 1.5 * t->guess_build_ms(c)) / threads;
-                    fresh.push_back(i);
-                    fresh_ms.push_back(interp);
-                    if (net > 0) gain += net;
-                    else fresh_ms.back() = -interp;  // not this one
-                }
-                for (size_t j = 0; j < fresh.size(); ++j) {
-                    Circuit& c = *v[fresh[j]];
-                    if (gain > kLoadMs && fresh_ms[j] > 0) {
-                        want.push_back(fresh[j]);
-                        continue;
-                    }
-                    double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
-                    while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + std::abs(fresh_ms[j]),
-                                                                    std::memory_order_relaxed)) {
-                    }
-                }
-                std::sort(want.begin(), want.end());
-            }
             const bool forced = o.kernel == FASTLEC_KERNEL_SPECIALIZED;
-            std::vector<std::shared_ptr<JitKernel>> got(want.size());
+            // A cone's gain is its share of a grouped interpreter launch (or of one on a kernel made for other
+            // spans) against its share of a native one; where the interpreter's stream is not planned yet,
+            // that planning (about as long as building a kernel) is saved too.  Building and planning run
+            // on all host threads.  A module load on top has to be paid by all new kernels together.
+            const double threads = (double)std::min<size_t>({k, 16, std::max(1u, std::thread::hardware_concurrency())});
+            struct Fresh {
+                size_t entry;
+                double ms;  // what it costs in this call without its kernel
+                bool pays;
+            };
+            double gain = 0;
+            std::vector<Fresh> fresh;
+            std::vector<std::shared_ptr<JitKernel>> got(k);
             std::vector<size_t> build;
-            for (size_t j = 0; j < want.size(); ++j) {
-                got[j] = t->ready(*v[want[j]], rs[want[j]].end - rs[want[j]].begin);
-                if (!got[j]) build.push_back(j);
+            for (size_t i = 0; i < k; ++i) {
+                Circuit& c = *v[i];
+                const uint64_t span = rs[i].end - rs[i].begin;
+                const double patterns = 32.0 * (double)span;
+                double ms = 0, aim = 0;
+                const std::shared_ptr<JitKernel> have = t->best(c, rs[i], span, &ms, &aim);
+                const bool exact = have && aim >= ms;
+                if (forced) {
+                    got[i] = have;
+                    if (!have || (!exact && native_pays(c, span, t->share_ms(*have, patterns), patterns))) build.push_back(i);
+                    continue;
+                }
+                double now = model_interp_share_ms(c.interp_gates(), c.interp_rows_guess(), patterns);
+                double plan = c.planned(4) ? 0.0 : kPlanMsPerGate * c.plan1.num_ands_tfi;
+                if (have && t->share_ms(*have, patterns) < now) {
+                    got[i] = have;
+                    now = t->share_ms(*have, patterns);
+                    plan = 0;
+                }
+                if (exact || t->refused(c, span, kBatchBuildWeight)) continue;
+                const double net = now + c.interp_ms_spent.load(std::memory_order_relaxed) +
+                                   (plan - 1.5 * t->guess_build_ms(c)) / threads;
+                if (net > 0) gain += net;
+                fresh.push_back({i, now, net > 0});
+            }
+            for (const Fresh& f : fresh) {
+                if (gain > kLoadMs && f.pays) build.push_back(f.entry);
+                else note_spent(*v[f.entry], f.ms);
             }
             parallel_for(build.size(), [&](size_t b) {
-                const size_t j = build[b];
-                got[j] = t->get(*v[want[j]], rs[want[j]].end - rs[want[j]].begin, forced ? 0.0 : kBatchBuildWeight, nullptr);
+                const size_t i = build[b];
+                auto made = t->get(*v[i], rs[i].end - rs[i].begin, forced ? 0.0 : kBatchBuildWeight, nullptr);
+                if (made) got[i] = made;
             });
-            for (size_t j = 0; j < want.size(); ++j) {
-                if (!got[j]) continue;  // its values fit neither registers nor LDS
-                is_nat[want[j]] = 1;
-                nat.push_back(want[j]);
-                nk.push_back(got[j]);
+            for (size_t i = 0; i < k; ++i) {
+                if (!got[i]) continue;  // none, or its values fit neither registers nor LDS
+                is_nat[i] = 1;
+                nat.push_back(i);
+                nk.push_back(got[i]);
             }
         }
         // The interpreter's streams of the others, planned and encoded on host threads.

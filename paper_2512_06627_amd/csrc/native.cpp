@@ -34,16 +34,11 @@ uint32_t inner_limit(const Circuit& c, uint64_t span) {
 
 double passes_of(double patterns) { return std::max(1.0, patterns / 2048.0); }
 
-std::shared_ptr<JitKernel> find(Circuit& c, uint64_t span, bool exact) {
-    const uint32_t limit = inner_limit(c, span);
+std::shared_ptr<JitKernel> ready(Circuit& c, uint64_t span) {
     std::lock_guard<std::mutex> g(c.mu);
-    auto it = c.native.upper_bound(limit);
-    if (it == c.native.begin()) return nullptr;
-    --it;
-    return exact && it->first != limit ? nullptr : it->second;
+    auto it = c.native.find(inner_limit(c, span));
+    return it == c.native.end() ? nullptr : it->second;
 }
-
-std::shared_ptr<JitKernel> ready(Circuit& c, uint64_t span) { return find(c, span, false); }
 
 // A build that found no choice of inner inputs to fit is not repeated: native_refused holds its limit, with
 // true when every choice was tried (weight 0; a build that weighs its own time tries a few).  Such a
@@ -55,7 +50,7 @@ bool refused(Circuit& c, uint64_t span, double weight) {
 }
 
 std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop) {
-    if (auto k = find(c, span, true)) return k;
+    if (auto k = ready(c, span)) return k;
     if (refused(c, span, weight)) return nullptr;
     std::unique_lock<std::mutex> build(c.native_mu, std::defer_lock);
     while (stop && !build.try_lock()) {  // another thread's build of this circuit
@@ -63,7 +58,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const s
         std::this_thread::sleep_for(std::chrono::microseconds(50));
     }
     if (!stop) build.lock();
-    if (auto k = find(c, span, true)) return k;
+    if (auto k = ready(c, span)) return k;
     if (refused(c, span, weight)) return nullptr;
     const uint32_t limit = inner_limit(c, span);
     const double patterns = 32.0 * (double)span;
@@ -77,6 +72,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const s
         std::lock_guard<std::mutex> g(c.mu);
         bool& all = c.native_refused[limit];
         all = all || weight <= 0;
+        c.interp_ms_spent.store(0, std::memory_order_relaxed);  // it has bought this
         return nullptr;
     }
     auto k = std::make_shared<JitKernel>();
@@ -91,6 +87,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const s
           n->bits.size(), n->code.valu, n->code.lds, n->waves, n->build_ms);
     std::lock_guard<std::mutex> g(c.mu);
     c.native[limit] = k;
+    c.interp_ms_spent.store(0, std::memory_order_relaxed);
     return k;
 }
 
@@ -99,19 +96,22 @@ double run_ms(const JitKernel& k, double patterns) {
     return 0.003 + native_run_ms(n.code.valu + n.code.lds, (uint32_t)n.bits.size(), passes_of(patterns));
 }
 
-std::shared_ptr<JitKernel> best(Circuit& c, const HwRange& r, double* ms, bool* fits) {
-    const uint32_t limit = inner_limit(c, r.end - r.begin);
+std::shared_ptr<JitKernel> best(Circuit& c, const HwRange& r, uint64_t span, double* ms, double* aim) {
+    const uint32_t limit = inner_limit(c, span);
+    const uint64_t size = r.end - r.begin, pieces = span < size ? (size + span - 1) / span : 1;
     std::shared_ptr<JitKernel> pick;
     std::lock_guard<std::mutex> g(c.mu);
     for (auto& kv : c.native) {
-        // A range is covered in whole blocks of patterns up to the highest inner input.
+        // A range is covered in whole blocks of patterns up to the highest inner input, a piece of it with
+        // about one block too many.
         const uint32_t block = kv.second->native->bits.empty() ? 0 : kv.second->native->bits.back() + 1;
-        const uint64_t covered = (((r.end + ((1ull << block) - 1)) >> block) - (r.begin >> block)) << block;
+        const uint64_t covered = pieces > 1 ? size + (block ? pieces << block : 0)
+                                            : (((r.end + ((1ull << block) - 1)) >> block) - (r.begin >> block)) << block;
         const double t = run_ms(*kv.second, 32.0 * (double)covered);
         if (pick && t >= *ms) continue;
         pick = kv.second;
         *ms = t;
-        *fits = kv.first == limit;
+        *aim = kv.first == limit ? t : kv.first > limit ? run_ms(*kv.second, 32.0 * (double)size) : 0.0;
     }
     return pick;
 }

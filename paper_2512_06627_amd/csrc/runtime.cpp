@@ -70,16 +70,20 @@ const NativeTier* native_tier() {
     return on ? g_native_tier : nullptr;
 }
 
+void note_spent(Circuit& c, double ms) {
+    double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
+    while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + ms, std::memory_order_relaxed)) {
+    }
+}
+
 bool native_pays(Circuit& c, uint64_t span, double interp_ms, double patterns) {
     const NativeTier* t = native_tier();
     if (!t || t->refused(c, span, 1.0)) return false;
     // Margin on the building: its estimate is good to about a factor of 1.5.  A module load takes
     // 0.6 to 1.3 ms.
     const double cost = t->guess_run_ms(c, patterns) + 1.5 * (t->guess_build_ms(c) + 1.0);
-    double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
-    if (interp_ms + spent > cost) return true;
-    while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + interp_ms, std::memory_order_relaxed)) {
-    }
+    if (interp_ms + c.interp_ms_spent.load(std::memory_order_relaxed) > cost) return true;
+    note_spent(c, interp_ms);
     return false;
 }
 

@@ -379,7 +379,7 @@ void native_many_enqueue(const NativeMany& m, hipStream_t stream);
 // of planning and a module load, not a compile.  The library links the tier; host-only builds of
 // its sources do without it (native_tier() is then null) and use the interpreter and hipRTC kernels.
 struct NativeTier {
-    // The circuit's kernel for checks that cover `span` half-words at a time of its space, if one is
+    // The circuit's kernel for checks that cover `span` half-words at a time of its space, if that one is
     // built (get: build it if not; null when the circuit's values fit neither registers nor LDS).
     // `weight`: what a millisecond of building costs against one of kernel time.  `stop`: set by another
     // thread to give the building up (null then, too).
@@ -387,9 +387,10 @@ struct NativeTier {
     std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop);
     // Whether get() is known to return null for this span.
     bool (*refused)(Circuit& c, uint64_t span, double weight);
-    // The built kernel that is expected to be fastest over `r`, whichever spans it was built for (*ms: its
-    // time there, *fits: whether get() would return it); null when none is built.
-    std::shared_ptr<JitKernel> (*best)(Circuit& c, const HwRange& r, double* ms, bool* fits);
+    // The built kernel that is expected to be fastest over `r` in pieces of `span` half-words, whichever spans
+    // it was built for; null when none is built.  *ms: its time there; *aim: what the kernel for this span could
+    // take, *ms itself when it is that one, 0 when that one may share more work.
+    std::shared_ptr<JitKernel> (*best)(Circuit& c, const HwRange& r, uint64_t span, double* ms, double* aim);
     // Expected kernel time over `patterns` patterns, and of get() for a circuit without one (the
     // module load on the first launch not included).
     double (*run_ms)(const JitKernel& k, double patterns);
@@ -405,12 +406,14 @@ void register_native_tier(const NativeTier* t);
 using SimRunner = bool (*)(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32_t* sig,
                            hipStream_t stream, double* kernel_ms);
 void register_sim_runner(SimRunner r);
-// Whether a native kernel pays for a circuit that has none: the interpreter's time for this check
-// plus what the interpreter has already taken for this circuit exceeds the native kernel's time
-// and its building.  A circuit checked again and again thus spends at most about twice the better
+// Whether a native kernel pays for a circuit that has none for this span: the time of this check without it
+// (interp_ms: on the interpreter, or on a kernel made for other spans) plus what such checks of this circuit
+// have already taken since its last kernel exceeds the kernel's time and its building.  A circuit checked again and again thus spends at most about twice the better
 // of the two; one checked once is built only when that check alone pays.  Never for a span that get()
 // is known to refuse.
 bool native_pays(Circuit& c, uint64_t span, double interp_ms, double patterns);
+// Adds to what checks of the circuit have taken without the kernel that they would have.
+void note_spent(Circuit& c, double ms);
 
 // The per-pass body as one asm statement with planner-assigned registers (v0.., s<sgpr_base>..).
 // Returns false, with the register counts in stats, when it needs more than the limits.

@@ -233,18 +233,27 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
         if (j->jit || j->compile_queued) continue;
         const double left = 32.0 * (double)(j->range.end - j->cursor);
         const NativeTier* nt = native_tier();
-        if (nt)
-            if (auto k = nt->ready(*j->c, slice_span(*j->c))) {
-                // Its launch is its own, while the jobs on the interpreter share one: 28 jobs of 16 to 20
-                // inputs took 175 us of a step as launches of native kernels, 95 together.
-                const double alone = model_interp_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
-                const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
-                const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
-                if (nt->run_ms(*k, left) + kLaunchMs < plan + std::max(share, alone / (double)act.size())) j->jit = k;
-                continue;
+        double have = 0, aim = 0;
+        std::shared_ptr<JitKernel> k;
+        if (nt) k = nt->best(*j->c, HwRange{j->cursor, j->range.end}, slice_span(*j->c), &have, &aim);
+        if (k) {
+            // Its launch is its own, while the jobs on the interpreter share one: 28 jobs of 16 to 20
+            // inputs took 175 us of a step as launches of native kernels, 95 together.
+            const double alone = model_interp_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
+            const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
+            const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
+            if (have + kLaunchMs < plan + std::max(share, alone / (double)act.size())) j->jit = k;
+            if (aim >= have) continue;
+            // One made for other spans runs the job until it has its own, if that pays.
+            if (jit_mode == 1 && j->jit && native_pays(*j->c, slice_span(*j->c), have, left)) {
+                j->compile_queued = true;
+                compile_queue.push_back(j);
+                cv_compile.notify_one();
             }
-        if (auto k = jit_ready(*j->c, specialized_waves_per_eu())) {
-            j->jit = k;
+            if (j->jit) continue;
+        }
+        if (auto rtc = jit_ready(*j->c, specialized_waves_per_eu())) {
+            j->jit = rtc;
             continue;
         }
         // A native kernel takes milliseconds to build, on a compile thread, while the job keeps

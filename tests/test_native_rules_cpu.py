@@ -170,3 +170,32 @@ for i in range(150):  # more than a kernel's building on the interpreter
 for kernel in ("auto", "interp", "specialized"):
     assert all(map(same, es.fastlec_es_check_batch(fresh, kernel=kernel), want)), kernel
 """, LD_PRELOAD=str(pre))
+
+
+@pytest.mark.parametrize("call", ["auto", "specialized", "batch", "batch_specialized"])
+def test_a_kernel_made_for_a_few_words_does_not_stay(lib, call):
+    """A 14x14 multiplier miter (with the first pattern failing, so that a check is quick) checked over two words
+    first, on a kernel without inner inputs; checks of its whole space have their own kernel built, once, when by
+    the model they have paid for it."""
+    r = run(lib, """
+call = %r
+g = miters.Aig(28)
+for o in miters.import_into(g, miters.mult_miter(14, "booth")):
+    g.add_output(o)
+g.add_output(g.input(0) ^ 1)
+c = load(g)
+kernel = "specialized" if "specialized" in call else "auto"
+for _ in range(3):
+    es.fastlec_es_check(c, kernel="specialized", end_word=2)
+print("whole", file=sys.stderr, flush=True)
+for _ in range(300):
+    if "batch" in call:
+        r = es.fastlec_es_check_batch([c], kernel=kernel)[0]
+    else:
+        r = es.fastlec_es_check(c, kernel=kernel)
+    assert r["verdict"] == 1 and r["cex"] == 0, r
+""" % call)
+    before, after = r.stderr.split("whole")
+    made = [ln.split("native: ")[1] for ln in after.splitlines() if "inner inputs" in ln]
+    assert "native: 0 inner inputs" in before, before[-2000:]
+    assert len(made) == 1, (made, after[-2000:])
