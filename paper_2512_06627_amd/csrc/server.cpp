@@ -50,7 +50,8 @@ struct Job {
     fastlec_es_result res{};
     bool compile_queued = false;     // handed to the compile threads
     bool compiling = false;          // a compile thread is using the circuit
-    bool no_kernel = false;          // the compile threads found none that fits
+    bool no_native = false;          // the compile threads found no native kernel that fits
+    bool compile_rtc = false;        // queued for a hipRTC kernel, not for a native one
     std::shared_ptr<JitKernel> jit;  // set when the specialized kernel is ready
 };
 
@@ -125,11 +126,20 @@ struct fastlec_es_server {
     std::deque<Job*> compile_queue;
     std::condition_variable cv_compile;
     std::vector<std::thread> compilers;
+    size_t num_compilers = 0, in_rtc = 0;  // compile threads, and those that are in hipRTC (0.1 s and more)
     void compile_loop();
     // A job whose native kernel is being built runs on the interpreter meanwhile only if its stream is
-    // already planned: planning takes about as long as building.  Call with mu held.
+    // already planned, since planning takes about as long as building, or if it would wait for a hipRTC
+    // compile.  Call with mu held.
     bool awaits_kernel(Job* j) const {
-        return jit_mode == 1 && native_tier() && j->compile_queued && !j->jit && !j->no_kernel && !j->c->planned(4);
+        return jit_mode == 1 && native_tier() && j->compile_queued && !j->compile_rtc && !j->jit &&
+               (j->compiling || in_rtc < num_compilers) && !j->c->planned(4);
+    }
+    void queue_compile(Job* j, bool rtc) {
+        j->compile_queued = true;
+        j->compile_rtc = rtc;
+        compile_queue.push_back(j);
+        cv_compile.notify_one();
     }
     void plan_tiers(const std::vector<Job*>& act);
 
@@ -179,46 +189,66 @@ void fastlec_es_server::compile_loop() {
             }
             if (group.empty()) continue;
         }
-        std::vector<Circuit*> cs;
-        for (Job* j : group) cs.push_back(j->c);
-        std::vector<std::shared_ptr<JitKernel>> ks;
-        try {
-            if (const NativeTier* t = native_tier())
-                for (Circuit* c : cs) ks.push_back(t->get(*c, slice_span(*c), kServerBuildWeight, nullptr));
-            else ks.assign(cs.size(), nullptr);
-            // what has no native kernel is compiled
-            std::vector<Circuit*> rest;
-            std::vector<size_t> at;
-            for (size_t t = 0; t < cs.size(); ++t)
-                if (!ks[t]) {
-                    rest.push_back(cs[t]);
-                    at.push_back(t);
-                }
-            if (!rest.empty()) {
-                const auto compiled = jit_kernels(rest, specialized_waves_per_eu(), nullptr,
-                                                  helpers ? CompileSplit::kEach : CompileSplit::kGroup);
-                for (size_t r = 0; r < rest.size(); ++r) ks[at[r]] = compiled[r];
-            }
-        } catch (...) {
-            // one kernel that does not compile must not keep the others on the interpreter
-            ks.assign(group.size(), nullptr);
-            for (size_t t = 0; t < group.size(); ++t) {
-                try {
-                    ks[t] = jit_kernel(*cs[t], specialized_waves_per_eu(), nullptr);
-                } catch (...) {
-                    ks[t] = nullptr;  // the job stays on the interpreter
-                }
-            }
-        }
-        std::lock_guard<std::mutex> g(mu);
-        for (size_t t = 0; t < group.size(); ++t) {
+        const size_t n = group.size();
+        std::vector<std::shared_ptr<JitKernel>> ks(n);
+        auto publish = [&](size_t t) {  // with mu held; the job runs on, with its kernel or without
             Job* j = group[t];
             j->compiling = false;
             if (ks[t] && ks[t]->code && !j->done) j->jit = ks[t];
-            else j->no_kernel = true;
+        };
+        // Native kernels first: the job goes on at once, also where there is none.  Whether a hipRTC
+        // kernel pays then is for the next step to say (plan_tiers).
+        std::vector<size_t> rest;
+        if (const NativeTier* nt = native_tier())
+            for (size_t t = 0; t < n; ++t) {
+                if (group[t]->compile_rtc) continue;
+                try {
+                    ks[t] = nt->get(*group[t]->c, slice_span(*group[t]->c), kServerBuildWeight, nullptr);
+                } catch (...) {
+                }
+            }
+        {
+            std::lock_guard<std::mutex> g(mu);
+            for (size_t t = 0; t < n; ++t) {
+                Job* j = group[t];
+                if (!ks[t]) {
+                    if (!j->compile_rtc) j->no_native = true;
+                    if (j->compile_rtc || jit_mode == 2) {
+                        rest.push_back(t);
+                        continue;
+                    }
+                    j->compile_queued = false;
+                }
+                publish(t);
+            }
+            if (!rest.empty()) ++in_rtc;
         }
         cv_done.notify_all();
         cv_work.notify_all();  // a step may be waiting for these kernels
+        if (rest.empty()) continue;
+        std::vector<Circuit*> cs;
+        for (size_t t : rest) cs.push_back(group[t]->c);
+        try {
+            const auto compiled = jit_kernels(cs, specialized_waves_per_eu(), nullptr,
+                                              helpers ? CompileSplit::kEach : CompileSplit::kGroup);
+            for (size_t r = 0; r < rest.size(); ++r) ks[rest[r]] = compiled[r];
+        } catch (...) {
+            // one kernel that does not compile must not keep the others on the interpreter
+            for (size_t r = 0; r < rest.size(); ++r) {
+                try {
+                    ks[rest[r]] = jit_kernel(*cs[r], specialized_waves_per_eu(), nullptr);
+                } catch (...) {
+                    ks[rest[r]] = nullptr;  // the job stays on the interpreter
+                }
+            }
+        }
+        {
+            std::lock_guard<std::mutex> g(mu);
+            for (size_t t : rest) publish(t);
+            --in_rtc;
+        }
+        cv_done.notify_all();
+        cv_work.notify_all();
     }
 }
 
@@ -245,11 +275,7 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
             if (have + kLaunchMs < plan + std::max(share, alone / (double)act.size())) j->jit = k;
             if (aim >= have) continue;
             // One made for other spans runs the job until it has its own, if that pays.
-            if (jit_mode == 1 && j->jit && native_pays(*j->c, slice_span(*j->c), have, left)) {
-                j->compile_queued = true;
-                compile_queue.push_back(j);
-                cv_compile.notify_one();
-            }
+            if (jit_mode == 1 && j->jit && native_pays(*j->c, slice_span(*j->c), have, left)) queue_compile(j, false);
             if (j->jit) continue;
         }
         if (auto rtc = jit_ready(*j->c, specialized_waves_per_eu())) {
@@ -257,15 +283,12 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
             continue;
         }
         // A native kernel takes milliseconds to build, on a compile thread, while the job keeps
-        // running on the interpreter.
-        if (nt && jit_mode == 1) {
+        // running on the interpreter; where there is none the rule for hipRTC kernels below holds.
+        if (nt && jit_mode == 1 && !j->no_native && !nt->refused(*j->c, slice_span(*j->c), kServerBuildWeight)) {
             const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
             const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
-            if (native_pays(*j->c, slice_span(*j->c), plan + share * (double)std::max<size_t>(1, sharing), left)) {
-                j->compile_queued = true;
-                compile_queue.push_back(j);
-                cv_compile.notify_one();
-            }
+            if (native_pays(*j->c, slice_span(*j->c), plan + share * (double)std::max<size_t>(1, sharing), left))
+                queue_compile(j, false);
             continue;
         }
         // The runtime model's rule: remaining interpreter time at this job's share against the
@@ -283,11 +306,7 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
             tj.lut_steps = j->c->lut_steps_known();
             want = server_wants_compile(tj, sharing, nullptr, nullptr);
         }
-        if (jit_mode == 2 || want) {
-            j->compile_queued = true;
-            compile_queue.push_back(j);
-            cv_compile.notify_one();
-        }
+        if (jit_mode == 2 || want) queue_compile(j, jit_mode != 2);
     }
 }
 
@@ -647,8 +666,9 @@ int fastlec_es_server_create(const fastlec_es_options* opts, size_t budget_bytes
         for (uint32_t i = kCapacity; i-- > 0;) s->free_slots.push_back(i);
         s->st.budget_bytes = budget_bytes;
         fastlec_es_server* raw = s.get();
+        s->num_compilers = (size_t)std::max(1, compile_helpers());
         s->th = std::thread([raw] { raw->loop(); });
-        for (int t = 0, n = std::max(1, compile_helpers()); t < n; ++t)
+        for (size_t t = 0; t < raw->num_compilers; ++t)
             s->compilers.emplace_back([raw] { raw->compile_loop(); });
         *out = s.release();
         return FASTLEC_OK;

@@ -199,3 +199,24 @@ for _ in range(300):
     made = [ln.split("native: ")[1] for ln in after.splitlines() if "inner inputs" in ln]
     assert "native: 0 inner inputs" in before, before[-2000:]
     assert len(made) == 1, (made, after[-2000:])
+
+
+def test_server_jobs_without_native_kernel_are_interpreted(lib):
+    """Jobs of a cone for which no native kernel fits: eight at a time are by the model worth a native kernel (its
+    first pattern fails, which the model does not know) and not a hipRTC compile, so none is compiled and all
+    run on the interpreter."""
+    r = run(lib, """
+g = miters.Aig(24)
+for o in miters.import_into(g, miters.layered_cone_miter(3, 24, 60000)):
+    g.add_output(o)
+g.add_output(g.input(0) ^ 1)
+cs = [load(g) for _ in range(8)]
+srv = es.Server(1 << 36)
+res = [srv.poll(t, wait=True) for t in [srv.submit(c) for c in cs]]
+assert all((x["verdict"], x["cex"]) == (1, 0) for x in res), res
+st = srv.stats()
+print(st)
+assert st["specialized_slices"] == 0 and st["completed"] == 8, st
+srv.close()
+""")
+    assert "native: no kernel" in r.stderr, r.stderr[-2000:]
