@@ -543,8 +543,10 @@ void fastlec_es_server::loop() {
         for (;;) {
             std::vector<Job*> act;
             std::vector<uint32_t> fresh;
+            uint64_t submitted = 0;  // jobs that this admission has looked at
             {
                 std::unique_lock<std::mutex> g(mu);
+                submitted = st.submitted;
                 // Admission: first fit in arrival order, unless the oldest job has waited
                 // more than two seconds, in which case nothing may pass it.
                 const double now = now_ms();
@@ -596,9 +598,9 @@ void fastlec_es_server::loop() {
                 std::vector<Job*> now;
                 for (Job* j : act)
                     if (!awaits_kernel(j)) now.push_back(j);
-                if (now.empty()) {
+                if (now.empty()) {  // a queued job that found no room finds none before one of these has run
                     cv_work.wait(g, [&] {
-                        if (stop || !queue.empty()) return true;
+                        if (stop || st.submitted != submitted) return true;
                         for (Job* j : act)
                             if (!awaits_kernel(j)) return true;
                         return false;

@@ -220,3 +220,28 @@ assert st["specialized_slices"] == 0 and st["completed"] == 8, st
 srv.close()
 """)
     assert "native: no kernel" in r.stderr, r.stderr[-2000:]
+
+
+def test_server_waits_for_a_kernel_without_spinning(lib):
+    """One job waits for its kernel (0.2 s of building) while another finds no room in the budget: the server's
+    loop sleeps, and the process takes the time of one thread that builds."""
+    run(lib, """
+def first_fails(seed):
+    g = miters.Aig(32)
+    for o in miters.import_into(g, chain(60000 + seed, 32)):
+        g.add_output(o)
+    g.add_output(g.input(0) ^ 1)
+    return load(g)
+a, b = first_fails(0), first_fails(1)
+charge = first_fails(0).info()["peak_live_slots"] * (1 << 22) * 8  # info() plans the interpreter's stream
+srv = es.Server(charge + charge // 2)
+cpu, wall = time.process_time(), time.perf_counter()
+t = [srv.submit(a), srv.submit(b)]
+assert srv.poll(t[0], wait=True)["cex"] == 0
+cpu, wall = time.process_time() - cpu, time.perf_counter() - wall
+print(cpu, wall)
+assert srv.poll(t[1], wait=True)["cex"] == 0
+assert srv.stats()["max_active"] == 1
+assert cpu < 1.4 * wall + 0.02, (cpu, wall)
+srv.close()
+""")
