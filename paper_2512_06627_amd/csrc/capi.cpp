@@ -148,8 +148,12 @@ std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o
             k = nullptr;
             *have = by_rtc;
         }
-        if (*have > 1.1 * aim && native_pays(c, span, *have, patterns))
+        if (*have <= 1.1 * aim) return k;
+        if (native_pays(c, span, *have, patterns)) {
             if (auto built = t->get(c, span, 0.0, nullptr)) return built;
+        } else {
+            note_spent(c, *have);
+        }
         return k;
     }
     if (o.words_per_thread || o.wg_size) return nullptr;
@@ -158,7 +162,9 @@ std::shared_ptr<JitKernel> native_kernel(Circuit& c, const fastlec_es_options& o
         k = nullptr;
         *have = interp;
     }
-    *later = !exact && *have > 1.1 * aim && native_pays(c, span, *have, patterns);
+    if (exact || *have <= 1.1 * aim) return k;
+    *later = native_pays(c, span, *have, patterns);
+    if (!*later) note_spent(c, *have);
     return k;
 }
 
@@ -468,7 +474,9 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                 const bool exact = have && aim >= ms;
                 if (forced) {
                     got[i] = have;
-                    if (!have || (!exact && native_pays(c, span, t->share_ms(*have, patterns), patterns))) build.push_back(i);
+                    const double share = have ? t->share_ms(*have, patterns) : 0.0;
+                    if (!have || (!exact && native_pays(c, span, share, patterns))) build.push_back(i);
+                    else if (!exact) note_spent(c, share);
                     continue;
                 }
                 double now = model_interp_share_ms(c.interp_gates(), c.interp_rows_guess(), patterns);

@@ -43,7 +43,7 @@ std::shared_ptr<JitKernel> ready(Circuit& c, uint64_t span) {
 // A build that found no choice of inner inputs to fit is not repeated: native_refused holds its limit, with
 // true when every choice was tried (weight 0; a build that weighs its own time tries a few).  Such a
 // build is as long as one that succeeds: 27,000 gates 28 ms, for a check of 0.3 ms on the interpreter.
-bool refused(Circuit& c, uint64_t span, double weight) {
+bool refused(const Circuit& c, uint64_t span, double weight) {
     std::lock_guard<std::mutex> g(c.mu);
     auto it = c.native_refused.find(inner_limit(c, span));
     return it != c.native_refused.end() && (weight > 0 || it->second);

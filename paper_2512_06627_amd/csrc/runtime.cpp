@@ -76,15 +76,13 @@ void note_spent(Circuit& c, double ms) {
     }
 }
 
-bool native_pays(Circuit& c, uint64_t span, double interp_ms, double patterns) {
+bool native_pays(const Circuit& c, uint64_t span, double interp_ms, double patterns) {
     const NativeTier* t = native_tier();
     if (!t || t->refused(c, span, 1.0)) return false;
     // Margin on the building: its estimate is good to about a factor of 1.5.  A module load takes
     // 0.6 to 1.3 ms.
     const double cost = t->guess_run_ms(c, patterns) + 1.5 * (t->guess_build_ms(c) + 1.0);
-    if (interp_ms + c.interp_ms_spent.load(std::memory_order_relaxed) > cost) return true;
-    note_spent(c, interp_ms);
-    return false;
+    return interp_ms + c.interp_ms_spent.load(std::memory_order_relaxed) > cost;
 }
 
 // ---- circuits --------------------------------------------------------------

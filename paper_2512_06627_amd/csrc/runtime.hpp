@@ -86,7 +86,7 @@ struct Circuit {
         return g ? g : 1u;
     }
     double plan_ms = 0;
-    std::mutex mu;
+    mutable std::mutex mu;
     std::map<uint32_t, std::unique_ptr<Plan>> bundled;                  // bundle size -> plan
     std::map<std::pair<int, uint32_t>, Instr*> dev_prog;                  // (device, bundle) -> stream
     std::map<int, std::shared_ptr<JitKernel>> jit;                       // waves_per_eu -> kernel
@@ -386,7 +386,7 @@ struct NativeTier {
     std::shared_ptr<JitKernel> (*ready)(Circuit& c, uint64_t span);
     std::shared_ptr<JitKernel> (*get)(Circuit& c, uint64_t span, double weight, const std::atomic<bool>* stop);
     // Whether get() is known to return null for this span.
-    bool (*refused)(Circuit& c, uint64_t span, double weight);
+    bool (*refused)(const Circuit& c, uint64_t span, double weight);
     // The built kernel that is expected to be fastest over `r` in pieces of `span` half-words, whichever spans
     // it was built for; null when none is built.  *ms: its time there; *aim: what the kernel for this span could
     // take, *ms itself when it is that one, 0 when that one may share more work.
@@ -409,9 +409,9 @@ void register_sim_runner(SimRunner r);
 // Whether a native kernel pays for a circuit that has none for this span: the time of this check without it
 // (interp_ms: on the interpreter, or on a kernel made for other spans) plus what such checks of this circuit
 // have already taken since its last kernel exceeds the kernel's time and its building.  A circuit checked again and again thus spends at most about twice the better
-// of the two; one checked once is built only when that check alone pays.  Never for a span that get()
-// is known to refuse.
-bool native_pays(Circuit& c, uint64_t span, double interp_ms, double patterns);
+// of the two, when whoever runs them says what they took (note_spent); one checked once is built only when
+// that check alone pays.  Never for a span that get() is known to refuse.
+bool native_pays(const Circuit& c, uint64_t span, double interp_ms, double patterns);
 // Adds to what checks of the circuit have taken without the kernel that they would have.
 void note_spent(Circuit& c, double ms);
 

@@ -53,6 +53,7 @@ struct Job {
     bool no_native = false;          // the compile threads found no native kernel that fits
     bool compile_rtc = false;        // queued for a hipRTC kernel, not for a native one
     std::shared_ptr<JitKernel> jit;  // set when the specialized kernel is ready
+    bool lacks_kernel = false;       // runs without the native kernel that it could have
 };
 
 uint64_t env_u64(const char* name, uint64_t dflt) {
@@ -194,7 +195,10 @@ void fastlec_es_server::compile_loop() {
         auto publish = [&](size_t t) {  // with mu held; the job runs on, with its kernel or without
             Job* j = group[t];
             j->compiling = false;
-            if (ks[t] && ks[t]->code && !j->done) j->jit = ks[t];
+            if (ks[t] && ks[t]->code && !j->done) {
+                j->jit = ks[t];
+                j->lacks_kernel = false;
+            }
         };
         // Native kernels first: the job goes on at once, also where there is none.  Whether a hipRTC
         // kernel pays then is for the next step to say (plan_tiers).
@@ -274,6 +278,7 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
             const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
             if (have + kLaunchMs < plan + std::max(share, alone / (double)act.size())) j->jit = k;
             if (aim >= have) continue;
+            j->lacks_kernel = true;
             // One made for other spans runs the job until it has its own, if that pays.
             if (jit_mode == 1 && j->jit && native_pays(*j->c, slice_span(*j->c), have, left)) queue_compile(j, false);
             if (j->jit) continue;
@@ -287,6 +292,7 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
         if (nt && jit_mode == 1 && !j->no_native && !nt->refused(*j->c, slice_span(*j->c), kServerBuildWeight)) {
             const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
             const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
+            j->lacks_kernel = true;
             if (native_pays(*j->c, slice_span(*j->c), plan + share * (double)std::max<size_t>(1, sharing), left))
                 queue_compile(j, false);
             continue;
@@ -327,9 +333,13 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
     const uint32_t pass_hw = 64u * kK;
     // Tier of every job for this step (a compile thread may set a kernel meanwhile).
     std::vector<std::shared_ptr<JitKernel>> jk(act.size());
+    std::vector<uint8_t> lacks(act.size());
     {
         std::lock_guard<std::mutex> g(mu);
-        for (size_t t = 0; t < act.size(); ++t) jk[t] = act[t]->jit;
+        for (size_t t = 0; t < act.size(); ++t) {
+            jk[t] = act[t]->jit;
+            lacks[t] = act[t]->lacks_kernel;
+        }
     }
     const double target_np = rate * step_ms_target / 1e3;
     size_t n_interp = 0;
@@ -340,6 +350,7 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
     std::vector<uint32_t> lds_i, hbm_i;
     const size_t lds_blk = dev->prop.sharedMemPerBlock ? dev->prop.sharedMemPerBlock : 65536;
     double step_np = 0;
+    std::vector<double> np(act.size(), 0);  // the interpreted jobs' parts of it
     std::vector<HwRange> windows(act.size());
     std::vector<size_t> jit_jobs;
     for (size_t t = 0; t < act.size(); ++t) {
@@ -363,7 +374,8 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
         slice = (slice + pass_hw - 1) / pass_hw * pass_hw;
         HwRange w{j->cursor, std::min(j->range.end, j->cursor + slice)};
         windows[t] = w;
-        step_np += per_hw * (double)(w.end - w.begin);
+        np[t] = per_hw * (double)(w.end - w.begin);
+        step_np += np[t];
         // The first group runs in the register tier (or LDS when the caller fixes the schedule);
         // files too large for registers go to device memory, where more waves per CU fit.
         const bool fits = regs_tier_enabled() && !opts.wg_size && !opts.words_per_thread
@@ -510,6 +522,8 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
     for (size_t t = 0; t < act.size(); ++t) {
         Job* j = act[t];
         j->kernel_ms += jk[t] ? jit_ms / (double)jit_jobs.size() : ms;
+        // What the job took without a kernel of its own counts towards one (native_pays): its part of the step.
+        if (lacks[t]) note_spent(*j->c, jk[t] ? jit_ms / (double)jit_jobs.size() : ms * np[t] / step_np);
         const uint64_t b = best[j->slot];
         const uint32_t n = j->c->plan1.num_inputs;
         if (b != ~0ull) {

@@ -14,11 +14,13 @@
 //   * A launch without workgroups is refused, as by HIP.
 //
 // Switches for tests: FASTLEC_STANDIN_FAIL_LAUNCH=k fails the k-th kernel launch of the process (from 1),
-// FASTLEC_STANDIN_LAUNCH_US=t makes every launch take at least t microseconds, FASTLEC_STANDIN_TRACE=1
-// prints launches and waits.
+// FASTLEC_STANDIN_LAUNCH_US=t makes every launch take at least t microseconds,
+// FASTLEC_STANDIN_SLOW_CLOCK=k makes launches seem k times as fast, FASTLEC_STANDIN_TRACE=1 prints launches
+// and waits.
 #include <elf.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstdio>
@@ -103,9 +105,11 @@ hipError_t admit(uint64_t grid) {
     return hipSuccess;
 }
 
+// The device's clock, in ticks of 10 ns.
 uint64_t ticks() {
     using namespace std::chrono;
-    return (uint64_t)duration_cast<nanoseconds>(steady_clock::now().time_since_epoch()).count() / 10;
+    static const long slow = std::max(1l, env_long("FASTLEC_STANDIN_SLOW_CLOCK"));
+    return (uint64_t)duration_cast<nanoseconds>(steady_clock::now().time_since_epoch()).count() / 10 / (uint64_t)slow;
 }
 
 struct Function {

@@ -245,3 +245,21 @@ assert srv.stats()["max_active"] == 1
 assert cpu < 1.4 * wall + 0.02, (cpu, wall)
 srv.close()
 """)
+
+
+def test_server_counts_what_a_job_took(lib):
+    """Jobs of many small steps: what counts towards a native kernel is what the steps took, not all that is left
+    at each of them.  A job that is by the model some ten times too short for a kernel gets none, however
+    many steps it is cut into."""
+    r = run(lib, """
+c = load(miters.layered_cone_miter(7, 24, 300))
+p = es.fastlec_es_predict(c)
+srv = es.Server(1 << 34)
+for _ in range(2):
+    x = srv.poll(srv.submit(c), wait=True)
+    assert x["verdict"] == 0 and x["patterns_evaluated"] == 1 << 24, x
+print(p, srv.stats())
+assert srv.stats()["steps"] >= 500, srv.stats()
+srv.close()
+""", FASTLEC_ES_SERVER_RATE="1000000000", FASTLEC_ES_SERVER_STEP_MS="1", FASTLEC_STANDIN_SLOW_CLOCK="10000")
+    assert "native: " not in r.stderr, r.stdout + r.stderr[-2000:]
