@@ -14,6 +14,7 @@ namespace {
 
 struct Prepared {
     std::mutex mu;  // one call at a time
+    bool spoilt = false;  // a call failed: its control block is no longer known to be clean
     int device = 0;
     std::vector<uint64_t> key;
     std::vector<std::shared_ptr<JitKernel>> kernels;  // kept while their code may run
@@ -127,7 +128,9 @@ std::shared_ptr<Prepared> prepare(Device& dev, const std::vector<BatchPart>& par
     return b;
 }
 
-void drop(const std::shared_ptr<Prepared>& b) {
+// After a failed call.
+void give_up(const std::shared_ptr<Prepared>& b) {
+    b->spoilt = true;
     std::lock_guard<std::mutex> g(g_mu);
     auto& v = kept();
     v.erase(std::remove(v.begin(), v.end(), b), v.end());
@@ -135,25 +138,31 @@ void drop(const std::shared_ptr<Prepared>& b) {
 
 void run_batch(Device& dev, const std::vector<BatchPart>& parts, size_t n, hipStream_t stream,
                std::vector<uint64_t>& best, double* ms) {
-    std::vector<uint64_t> key = key_of(parts, n);
+    const std::vector<uint64_t> key = key_of(parts, n);
     std::shared_ptr<Prepared> b;
-    {
-        std::lock_guard<std::mutex> g(g_mu);
-        for (auto& x : kept())
-            if (x->device == dev.ordinal && x->key == key) b = x;
-        if (b) b->last_use = ++g_clock;
+    std::unique_lock<std::mutex> one;
+    for (;;) {
+        b = nullptr;
+        {
+            std::lock_guard<std::mutex> g(g_mu);
+            for (auto& x : kept())
+                if (x->device == dev.ordinal && x->key == key) b = x;
+            if (b) b->last_use = ++g_clock;
+        }
+        if (!b) {
+            b = prepare(dev, parts, n, stream, key);
+            std::lock_guard<std::mutex> g(g_mu);
+            auto& v = kept();
+            if (v.size() >= kMaxPrepared)
+                v.erase(std::min_element(v.begin(), v.end(),
+                                         [](const auto& x, const auto& y) { return x->last_use < y->last_use; }));
+            b->last_use = ++g_clock;
+            v.push_back(b);
+        }
+        one = std::unique_lock<std::mutex>(b->mu);
+        if (!b->spoilt) break;  // another thread's call failed meanwhile
+        one.unlock();
     }
-    if (!b) {
-        b = prepare(dev, parts, n, stream, std::move(key));
-        std::lock_guard<std::mutex> g(g_mu);
-        auto& v = kept();
-        if (v.size() >= kMaxPrepared)
-            v.erase(std::min_element(v.begin(), v.end(),
-                                     [](const auto& x, const auto& y) { return x->last_use < y->last_use; }));
-        b->last_use = ++g_clock;
-        v.push_back(b);
-    }
-    std::lock_guard<std::mutex> one(b->mu);
     uint8_t *host = (uint8_t*)b->buf.host, *devp = (uint8_t*)b->buf.dev;
     unsigned long long* const found = (unsigned long long*)(host + b->best_off);
     double t = 0;
@@ -167,7 +176,7 @@ void run_batch(Device& dev, const std::vector<BatchPart>& parts, size_t n, hipSt
                               (unsigned long long*)(devp + b->best_off), (uint32_t)n, found, stream));
         t = wait_finished(found + n, stream);
     } catch (...) {
-        drop(b);  // its control block is no longer known to be clean
+        give_up(b);
         throw;
     }
     if (ms) *ms = t;

@@ -14,7 +14,7 @@
 //   * A launch without workgroups is refused, as by HIP.
 //
 // Switches for tests: FASTLEC_STANDIN_FAIL_LAUNCH=k fails the k-th kernel launch of the process (from 1),
-// FASTLEC_STANDIN_LAUNCH_US=t makes every launch take at least t microseconds,
+// FASTLEC_STANDIN_LAUNCH_US=t makes every launch, and the call of one that fails, take t microseconds more,
 // FASTLEC_STANDIN_SLOW_CLOCK=k makes launches seem k times as fast, FASTLEC_STANDIN_TRACE=1 prints launches
 // and waits.
 #include <elf.h>
@@ -98,6 +98,7 @@ hipError_t admit(uint64_t grid) {
     static const long fail = env_long("FASTLEC_STANDIN_FAIL_LAUNCH");
     if (grid == 0) return hipErrorInvalidConfiguration;
     if (g_launches.fetch_add(1) + 1 == fail) {
+        std::this_thread::sleep_for(std::chrono::microseconds(env_long("FASTLEC_STANDIN_LAUNCH_US")));
         note("launch refused");
         return hipErrorLaunchFailure;
     }
@@ -110,6 +111,15 @@ uint64_t ticks() {
     using namespace std::chrono;
     static const long slow = std::max(1l, env_long("FASTLEC_STANDIN_SLOW_CLOCK"));
     return (uint64_t)duration_cast<nanoseconds>(steady_clock::now().time_since_epoch()).count() / 10 / (uint64_t)slow;
+}
+
+// A launch finds its claim counters at zero and leaves them used.
+void claim(unsigned long long* counters) {
+    using namespace fes;
+    for (uint32_t i = 0; i < kClaimCounters; ++i)
+        if (counters[i * kClaimStride]) std::fprintf(stderr, "standin: claim counter %u is not zero\n", i);
+    counters[0] = 64;
+    counters[kStartWord] = ticks();
 }
 
 struct Function {
@@ -130,7 +140,7 @@ const uint32_t* generated_code(const char* module) {
 
 void run_native(const char* module, const fes::NativeLaunch& L) {
     const char* code = (const char*)generated_code(module);
-    L.counters[fes::kStartWord] = ticks();
+    claim(L.counters);
     const fes::NativeDesc* cones = L.cones ? L.cones : &L.one;
     for (uint32_t k = 0; k < L.num_cones; ++k) {
         const fes::NativeDesc& c = cones[k];
@@ -205,7 +215,7 @@ hipError_t queue_interp(const InterpLaunch& L, int grid, Launch launch) {
     Queue::get().add([L, launch] {
         InterpLaunch x = L;
         if (!x.cones) x.cones = &x.one;
-        x.ctl->next_item[kStartWord] = ticks();
+        claim(x.ctl->next_item);
         (void)launch(x);
     });
     return hipSuccess;

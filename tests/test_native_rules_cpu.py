@@ -263,3 +263,25 @@ assert srv.stats()["steps"] >= 500, srv.stats()
 srv.close()
 """, FASTLEC_ES_SERVER_RATE="1000000000", FASTLEC_ES_SERVER_STEP_MS="1", FASTLEC_STANDIN_SLOW_CLOCK="10000")
     assert "native: " not in r.stderr, r.stdout + r.stderr[-2000:]
+
+
+def test_threads_with_one_batch_when_a_call_fails(lib):
+    """Two threads run the same batch and meet on what is kept for it; the first one's finish kernel is refused.  The
+    other one does not use the claim counters that it left."""
+    r = run(lib, """
+import threading
+cs = [load(miters.layered_cone_miter(50 + i, 12, 300, fault_seed=2)) for i in range(2)]
+cs += [load(miters.layered_cone_miter(60 + i, 12, 12000, fault_seed=2)) for i in range(2)]
+want = [(x["verdict"], x["cex"]) for x in es.fastlec_es_check_batch(cs, kernel="interp")]  # launches 1 and 2
+errors, good = [], []
+def call():
+    try:
+        good.append([(x["verdict"], x["cex"]) for x in es.fastlec_es_check_batch(cs, kernel="interp")])
+    except es.EsError as e:
+        errors.append(e)
+threads = [threading.Thread(target=call) for _ in range(2)]
+[t.start() for t in threads]
+[t.join() for t in threads]
+assert len(errors) == 1 and good == [want], (errors, good)
+""", FASTLEC_STANDIN_FAIL_LAUNCH="4", FASTLEC_STANDIN_LAUNCH_US="50000", FASTLEC_STANDIN_TRACE="1")
+    assert "launch refused" in r.stderr and "not zero" not in r.stderr, r.stderr[-2000:]
