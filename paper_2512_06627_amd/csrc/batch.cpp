@@ -128,12 +128,15 @@ std::shared_ptr<Prepared> prepare(Device& dev, const std::vector<BatchPart>& par
     return b;
 }
 
-// After a failed call.
-void give_up(const std::shared_ptr<Prepared>& b) {
+// After a failed call: launches of it may still run, on memory and code that b holds.
+void give_up(const std::shared_ptr<Prepared>& b, hipStream_t stream) {
     b->spoilt = true;
-    std::lock_guard<std::mutex> g(g_mu);
-    auto& v = kept();
-    v.erase(std::remove(v.begin(), v.end(), b), v.end());
+    {
+        std::lock_guard<std::mutex> g(g_mu);
+        auto& v = kept();
+        v.erase(std::remove(v.begin(), v.end(), b), v.end());
+    }
+    if (hipStreamSynchronize(stream) != hipSuccess) new std::shared_ptr<Prepared>(b);  // kept for good
 }
 
 void run_batch(Device& dev, const std::vector<BatchPart>& parts, size_t n, hipStream_t stream,
@@ -176,7 +179,7 @@ void run_batch(Device& dev, const std::vector<BatchPart>& parts, size_t n, hipSt
                               (unsigned long long*)(devp + b->best_off), (uint32_t)n, found, stream));
         t = wait_finished(found + n, stream);
     } catch (...) {
-        give_up(b);
+        give_up(b, stream);
         throw;
     }
     if (ms) *ms = t;

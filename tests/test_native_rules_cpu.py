@@ -265,6 +265,25 @@ srv.close()
     assert "native: " not in r.stderr, r.stdout + r.stderr[-2000:]
 
 
+def test_a_failing_batch_waits_for_its_launches(lib):
+    """A batch's second launch (its finish kernel) is refused while the first one runs: what they read on the device goes back to
+    the pool only when nothing runs any more, and the same batch works again."""
+    r = run(lib, """
+cs = [load(miters.layered_cone_miter(50 + i, 12, 300, fault_seed=2)) for i in range(2)]
+cs += [load(miters.layered_cone_miter(60 + i, 12, 12000, fault_seed=2)) for i in range(2)]
+try:
+    es.fastlec_es_check_batch(cs, kernel="interp")
+    assert False
+except es.EsError as e:
+    print("failed", file=sys.stderr, flush=True)
+want = [es.fastlec_es_check(c, kernel="interp") for c in cs]
+got = es.fastlec_es_check_batch(cs, kernel="interp")
+assert [(x["verdict"], x["cex"]) for x in got] == [(x["verdict"], x["cex"]) for x in want]
+""", FASTLEC_STANDIN_FAIL_LAUNCH="2", FASTLEC_STANDIN_LAUNCH_US="50000", FASTLEC_STANDIN_TRACE="1")
+    during = r.stderr.split("failed")[0]
+    assert "launch refused" in during and "synchronize" in during.split("launch refused")[1], during[-1500:]
+
+
 def test_threads_with_one_batch_when_a_call_fails(lib):
     """Two threads run the same batch and meet on what is kept for it; the first one's finish kernel is refused.  The
     other one does not use the claim counters that it left."""
