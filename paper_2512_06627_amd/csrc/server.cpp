@@ -112,9 +112,10 @@ struct fastlec_es_server {
     std::string fatal;
     int fatal_code = 0;
 
-    // device job table: [ctl lds][ctl hbm][ctl specialized x capacity][best x capacity][ticks]
+    // device job table: [ctl lds][ctl hbm][ctl specialized x capacity][best x capacity]
     // [desc lds x capacity][desc hbm x capacity].  Between steps every control word is zero and every best
-    // all ones: each step ends with the finish kernel (in host-only builds with copies).
+    // all ones: each step ends with the finish kernel (in host-only builds with copies), which puts the
+    // best values and its ticks where the control words would be on the host.
     Buffer table;
     size_t off_ctl_jit = 2 * sizeof(LaunchCtl), off_best = 0, off_desc_lds = 0, off_desc_hbm = 0;
     Buffer files;  // value files of the device-memory tier
@@ -495,10 +496,11 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
         if (events) FES_HIP(hipEventRecord(ev[2].e, stream));
     }
     float ms = 0, jit_ms = 0;
+    const uint64_t* const best = (const uint64_t*)(host + (finish_kernel ? 0 : off_best));
     if (finish_kernel) {
         uint32_t n = 0;
         for (Job* j : act) n = std::max(n, j->slot + 1);
-        unsigned long long* const found = (unsigned long long*)(host + off_best);
+        unsigned long long* const found = (unsigned long long*)best;
         __atomic_store_n(found + n, kPending, __ATOMIC_RELEASE);
         FES_HIP(finish_kernel((unsigned long long*)devp, (uint32_t)(ctl_bytes / 8), (unsigned long long*)(devp + off_best),
                               n, found, stream));
@@ -513,7 +515,6 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
     if (n_interp && ms > 0.5f) rate = 0.7 * rate + 0.3 * (step_np / (ms / 1e3));
     if (jit_np > 0 && jit_ms > 0.5f) jit_rate = 0.7 * jit_rate + 0.3 * (jit_np / (jit_ms / 1e3));
 
-    const uint64_t* best = (const uint64_t*)(host + off_best);
     const double now = now_ms();
     std::lock_guard<std::mutex> g(mu);
     st.steps++;
@@ -672,7 +673,7 @@ int fastlec_es_server_create(const fastlec_es_options* opts, size_t budget_bytes
         s->stream = s->opts.hip_stream ? (hipStream_t)s->opts.hip_stream : s->dev->stream;
         s->jit_mode = (int)std::min<uint64_t>(2, env_u64("FASTLEC_ES_SERVER_JIT", 1));
         s->off_best = s->off_ctl_jit + kClaimBytes * kCapacity;
-        s->off_desc_lds = (s->off_best + 8ull * (kCapacity + 1) + 255) & ~size_t(255);
+        s->off_desc_lds = (s->off_best + 8ull * kCapacity + 255) & ~size_t(255);
         s->off_desc_hbm = s->off_desc_lds + sizeof(ConeDesc) * kCapacity;
         s->table = s->dev->acquire(s->off_desc_hbm + sizeof(ConeDesc) * kCapacity);
         if (s->table.bytes >= budget_bytes) {

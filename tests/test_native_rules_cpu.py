@@ -304,3 +304,22 @@ threads = [threading.Thread(target=call) for _ in range(2)]
 assert len(errors) == 1 and good == [want], (errors, good)
 """, FASTLEC_STANDIN_FAIL_LAUNCH="4", FASTLEC_STANDIN_LAUNCH_US="50000", FASTLEC_STANDIN_TRACE="1")
     assert "launch refused" in r.stderr and "not zero" not in r.stderr, r.stderr[-2000:]
+
+
+def test_server_budget_just_above_the_job_table(lib):
+    """The table is 551 pages of device memory; every budget above that is accepted, and jobs run in it."""
+    run(lib, """
+table = 551 * 4096
+try:
+    es.Server(table)
+    assert False
+except es.EsError as e:
+    assert e.code == es.FASTLEC_ERR_INVALID
+srv = es.Server(table + 1)
+cs = [load(miters.layered_cone_miter(70 + i, 12, 300, fault_seed=i or None)) for i in range(4)]
+want = [es.fastlec_es_check(c, kernel="interp") for c in cs]
+got = [srv.poll(t, wait=True) for t in [srv.submit(c) for c in cs]]
+assert [(x["verdict"], x["cex"]) for x in got] == [(x["verdict"], x["cex"]) for x in want]
+assert srv.stats()["device_bytes"] == table
+srv.close()
+""")
