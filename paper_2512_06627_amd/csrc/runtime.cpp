@@ -352,7 +352,7 @@ void Device::release(Buffer b) {
     free_bufs.push_back(b);
 }
 
-ControlSlot Device::acquire_slot() {
+ControlSlot Device::acquire_slot(hipStream_t caller) {
     {
         std::lock_guard<std::mutex> g(mu);
         if (!free_slots.empty()) {
@@ -368,8 +368,9 @@ ControlSlot Device::acquire_slot() {
     std::memset((uint8_t*)b.host + kClaimBytes, 0xFF, 8);
     ControlSlot s;
     s.dev = (uint8_t*)b.dev;
-    FES_HIP(hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream));
-    FES_HIP(hipStreamSynchronize(stream));
+    // On the caller's stream: the library's own may be busy with another thread's check.
+    FES_HIP(hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, caller));
+    FES_HIP(hipStreamSynchronize(caller));
     s.host_best = (unsigned long long*)b.host;
     return s;
 }
@@ -399,7 +400,7 @@ uint64_t run_on_slot(Device& dev, hipStream_t stream, double* kernel_ms,
     // kernel and kept events 22; the kernels' own start time and polling 8.5 (waiting for
     // the stream 13.5).  What earlier kernels of the call wrote is visible with that store: the finish
     // kernel comes after them on the stream, and its release is at system scope.
-    const ControlSlot s = dev.acquire_slot();
+    const ControlSlot s = dev.acquire_slot(stream);
     unsigned long long* const ticks = s.host_best + 1;
     __atomic_store_n(ticks, kPending, __ATOMIC_RELEASE);
     launch(s);

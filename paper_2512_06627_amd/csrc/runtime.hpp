@@ -166,7 +166,7 @@ struct Device {
     // Control slots (at most one per concurrent check is ever made).  Only a slot whose finish kernel
     // has run goes back; a slot of a failed call is dropped.
     std::vector<ControlSlot> free_slots;
-    ControlSlot acquire_slot();
+    ControlSlot acquire_slot(hipStream_t stream);
     void release_slot(const ControlSlot& s);
     // Device address of the no-allocation entry point's static scratch array on this device
     // (looked up once, at set-up, with this device current).

@@ -162,9 +162,11 @@ void run_native(const char* module, const fes::NativeLaunch& L) {
 
 extern "C" {
 
-hipError_t hipStreamSynchronize(hipStream_t) {
+hipError_t hipStreamSynchronize(hipStream_t stream) {
     Queue::get().drain();
-    note("synchronize");
+    char what[64];
+    std::snprintf(what, sizeof what, "synchronize %p", (void*)stream);
+    note(what);
     return hipSuccess;
 }
 hipError_t hipFree(void* p) {

@@ -323,3 +323,19 @@ assert [(x["verdict"], x["cex"]) for x in got] == [(x["verdict"], x["cex"]) for 
 assert srv.stats()["device_bytes"] == table
 srv.close()
 """)
+
+
+def test_calls_wait_on_their_own_stream(lib):
+    """Checks, batches and explicit kernels on a stream of the caller wait for no other one (the library's may be
+    busy with another thread's check), from the first call on."""
+    r = run(lib, """
+c = load(miters.layered_cone_miter(80, 12, 300, fault_seed=1))
+want = None
+for kernel in ("interp", "specialized", "auto"):
+    x = es.fastlec_es_check(c, kernel=kernel, stream=0x7000)
+    y = es.fastlec_es_check_batch([c, c], kernel=kernel, stream=0x7000)
+    want = want or (x["verdict"], x["cex"])
+    assert all((z["verdict"], z["cex"]) == want for z in [x] + y)
+""", FASTLEC_STANDIN_TRACE="1")
+    waits = [ln.split()[-1] for ln in r.stderr.splitlines() if ln.startswith("standin: synchronize")]
+    assert waits and set(waits) == {"0x7000"}, waits
