@@ -64,7 +64,8 @@ hipError_t launch_interp_sim(const InterpLaunch& L, int K, int B, bool lds, int 
 
 // Per row of a signature matrix (rows x words, row-major): the number of ones and the
 // complement-normalised hash sum_k word'_k * (fmix32(k) | 1) mod 2^64, where word' is the
-// row complemented when its first bit is 1.  One wave per row, grid-stride over rows.
+// row complemented when its first bit is 1.  A workgroup of up to 16 waves per group of one or two rows
+// (rsim.hip); cus: the device's CUs.
 hipError_t launch_signature_hash(const uint32_t* sig, uint64_t rows, uint64_t words, uint64_t* hash,
                                  uint64_t* ones, int cus, hipStream_t stream);
 
@@ -92,8 +93,8 @@ void encode_sim_stream(const Plan& p, std::vector<uint32_t>& out, uint32_t* gate
 // 2^30), simulated once each; `regs` as for launch_interp_regs.
 hipError_t launch_sim_regs(const InterpLaunch& L, int regs, int grid, hipStream_t stream);
 
-// Register tier: value files in VGPRs (one wave per workgroup, bundles of 4, one 32-bit word per
-// lane).  interp_regs_rows: the file size (104, 144 or 232 rows) that holds `rows`, 0 if none
+// Register tier: value files in VGPRs (bundles of 4, one 32-bit word per lane; workgroups of one wave for a
+// launch of one cone, of eight for several; `grid` counts waves).  interp_regs_rows: the file size (104, 144 or 232 rows) that holds `rows`, 0 if none
 // does, with the waves per SIMD it allows.  launch_interp_regs: `regs` is that file size.
 int interp_regs_rows(uint32_t rows, int* waves_per_simd);
 hipError_t launch_interp_regs(const InterpLaunch& L, int regs, int grid, hipStream_t stream);

@@ -26,9 +26,10 @@ double clock_ms() {
 constexpr double kMsPerWaveInstr = 1.0e-9, kMsPerLoneInstr = 2.1e-6, kBuildMsPerGate = 0.8e-3;
 constexpr double kLutsPerSharedGate = 0.26;
 constexpr double kChipWaves = 256 * 4 * 2;
-// A pass that shares work is not made longer than this: the 16x16 miter's 8,519 instructions with
-// five inner inputs still beat four (0.72 against 0.77 ms), though beyond 64 KB they stream through
-// the instruction cache.
+// A pass that shares work is not made longer than this: beyond 64 KB it streams through the instruction
+// cache.  16x16 miter, 2^32 patterns: 8,519 instructions with five inner inputs, two waves per SIMD, 0.71 ms;
+// 5,055 with four, three waves, 0.77.  MAC8: 5,368 with five 0.48 ms, 2,468 with four 0.43.  The estimate
+// below takes four for both.
 constexpr double kMaxSharedValu = 9000;
 // Registers of the mapped and reordered program against values alive at once in the graph (0.5 to
 // 0.75 on multipliers, up to 0.97 on layered cones).

@@ -186,7 +186,7 @@ struct Schedule {
     uint64_t tile_hw = 0;  // 0 = derived
     bool lds = true;
     int grid = 0;          // 0 = derived (persistent: fill the chip)
-    int regs = 0;          // register tier: value-file rows in VGPRs (K 1, B 4, one wave per workgroup)
+    int regs = 0;          // register tier: value-file rows in VGPRs (K 1, B 4, block 64: grid = waves)
 };
 // Launch the interpreter kernel a schedule names (register, LDS or device-memory tier).
 hipError_t launch_schedule(const InterpLaunch& L, const Schedule& sch, hipStream_t stream);
@@ -303,7 +303,7 @@ void run_sim(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32
 // cone's range and cached per device and batch shape.
 Schedule autotune(Device& dev, const std::vector<Circuit*>& cs, const std::vector<HwRange>& ranges, hipStream_t stream,
                   bool hbm);
-// A batch of one interpreter launch.
+// A batch of one interpreter launch (no graph: launches of prepared descriptors, see batch.cpp).
 void run_batch_graph(Device& dev, const std::vector<Circuit*>& cs, const std::vector<HwRange>& ranges,
                      const Schedule& sch, hipStream_t stream, std::vector<uint64_t>& best, double* ms);
 

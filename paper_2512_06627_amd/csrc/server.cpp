@@ -62,9 +62,14 @@ uint64_t env_u64(const char* name, uint64_t dflt) {
     return std::strtoull(v, nullptr, 0);
 }
 
-// Half-words of a job that one native slice covers: its whole space, or a sixteenth of it (a slice
-// is about a step of work, so large jobs run as many slices and their kernel's inner inputs must
-// fit in one).
+// Half-words that a job's native kernel is built for: its whole space up to 26 inputs (a first slice of 2e13
+// gate evaluations holds those of 300,000 gates), a sixteenth of it above.  A slice is covered in whole blocks of
+// patterns up to the highest inner input, so that a job of several slices on its whole space's kernel may go
+// through the space once for each.  Milliseconds for a burst that has been served before, a sixteenth against
+// the whole: 17x17 miter alone 13.7 to 14.4 against 3.8 to 8.1 (its first burst 26 against 31), 17x17, 16x16 and
+// 15x15 miters 17.6 against 9.2, 16x16 and MAC8 4.6 against 1.9, 16 layered cones of 27 to 34 inputs 21.7
+// against 20.3 and 86 against 86; a quarter in place of a sixteenth 9, 12.6, 4.0, 20.9 and 86.  So the line is on the
+// safe side: it costs arithmetic jobs of one or two slices up to two thirds of their shared work.
 uint64_t slice_span(const Circuit& c) {
     const uint32_t n = c.plan1.num_inputs;
     const uint64_t whole = n >= 5 ? 1ull << (n - 5) : 1ull;

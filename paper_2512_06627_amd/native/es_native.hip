@@ -20,8 +20,8 @@
 // The pass is bound by VALU issue (one v_bitop3_b32 per three-input LUT; a wave issues at most one
 // every five clocks, a SIMD one every two): one wave per workgroup, and as many of two to four waves
 // per SIMD as the pass's registers allow.  16x16 miter without inner inputs, 2^32 patterns: 2.96 ms
-// at four waves (1.10e12 instructions a second), 3.05 at three, 3.48 at two; with five inner inputs
-// 0.72 ms at two.
+// at four waves (1.10e12 instructions a second), 3.05 at three, 3.48 at two; with the four inner inputs
+// that the library takes 0.77 ms at three (0.68 in calls one after the other), with five 0.71 at two.
 //
 // Contract with the generated code.  Inputs: v2..v7 lane words of inputs 5..10, v8 byte address
 // of the lane's first LDS spill slot, s[38:39] packed half-word index, s[48:49] fes_native_report,
