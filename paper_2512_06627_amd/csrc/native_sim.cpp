@@ -59,7 +59,7 @@ bool run(Device& dev, Circuit& c, const uint32_t* pi, uint64_t words, uint32_t* 
         const double spent = c.sim_ms_spent.load(std::memory_order_relaxed) + interp;
         c.sim_ms_spent.store(spent, std::memory_order_relaxed);
         if (spent < 1.5 * (kBuildMs * gates + kLoadMs)) return false;
-        std::lock_guard<std::mutex> one(c.native_mu);
+        std::lock_guard<std::mutex> one(c.native_sim_mu);
         {
             std::lock_guard<std::mutex> g(c.mu);
             k = c.native_sim;

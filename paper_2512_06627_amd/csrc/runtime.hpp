@@ -92,7 +92,7 @@ struct Circuit {
     std::map<int, std::shared_ptr<JitKernel>> jit;                       // waves_per_eu -> kernel
     std::map<uint32_t, std::shared_ptr<JitKernel>> native;               // inner-input limit -> native kernel
     std::map<uint32_t, bool> native_refused;                             // limits without one (see native.cpp)
-    std::mutex native_mu;                                                 // one native build at a time
+    std::mutex native_mu, native_sim_mu;                                 // one native build of a kind at a time
     std::atomic<double> interp_ms_spent{0};                               // see native_pays
     std::unique_ptr<LutProgram> lut;                                      // specialized-kernel program
     std::map<uint32_t, std::unique_ptr<Plan>> sim;                        // bundle -> simulation plan

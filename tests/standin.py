@@ -2,8 +2,8 @@
 (tests/sanitize/): as a shared library for the package, or as a program with a sanitizer.
 
 The stand-in runs interpreter launches from the descriptors and streams that the kernels read, native
-launches by executing the generated machine code, and the finish kernel on a thread of its own.  It has
-no simulation, hashing or autotuning.
+launches by executing the generated machine code, and the finish kernel on a thread of its own.  Its
+simulations and hashes plan and build like the library's and then fail, and it has no autotuning.
 """
 import concurrent.futures
 import os
@@ -16,7 +16,7 @@ CSRC = os.path.join(ROOT, "paper_2512_06627_amd", "csrc")
 SAN = os.path.join(ROOT, "tests", "sanitize")
 CLANG = "/opt/rocm/llvm/bin/clang++"
 HOST_SOURCES = ("aig", "batch", "capi", "cofactor", "emit_block", "lut", "model", "native", "native_build",
-                "native_emit", "plan", "runtime", "server", "sweep")
+                "native_emit", "native_sim", "native_sim_emit", "plan", "runtime", "server", "sweep")
 # Functions of fake_device.cpp that native_device.cpp replaces and calls, by their second name.
 SECOND_NAMES = {"launch_interp(": "standin_interp", "launch_interp_regs(": "standin_regs",
                 "jit_prepare(": "standin_prepare", "jit_enqueue(": "standin_enqueue"}

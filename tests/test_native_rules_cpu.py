@@ -201,6 +201,33 @@ for _ in range(300):
     assert len(made) == 1, (made, after[-2000:])
 
 
+def test_simulations_do_not_wait_for_a_check_s_kernel(lib):
+    """A thread simulates a circuit while another one builds its native kernel (0.2 s and more); the stand-in
+    has no simulation, so that every call ends at its launch, but none comes late."""
+    run(lib, """
+import ctypes, threading
+c = load(chain(60000, 32))
+sig = ctypes.addressof(ctypes.create_string_buffer(64))
+def simulate():
+    t = time.perf_counter()
+    try:
+        es.fastlec_es_simulate(c, sig, 64, sig)
+        assert False
+    except es.EsError:
+        return time.perf_counter() - t
+simulate()  # plans
+t = threading.Thread(target=lambda: es.fastlec_es_native_info(c))
+start = time.perf_counter()
+t.start()
+late = []
+while t.is_alive():
+    late.append(simulate())
+    time.sleep(0.001)
+build = time.perf_counter() - start
+assert len(late) > 20 and max(late) < 0.4 * build, (build, len(late), max(late))
+""")
+
+
 def test_server_jobs_without_native_kernel_are_interpreted(lib):
     """Jobs of a cone for which no native kernel fits: eight at a time are by the model worth a native kernel (its
     first pattern fails, which the model does not know) and not a hipRTC compile, so none is compiled and all
