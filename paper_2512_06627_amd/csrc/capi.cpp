@@ -486,9 +486,10 @@ int fastlec_es_check_batch(const fastlec_es_circuit* const* cs, size_t k, const 
                     now = t->share_ms(*have, patterns);
                     plan = 0;
                 }
-                if (exact || t->refused(c, span, kBatchBuildWeight)) continue;
+                if (exact) continue;
                 const double net = now + c.interp_ms_spent.load(std::memory_order_relaxed) +
                                    (plan - 1.5 * t->guess_build_ms(c)) / threads;
+                if (net > 0 && t->refused(c, span, kBatchBuildWeight)) continue;
                 if (net > 0) gain += net;
                 fresh.push_back({i, now, net > 0});
             }

@@ -73,6 +73,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const s
         bool& all = c.native_refused[limit];
         all = all || weight <= 0;
         c.interp_ms_spent.store(0, std::memory_order_relaxed);  // it has bought this
+        c.serve_ms_waited.store(0, std::memory_order_relaxed);
         return nullptr;
     }
     auto k = std::make_shared<JitKernel>();
@@ -88,6 +89,7 @@ std::shared_ptr<JitKernel> get(Circuit& c, uint64_t span, double weight, const s
     std::lock_guard<std::mutex> g(c.mu);
     c.native[limit] = k;
     c.interp_ms_spent.store(0, std::memory_order_relaxed);
+    c.serve_ms_waited.store(0, std::memory_order_relaxed);
     return k;
 }
 

@@ -70,11 +70,13 @@ const NativeTier* native_tier() {
     return on ? g_native_tier : nullptr;
 }
 
-void note_spent(Circuit& c, double ms) {
-    double spent = c.interp_ms_spent.load(std::memory_order_relaxed);
-    while (!c.interp_ms_spent.compare_exchange_weak(spent, spent + ms, std::memory_order_relaxed)) {
+void add_ms(std::atomic<double>& to, double ms) {
+    double was = to.load(std::memory_order_relaxed);
+    while (!to.compare_exchange_weak(was, was + ms, std::memory_order_relaxed)) {
     }
 }
+
+void note_spent(Circuit& c, double ms) { add_ms(c.interp_ms_spent, ms); }
 
 bool native_pays(const Circuit& c, uint64_t span, double interp_ms, double patterns) {
     const NativeTier* t = native_tier();

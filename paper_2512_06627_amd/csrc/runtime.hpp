@@ -94,6 +94,7 @@ struct Circuit {
     std::map<uint32_t, bool> native_refused;                             // limits without one (see native.cpp)
     std::mutex native_mu, native_sim_mu;                                 // one native build of a kind at a time
     std::atomic<double> interp_ms_spent{0};                               // see native_pays
+    std::atomic<double> serve_ms_waited{0};                               // served jobs, beyond that (server.cpp)
     std::unique_ptr<LutProgram> lut;                                      // specialized-kernel program
     std::map<uint32_t, std::unique_ptr<Plan>> sim;                        // bundle -> simulation plan
     std::map<std::pair<int, uint32_t>, Instr*> dev_sim_prog;              // (device, bundle) -> stream
@@ -414,6 +415,7 @@ void register_sim_runner(SimRunner r);
 bool native_pays(const Circuit& c, uint64_t span, double interp_ms, double patterns);
 // Adds to what checks of the circuit have taken without the kernel that they would have.
 void note_spent(Circuit& c, double ms);
+void add_ms(std::atomic<double>& to, double ms);
 
 // The per-pass body as one asm statement with planner-assigned registers (v0.., s<sgpr_base>..).
 // Returns false, with the register counts in stats, when it needs more than the limits.

@@ -299,7 +299,8 @@ void fastlec_es_server::plan_tiers(const std::vector<Job*>& act) {
             const double share = model_interp_share_ms(j->c->interp_gates(), j->c->interp_rows_guess(), left);
             const double plan = j->c->planned(4) ? 0.0 : kPlanMsPerGate * j->c->plan1.num_ands_tfi;
             j->lacks_kernel = true;
-            if (native_pays(*j->c, slice_span(*j->c), plan + share * (double)std::max<size_t>(1, sharing), left))
+            const double waited = j->c->serve_ms_waited.load(std::memory_order_relaxed);
+            if (native_pays(*j->c, slice_span(*j->c), waited + plan + share * (double)std::max<size_t>(1, sharing), left))
                 queue_compile(j, false);
             continue;
         }
@@ -528,8 +529,14 @@ void fastlec_es_server::step(const std::vector<Job*>& act) {
     for (size_t t = 0; t < act.size(); ++t) {
         Job* j = act[t];
         j->kernel_ms += jk[t] ? jit_ms / (double)jit_jobs.size() : ms;
-        // What the job took without a kernel of its own counts towards one (native_pays): its part of the step.
-        if (lacks[t]) note_spent(*j->c, jk[t] ? jit_ms / (double)jit_jobs.size() : ms * np[t] / step_np);
+        // What the job took without a kernel of its own counts towards one (native_pays): its part of the step
+        // for every caller, all of the launch that it waited for when the server asks.
+        if (lacks[t]) {
+            const double launch = jk[t] ? jit_ms : ms;
+            const double part = jk[t] ? jit_ms / (double)jit_jobs.size() : ms * np[t] / step_np;
+            note_spent(*j->c, part);
+            add_ms(j->c->serve_ms_waited, launch - part);
+        }
         const uint64_t b = best[j->slot];
         const uint32_t n = j->c->plan1.num_inputs;
         if (b != ~0ull) {
